@@ -172,8 +172,8 @@ nc_status nc_quantize_cdf24(const float* probs, uint32_t rows, uint32_t vocab, u
  * capture, serving loops, harnesses that forbid hipMalloc): same arguments, same integers, but
  * its kernels take their workspace from a fixed device array of 65,536 segment partials
  * (1 MiB per GPU, held until the process ends) instead of a library-allocated buffer; it calls
- * no hipMalloc or hipFree.  The workspace is needed on the segment path (up to 64 rows, rows not
- * 16-byte aligned or with vocab not a multiple of 4, or vocab > 49,152): there rows *
+ * no hipMalloc or hipFree.  The array is used for up to 64 rows, rows not
+ * 16-byte aligned or with vocab not a multiple of 4, or vocab > 49,152: there rows *
  * ceil(vocab / 4096) must not exceed 65,536, else NC_E_CAPACITY and nothing is launched.  Every
  * call on one GPU shares that GPU's array (nothing in it needs clearing between calls), so two
  * calls whose work overlaps on one GPU -- on different streams, or from different threads --
@@ -328,6 +328,20 @@ nc_status nc_ensemble_backward(const float* z, float* b, float* theta, const flo
                                const int32_t* target, const float* grad_loss, uint32_t rows,
                                uint32_t vocab, uint32_t n_experts, float lr, float* grad_b,
                                float* grad_theta, void* stream);
+
+/* The same pair for callers that keep the rows' logsumexp between the two calls: the forward also
+ * writes lse[r] = logsumexp(z_r + b) (device, rows), and the backward takes it instead of reading
+ * z a second time for it (z and b must be unchanged in between).  grad_loss may be NULL: a
+ * gradient of one for every row.  The backward uses no workspace. */
+nc_status nc_ensemble_forward_lse(const float* z, const float* b, const float* theta,
+                                  const float* P, const int32_t* target, uint32_t rows,
+                                  uint32_t vocab, uint32_t n_experts, float* loss, float* resp,
+                                  float* lse, void* stream);
+nc_status nc_ensemble_backward_lse(const float* z, float* b, float* theta, const float* resp,
+                                   const float* lse, const int32_t* target,
+                                   const float* grad_loss, uint32_t rows, uint32_t vocab,
+                                   uint32_t n_experts, float lr, float* grad_b,
+                                   float* grad_theta, void* stream);
 
 /* Thread-local message of the last error on this thread ("" if none). */
 const char* nc_last_error(void);

@@ -92,6 +92,10 @@ _SIG = {
                                       _P, _P, _P, _P]),
     "nc_ensemble_backward": (C.c_int, [_P, _P, _P, _P, _P, _P, C.c_uint32, C.c_uint32,
                                        C.c_uint32, C.c_float, _P, _P, _P]),
+    "nc_ensemble_forward_lse": (C.c_int, [_P, _P, _P, _P, _P, C.c_uint32, C.c_uint32, C.c_uint32,
+                                          _P, _P, _P, _P]),
+    "nc_ensemble_backward_lse": (C.c_int, [_P, _P, _P, _P, _P, _P, _P, C.c_uint32, C.c_uint32,
+                                           C.c_uint32, C.c_float, _P, _P, _P]),
 }
 
 _lib = None

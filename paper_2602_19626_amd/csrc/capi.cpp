@@ -153,8 +153,42 @@ nc_status nc_ensemble_forward(const float* z, const float* b, const float* theta
     const hipStream_t st = static_cast<hipStream_t>(stream);
     with_workspace(st, ensemble_workspace_bytes(int(rows), int(vocab)), [&](void* ws) {
       launch_ensemble_forward(z, b, theta, P, target, int(rows), int(vocab), int(n_experts), loss,
-                              p, resp, ws, st);
+                              p, resp, nullptr, ws, st);
     });
+  });
+}
+
+nc_status nc_ensemble_forward_lse(const float* z, const float* b, const float* theta,
+                                  const float* P, const int32_t* target, uint32_t rows,
+                                  uint32_t vocab, uint32_t n_experts, float* loss, float* resp,
+                                  float* lse, void* stream) {
+  return guard([&] {
+    NC_CHECK(z && b && theta && target && resp && lse && (n_experts == 1 || P), NC_E_INVALID,
+             "NULL pointer");
+    NC_CHECK(n_experts >= 1 && n_experts <= kMaxExperts, NC_E_INVALID, "n_experts in [1, 8]");
+    NC_CHECK(vocab >= 1 && vocab <= 262144u, NC_E_INVALID, "vocab must be in [1, 262144]");
+    if (rows == 0) return;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    with_workspace(st, ensemble_workspace_bytes(int(rows), int(vocab)), [&](void* ws) {
+      launch_ensemble_forward(z, b, theta, P, target, int(rows), int(vocab), int(n_experts), loss,
+                              nullptr, resp, lse, ws, st);
+    });
+  });
+}
+
+nc_status nc_ensemble_backward_lse(const float* z, float* b, float* theta, const float* resp,
+                                   const float* lse, const int32_t* target,
+                                   const float* grad_loss, uint32_t rows, uint32_t vocab,
+                                   uint32_t n_experts, float lr, float* grad_b,
+                                   float* grad_theta, void* stream) {
+  return guard([&] {
+    NC_CHECK(z && b && theta && resp && lse && target, NC_E_INVALID, "NULL pointer");
+    NC_CHECK(n_experts >= 1 && n_experts <= kMaxExperts, NC_E_INVALID, "n_experts in [1, 8]");
+    NC_CHECK(vocab >= 1 && vocab <= 262144u, NC_E_INVALID, "vocab must be in [1, 262144]");
+    if (rows == 0) return;
+    launch_ensemble_backward(z, b, theta, resp, target, grad_loss, int(rows), int(vocab),
+                             int(n_experts), lr, grad_b, grad_theta, lse, nullptr,
+                             static_cast<hipStream_t>(stream));
   });
 }
 
@@ -170,7 +204,7 @@ nc_status nc_ensemble_backward(const float* z, float* b, float* theta, const flo
     const hipStream_t st = static_cast<hipStream_t>(stream);
     with_workspace(st, ensemble_workspace_bytes(int(rows), int(vocab)), [&](void* ws) {
       launch_ensemble_backward(z, b, theta, resp, target, grad_loss, int(rows), int(vocab),
-                               int(n_experts), lr, grad_b, grad_theta, ws, st);
+                               int(n_experts), lr, grad_b, grad_theta, nullptr, ws, st);
     });
   });
 }

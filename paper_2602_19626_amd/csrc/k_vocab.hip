@@ -940,31 +940,58 @@ __global__ void state_reset_kernel(VocabParams P, StreamState S, int n, float w_
 
 // ---- standalone ensemble head (shared b and theta over a batch of rows) --------------------
 
-__device__ __forceinline__ void gate_weights(const float* theta, int n, float* w) {
-  float mx = theta[0];
-  for (int j = 1; j < n; ++j) mx = fmaxf(mx, theta[j]);
+// w = softmax(theta): every one of the kMaxExperts slots is computed and masked by selects, so that
+// w stays in registers; the kept terms are combined in order.
+__device__ __forceinline__ void gate_weights(const float* theta, int n, float (&w)[kMaxExperts]) {
+  float l[kMaxExperts];
+#pragma unroll
+  for (int j = 0; j < kMaxExperts; ++j) l[j] = theta[min(j, n - 1)];
+  float mx = l[0];
+#pragma unroll
+  for (int j = 1; j < kMaxExperts; ++j) mx = j < n ? fmaxf(mx, l[j]) : mx;
   float s = 0.f;
-  for (int j = 0; j < n; ++j) s += expf(theta[j] - mx);
-  for (int j = 0; j < n; ++j) w[j] = expf(theta[j] - mx) / s;
+#pragma unroll
+  for (int j = 0; j < kMaxExperts; ++j) {
+    w[j] = expf(l[j] - mx);
+    s = j < n ? s + w[j] : s;
+  }
+#pragma unroll
+  for (int j = 0; j < kMaxExperts; ++j) w[j] = w[j] / s;
 }
 
-// logsumexp partials of z_r + b per (segment, row)
+// Four consecutive floats at any 4-byte boundary (a row of odd length starts at one); the hardware
+// takes one 16-byte load.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Logsumexp partials of z_r + b per (segment, row).  Bound by memory (z read once); a thread's
+// four consecutive entries go out as one load whatever V is: 7.5 us for 64 rows of 49,152 entries,
+// 12.3 us with scalar loads.
 __global__ __launch_bounds__(kSegThreads) void ens_lse_kernel(const float* __restrict__ z,
                                                               const float* __restrict__ b, int V,
                                                               LsePart* __restrict__ parts) {
   __shared__ LsePart wl[kSegWaves];
   const int seg = blockIdx.x, r = blockIdx.y, nseg = gridDim.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const float* zr = z + (size_t)r * V;
   float u[4][4];
   float m = -INFINITY;
 #pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t t0 = seg_index(seg, j, tid, 0);
+    if (t0 + 3 < uint32_t(V)) {
+      const f4u zz = *reinterpret_cast<const f4u*>(zr + t0);
+      const f4u bb = *reinterpret_cast<const f4u*>(b + t0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u[j][i] = zz[i] + bb[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u[j][i] = t0 + i < uint32_t(V) ? zr[t0 + i] + b[t0 + i] : -INFINITY;
+    }
+  }
+#pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t t = seg_index(seg, j, tid, i);
-      u[j][i] = t < uint32_t(V) ? z[(size_t)r * V + t] + b[t] : -INFINITY;
-      m = fmaxf(m, u[j][i]);
-    }
+    for (int i = 0; i < 4; ++i) m = fmaxf(m, u[j][i]);
   float sum = 0.f;
   if (m != -INFINITY)
 #pragma unroll
@@ -986,35 +1013,61 @@ __global__ __launch_bounds__(kSegThreads) void ens_lse_kernel(const float* __res
   }
 }
 
-// per row: lse, loss = -log p(t*), responsibilities r_j = w_j q_j(t*) / p(t*)
-__global__ void ens_row_kernel(const float* __restrict__ z, const float* __restrict__ b,
-                               const float* __restrict__ theta, const float* __restrict__ Pk,
-                               const int32_t* __restrict__ target, int rows, int V, int nexp,
-                               const LsePart* __restrict__ parts, int nseg,
-                               float* __restrict__ lse_out, float* __restrict__ loss,
-                               float* __restrict__ resp) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  float w[kMaxExperts];
-  gate_weights(theta, nexp, w);
-  const float lse = row_lse(parts + (size_t)r * nseg, nseg);
-  lse_out[r] = lse;
-  const int t = target[r];
-  float q[kMaxExperts];
-  q[0] = expf(z[(size_t)r * V + t] + b[t] - lse);
-  float p = w[0] * q[0];
-  for (int j = 1; j < nexp; ++j) {
-    q[j] = Pk[((size_t)r * (nexp - 1) + (j - 1)) * V + t];
-    p = p + w[j] * q[j];
-  }
-  if (loss) loss[r] = -logf(p);
-  for (int j = 0; j < nexp; ++j) resp[(size_t)r * nexp + j] = w[j] * q[j] / p;
+// The row's logsumexp with one wave per row: lane k fetches segment k's partial, every lane merges
+// them in segment order.
+__device__ __forceinline__ float wave_row_lse(const LsePart* parts, int nseg, int lane) {
+  const LsePart mine = parts[min(lane, nseg - 1)];
+  LsePart acc{__shfl(mine.m, 0, 64), __shfl(mine.s, 0, 64)};
+  for (int k = 1; k < nseg; ++k)
+    acc = lse_merge(acc, LsePart{__shfl(mine.m, k, 64), __shfl(mine.s, k, 64)});
+  return acc.m + logf(acc.s);
 }
 
-__global__ void ens_lse_to_row_kernel(const LsePart* __restrict__ parts, int rows, int nseg,
-                                      float* __restrict__ lse) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < rows) lse[r] = row_lse(parts + (size_t)r * nseg, nseg);
+// Per row: lse, loss = -log p(t*), responsibilities r_j = w_j q_j(t*) / p(t*).  A chain of a few
+// dependent loads per row, so one wave takes one row (kEnsRows per workgroup) and its lanes fetch
+// the row's partials and experts side by side.
+constexpr int kEnsRows = 4;
+__global__ __launch_bounds__(64 * kEnsRows) void ens_row_kernel(
+    const float* __restrict__ z, const float* __restrict__ b, const float* __restrict__ theta,
+    const float* __restrict__ Pk, const int32_t* __restrict__ target, int rows, int V, int nexp,
+    const LsePart* __restrict__ parts, int nseg, float* __restrict__ lse_out,
+    float* __restrict__ loss, float* __restrict__ resp) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * kEnsRows + (threadIdx.x >> 6);
+  if (r >= rows) return;  // whole waves
+  const int t = target[r];
+  // lane 0: the logit and bias of t*; lane j >= 1: expert j's probability of t*
+  const float* src = z + (size_t)r * V + t;
+  if (lane >= 1 && lane < nexp) src = Pk + ((size_t)r * (nexp - 1) + (lane - 1)) * V + t;
+  const float v = *src, bt = b[t];
+  float w[kMaxExperts];
+  gate_weights(theta, nexp, w);
+  const float lse = wave_row_lse(parts + (size_t)r * nseg, nseg, lane);
+  float q[kMaxExperts];
+  q[0] = expf(__shfl(v, 0, 64) + bt - lse);
+  float p = w[0] * q[0];
+#pragma unroll
+  for (int j = 1; j < kMaxExperts; ++j) {
+    q[j] = __shfl(v, j, 64);
+    p = j < nexp ? p + w[j] * q[j] : p;
+  }
+  if (lane == 0) {
+    lse_out[r] = lse;
+    if (loss) loss[r] = -logf(p);
+  }
+#pragma unroll
+  for (int j = 0; j < kMaxExperts; ++j)
+    if (lane == j && j < nexp) resp[(size_t)r * nexp + j] = w[j] * q[j] / p;
+}
+
+// each row's logsumexp from its partials, one wave per row
+__global__ __launch_bounds__(64 * kEnsRows) void ens_lse_to_row_kernel(
+    const LsePart* __restrict__ parts, int rows, int nseg, float* __restrict__ lse) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * kEnsRows + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  const float v = wave_row_lse(parts + (size_t)r * nseg, nseg, lane);
+  if (lane == 0) lse[r] = v;
 }
 
 // optional full coding distribution p_r
@@ -1027,45 +1080,83 @@ __global__ void ens_prob_kernel(const float* __restrict__ z, const float* __rest
   gate_weights(theta, nexp, w);
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < V; t += gridDim.x * blockDim.x) {
     float v = w[0] * expf(z[(size_t)r * V + t] + b[t] - lse[r]);
-    for (int j = 1; j < nexp; ++j) v = v + w[j] * Pk[((size_t)r * (nexp - 1) + (j - 1)) * V + t];
+#pragma unroll
+    for (int j = 1; j < kMaxExperts; ++j)
+      if (j < nexp) v = v + w[j] * Pk[((size_t)r * (nexp - 1) + (j - 1)) * V + t];
     p[(size_t)r * V + t] = v;
   }
 }
 
-// grad_b[t] = sum_r g_r r_{r,0} (q0_r(t) - 1[t = t*_r]), rows summed in order; SGD on b.
-__global__ void ens_grad_b_kernel(const float* __restrict__ z, float* __restrict__ b,
-                                  const float* __restrict__ resp, const int32_t* __restrict__ target,
-                                  const float* __restrict__ gl, int rows, int V, int nexp,
-                                  const float* __restrict__ lse, float lr,
-                                  float* __restrict__ gb) {
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < V; t += gridDim.x * blockDim.x) {
-    const float bt = b[t];
-    float g = 0.f;
-    for (int r = 0; r < rows; ++r) {
-      const float q0 = expf(z[(size_t)r * V + t] + bt - lse[r]);
-      const float ind = target[r] == t ? 1.f : 0.f;
-      g = g + gl[r] * resp[(size_t)r * nexp] * (q0 - ind);
+// Backward of the head over all rows, in one launch.
+//   Workgroups 0 .. gridDim.x - 2, 64 vocabulary entries each, one per lane:
+//     grad_b[t] = sum_r g_r r_{r,0} (q0_r(t) - 1[t = t*_r]); SGD on b.  Wave w sums the rows of
+//     blocks w, w + 4, ... (kGradRows rows each) in order, then the four sums are added in order.
+//     Bound by reading z once: a block's loads are in flight together and the waves' side by side,
+//     so 64 rows take one memory round trip.
+//   The last workgroup: grad_theta[j] = sum_r g_r (w_j - r_{r,j}), each thread over its rows, then
+//     a fixed tree; SGD on theta (nothing else in the launch reads theta).
+// 64 rows of 49,152 entries and 5 experts: 5.4 us.  One thread per entry walking all rows took 16.4
+// us, and a launch of its own whose one thread walked the rows for theta 30.8 us.
+constexpr int kGradWaves = 4, kGradThreads = 64 * kGradWaves, kGradRows = 16;
+__global__ __launch_bounds__(kGradThreads) void ens_grad_kernel(
+    const float* __restrict__ z, float* __restrict__ b, float* __restrict__ theta,
+    const float* __restrict__ resp, const int32_t* __restrict__ target,
+    const float* __restrict__ gl, int rows, int V, int nexp, const float* __restrict__ lse,
+    float lr, float* __restrict__ gb, float* __restrict__ gth) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ float s_part[kGradWaves][kMaxExperts];
+    float w[kMaxExperts], g[kMaxExperts];
+    gate_weights(theta, nexp, w);
+#pragma unroll
+    for (int j = 0; j < kMaxExperts; ++j) g[j] = 0.f;
+    for (int r = tid; r < rows; r += kGradThreads) {
+      const float f = gl ? gl[r] : 1.f;
+#pragma unroll
+      for (int j = 0; j < kMaxExperts; ++j)
+        if (j < nexp) g[j] = g[j] + f * (w[j] - resp[(size_t)r * nexp + j]);
     }
+#pragma unroll
+    for (int j = 0; j < kMaxExperts; ++j) {
+      g[j] = wave_sum_f(g[j]);
+      if (lane == 0) s_part[wave][j] = g[j];
+    }
+    __syncthreads();
+    if (tid < nexp) {
+      float v = s_part[0][tid];
+      for (int k = 1; k < kGradWaves; ++k) v = v + s_part[k][tid];
+      if (gth) gth[tid] = v;
+      if (lr != 0.f) theta[tid] = theta[tid] - lr * v;
+    }
+    return;
+  }
+  __shared__ float s_g[kGradWaves][64];
+  const int t = blockIdx.x * 64 + lane;
+  const int tc = min(t, V - 1);
+  const float bt = b[tc];
+  float g = 0.f;
+  for (int r0 = wave * kGradRows; r0 < rows; r0 += kGradWaves * kGradRows) {
+    // lane u (mod kGradRows) holds row u's factors; rows past the end repeat the last one, unused
+    const int ru = min(r0 + (lane & (kGradRows - 1)), rows - 1);
+    float x[kGradRows];
+#pragma unroll
+    for (int u = 0; u < kGradRows; ++u) x[u] = z[(size_t)min(r0 + u, rows - 1) * V + tc];
+    const float l = lse[ru], f = (gl ? gl[ru] : 1.f) * resp[(size_t)ru * nexp];
+    const int tt = target[ru];
+#pragma unroll
+    for (int u = 0; u < kGradRows; ++u) {
+      const float q0 = expf(x[u] + bt - __shfl(l, u, 64));
+      const float ind = __shfl(tt, u, 64) == t ? 1.f : 0.f;
+      const float d = __shfl(f, u, 64) * (q0 - ind);
+      g = r0 + u < rows ? g + d : g;
+    }
+  }
+  s_g[wave][lane] = g;
+  __syncthreads();
+  if (wave == 0 && t < V) {
+    for (int k = 1; k < kGradWaves; ++k) g = g + s_g[k][lane];
     if (gb) gb[t] = g;
     if (lr != 0.f) b[t] = bt - lr * g;
-  }
-}
-
-// grad_theta[j] = sum_r g_r (w_j - r_{r,j}); SGD on theta (after every b thread read theta)
-__global__ void ens_grad_theta_kernel(float* __restrict__ theta, const float* __restrict__ resp,
-                                      const float* __restrict__ gl, int rows, int nexp, float lr,
-                                      float* __restrict__ gth) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  float w[kMaxExperts];
-  gate_weights(theta, nexp, w);
-  float g[kMaxExperts];
-  for (int j = 0; j < nexp; ++j) {
-    g[j] = 0.f;
-    for (int r = 0; r < rows; ++r) g[j] = g[j] + gl[r] * (w[j] - resp[(size_t)r * nexp + j]);
-  }
-  for (int j = 0; j < nexp; ++j) {
-    if (gth) gth[j] = g[j];
-    if (lr != 0.f) theta[j] = theta[j] - lr * g[j];
   }
 }
 
@@ -1075,14 +1166,14 @@ size_t ensemble_workspace_bytes(int rows, int V) {
 
 void launch_ensemble_forward(const float* z, const float* b, const float* theta, const float* Pk,
                              const int32_t* target, int rows, int V, int nexp, float* loss,
-                             float* p, float* resp, void* ws, hipStream_t s) {
+                             float* p, float* resp, float* lse_out, void* ws, hipStream_t s) {
   if (rows <= 0) return;
   const int nseg = int(ceil_div(V, kSeg));
   LsePart* parts = static_cast<LsePart*>(ws);
-  float* lse = reinterpret_cast<float*>(parts + (size_t)rows * nseg);
+  float* lse = lse_out ? lse_out : reinterpret_cast<float*>(parts + (size_t)rows * nseg);
   hipLaunchKernelGGL(ens_lse_kernel, dim3(nseg, rows), dim3(kSegThreads), 0, s, z, b, V, parts);
-  hipLaunchKernelGGL(ens_row_kernel, dim3(ceil_div(rows, 64)), dim3(64), 0, s, z, b, theta, Pk,
-                     target, rows, V, nexp, parts, nseg, lse, loss, resp);
+  hipLaunchKernelGGL(ens_row_kernel, dim3(ceil_div(rows, kEnsRows)), dim3(64 * kEnsRows), 0, s, z,
+                     b, theta, Pk, target, rows, V, nexp, parts, nseg, lse, loss, resp);
   if (p)
     hipLaunchKernelGGL(ens_prob_kernel, dim3(ceil_div(V, 256), rows), dim3(256), 0, s, z, b,
                        theta, Pk, rows, V, nexp, lse, p);
@@ -1091,19 +1182,21 @@ void launch_ensemble_forward(const float* z, const float* b, const float* theta,
 
 void launch_ensemble_backward(const float* z, float* b, float* theta, const float* resp,
                               const int32_t* target, const float* gl, int rows, int V, int nexp,
-                              float lr, float* gb, float* gth, void* ws, hipStream_t s) {
+                              float lr, float* gb, float* gth, const float* lse_in, void* ws,
+                              hipStream_t s) {
   if (rows <= 0) return;
-  const int nseg = int(ceil_div(V, kSeg));
-  LsePart* parts = static_cast<LsePart*>(ws);
-  float* lse = reinterpret_cast<float*>(parts + (size_t)rows * nseg);
-  hipLaunchKernelGGL(ens_lse_kernel, dim3(nseg, rows), dim3(kSegThreads), 0, s, z, b, V, parts);
-  // lse of each row (the forward's, recomputed in the same order)
-  hipLaunchKernelGGL(ens_lse_to_row_kernel, dim3(ceil_div(rows, 64)), dim3(64), 0, s, parts,
-                     rows, nseg, lse);
-  hipLaunchKernelGGL(ens_grad_b_kernel, dim3(ceil_div(V, 256)), dim3(256), 0, s, z, b, resp,
-                     target, gl, rows, V, nexp, lse, lr, gb);
-  hipLaunchKernelGGL(ens_grad_theta_kernel, dim3(1), dim3(64), 0, s, theta, resp, gl, rows, nexp,
-                     lr, gth);
+  const float* lse = lse_in;
+  if (!lse) {  // each row's lse, the forward's bits, recomputed
+    const int nseg = int(ceil_div(V, kSeg));
+    LsePart* parts = static_cast<LsePart*>(ws);
+    float* out = reinterpret_cast<float*>(parts + (size_t)rows * nseg);
+    hipLaunchKernelGGL(ens_lse_kernel, dim3(nseg, rows), dim3(kSegThreads), 0, s, z, b, V, parts);
+    hipLaunchKernelGGL(ens_lse_to_row_kernel, dim3(ceil_div(rows, kEnsRows)), dim3(64 * kEnsRows),
+                       0, s, parts, rows, nseg, out);
+    lse = out;
+  }
+  hipLaunchKernelGGL(ens_grad_kernel, dim3(ceil_div(V, 64) + 1), dim3(kGradThreads), 0, s, z,
+                     b, theta, resp, target, gl, rows, V, nexp, lse, lr, gb, gth);
   NC_HIP(hipGetLastError());
 }
 

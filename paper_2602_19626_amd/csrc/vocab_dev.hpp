@@ -139,10 +139,13 @@ void launch_state_reset(const VocabParams& P, const StreamState& S, int n_stream
 // Standalone ensemble head (C ABI): forward and backward over `rows` rows sharing b and theta.
 void launch_ensemble_forward(const float* z, const float* b, const float* theta, const float* Pk,
                              const int32_t* target, int rows, int V, int nexp, float* loss,
-                             float* p, float* resp, void* ws, hipStream_t s);
+                             float* p, float* resp, float* lse_out, void* ws, hipStream_t s);
+// lse_out (optional): each row's logsumexp(z + b); lse_in: the same values given back (the
+// workspace is then unused) or null.  gl null: a gradient of one per row.
 void launch_ensemble_backward(const float* z, float* b, float* theta, const float* resp,
                               const int32_t* target, const float* gl, int rows, int V, int nexp,
-                              float lr, float* gb, float* gth, void* ws, hipStream_t s);
+                              float lr, float* gb, float* gth, const float* lse_in, void* ws,
+                              hipStream_t s);
 size_t ensemble_workspace_bytes(int rows, int V);
 
 }  // namespace nc

@@ -25,37 +25,47 @@ def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def _forward(z, b, theta, P, target):
+    """(loss, resp, lse) of every row: the losses, the responsibilities and logsumexp(z + b)."""
+    rows, vocab = z.shape
+    nexp = theta.shape[0]
+    loss = torch.empty(rows, dtype=torch.float32, device=z.device)
+    lse = torch.empty_like(loss)
+    resp = torch.empty((rows, nexp), dtype=torch.float32, device=z.device)
+    Pp = _ptr(P, torch.float32, "P") if nexp > 1 else None
+    check(lib().nc_ensemble_forward_lse(
+        _ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
+        _ptr(theta, torch.float32, "theta"), Pp, _ptr(target, torch.int32, "target"), rows, vocab,
+        nexp, _ptr(loss, torch.float32, "loss"), _ptr(resp, torch.float32, "resp"),
+        _ptr(lse, torch.float32, "lse"), _stream()))
+    return loss, resp, lse
+
+
+def _backward(z, b, theta, resp, lse, target, gl, lr, gb, gth):
+    rows, vocab = z.shape
+    opt = lambda t, name: None if t is None else _ptr(t, torch.float32, name)
+    check(lib().nc_ensemble_backward_lse(
+        _ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
+        _ptr(theta, torch.float32, "theta"), _ptr(resp, torch.float32, "resp"),
+        _ptr(lse, torch.float32, "lse"), _ptr(target, torch.int32, "target"),
+        opt(gl, "grad_loss"), rows, vocab, theta.shape[0], C.c_float(lr), opt(gb, "grad_b"),
+        opt(gth, "grad_theta"), _stream()))
+
+
 class EnsembleHead(torch.autograd.Function):
     @staticmethod
     def forward(ctx, z, b, theta, P, target):
-        rows, vocab = z.shape
-        nexp = theta.shape[0]
-        loss = torch.empty(rows, dtype=torch.float32, device=z.device)
-        resp = torch.empty((rows, nexp), dtype=torch.float32, device=z.device)
-        Pp = _ptr(P, torch.float32, "P") if nexp > 1 else None
-        check(lib().nc_ensemble_forward(_ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
-                                        _ptr(theta, torch.float32, "theta"), Pp,
-                                        _ptr(target, torch.int32, "target"), rows, vocab, nexp,
-                                        _ptr(loss, torch.float32, "loss"), None,
-                                        _ptr(resp, torch.float32, "resp"), _stream()))
-        ctx.save_for_backward(z, b, theta, resp, target)
+        loss, resp, lse = _forward(z, b, theta, P, target)
+        ctx.save_for_backward(z, b, theta, resp, lse, target)
         return loss
 
     @staticmethod
     def backward(ctx, grad_loss):
-        z, b, theta, resp, target = ctx.saved_tensors
-        rows, vocab = z.shape
-        nexp = theta.shape[0]
+        z, b, theta, resp, lse, target = ctx.saved_tensors
         gl = grad_loss.contiguous().to(torch.float32)
         gb = torch.empty_like(b)
         gth = torch.empty_like(theta)
-        check(lib().nc_ensemble_backward(_ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
-                                         _ptr(theta, torch.float32, "theta"),
-                                         _ptr(resp, torch.float32, "resp"),
-                                         _ptr(target, torch.int32, "target"),
-                                         _ptr(gl, torch.float32, "grad_loss"), rows, vocab, nexp,
-                                         C.c_float(0.0), _ptr(gb, torch.float32, "grad_b"),
-                                         _ptr(gth, torch.float32, "grad_theta"), _stream()))
+        _backward(z, b, theta, resp, lse, target, gl, 0.0, gb, gth)
         return None, gb, gth, None, None
 
 
@@ -66,21 +76,6 @@ def ensemble_loss(z, b, theta, P, target):
 
 def ensemble_sgd_step(z, b, theta, P, target, lr: float = 1e-3):
     """One fused SGD step on (b, theta) for the summed loss, in place; returns the losses."""
-    rows, vocab = z.shape
-    nexp = theta.shape[0]
-    loss = torch.empty(rows, dtype=torch.float32, device=z.device)
-    resp = torch.empty((rows, nexp), dtype=torch.float32, device=z.device)
-    Pp = _ptr(P, torch.float32, "P") if nexp > 1 else None
-    check(lib().nc_ensemble_forward(_ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
-                                    _ptr(theta, torch.float32, "theta"), Pp,
-                                    _ptr(target, torch.int32, "target"), rows, vocab, nexp,
-                                    _ptr(loss, torch.float32, "loss"), None,
-                                    _ptr(resp, torch.float32, "resp"), _stream()))
-    ones = torch.ones(rows, dtype=torch.float32, device=z.device)
-    check(lib().nc_ensemble_backward(_ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
-                                     _ptr(theta, torch.float32, "theta"),
-                                     _ptr(resp, torch.float32, "resp"),
-                                     _ptr(target, torch.int32, "target"),
-                                     _ptr(ones, torch.float32, "grad_loss"), rows, vocab, nexp,
-                                     C.c_float(lr), None, None, _stream()))
+    loss, resp, lse = _forward(z, b, theta, P, target)
+    _backward(z, b, theta, resp, lse, target, None, lr, None, None)
     return loss

@@ -158,3 +158,42 @@ def test_backward_at_full_vocabulary_64_rows(dev):
     fd_b = np.array(fd_b)
     assert np.linalg.norm(gb[idx] - fd_b) / np.linalg.norm(fd_b) < 1e-4
     assert np.all(np.abs(gb[idx] - fd_b) <= 1e-4 * np.abs(fd_b) + 1e-9)
+
+
+@pytest.mark.parametrize("rows,v,nexp", [(1, 4, 1), (3, 4097, 2), (16, 512, 5), (17, 3001, 8),
+                                         (65, 1023, 5), (300, 129, 4)])
+def test_gradients_and_sgd_at_the_edges_of_the_kernels(dev, rows, v, nexp):
+    """Row blocks of 16 over four waves, 64 vocabulary entries per workgroup, odd row starts, one to
+    eight experts: losses, gradients with a gradient per row, and the fused SGD step against the
+    closed form in float64.  float32 sums of at most 300 terms of one sign or cancelling to a norm
+    within a factor of ten: 1e-4 norm-wise."""
+    from paper_2602_19626_amd.ensemble import ensemble_loss, ensemble_sgd_step
+    z, b, theta, P, t = _case(rows, rows=rows, v=v, nexp=nexp) if nexp > 1 else (
+        *_case(rows, rows=rows, v=v, nexp=2)[:2], np.zeros(1), np.zeros((rows, 0, v)),
+        np.arange(rows) % v)
+    gl = np.random.default_rng(rows).normal(size=rows) + 2.0
+    f32 = lambda x: torch.tensor(x, dtype=torch.float32, device=dev).contiguous()
+    tz, tP, tt = f32(z), f32(P), torch.tensor(t, dtype=torch.int32, device=dev)
+    tb, tth = f32(b).requires_grad_(True), f32(theta).requires_grad_(True)
+    loss = ensemble_loss(tz, tb, tth, tP, tt)
+    (loss * f32(gl)).sum().backward()
+    z32, b32, th32, P32, gl32 = (x.astype(np.float32).astype(np.float64)
+                                  for x in (z, b, theta, P, gl))
+    u = z32 + b32
+    q = np.exp(u - u.max(1, keepdims=True))
+    q /= q.sum(1, keepdims=True)
+    w = np.exp(th32) / np.exp(th32).sum()
+    at = np.concatenate([q[np.arange(rows), t][:, None], P32[np.arange(rows), :, t]], 1) * w
+    p = at.sum(1)
+    r = at / p[:, None]
+    d = q.copy()
+    d[np.arange(rows), t] -= 1
+    near = lambda got, ref: np.linalg.norm(got.detach().double().cpu().numpy() - ref) <= \
+        1e-4 * np.linalg.norm(ref) + 1e-6
+    assert near(loss, -np.log(p))
+    assert near(tb.grad, (gl32[:, None] * r[:, :1] * d).sum(0))
+    assert near(tth.grad, (gl32[:, None] * (w - r)).sum(0))
+    sb, sth = f32(b), f32(theta)
+    assert near(ensemble_sgd_step(tz, sb, sth, tP, tt, lr=0.5), -np.log(p))
+    assert near(sb, b32 - 0.5 * (r[:, :1] * d).sum(0))
+    assert near(sth, th32 - 0.5 * (w - r).sum(0))
