@@ -8,7 +8,8 @@ namespace nc {
 // CDF-24 quantise + scan, reduce-then-scan over 4096-entry segments (k_cdf.hip).  The workspace
 // holds quantize_workspace_bytes(rows, V) bytes of device memory.
 size_t quantize_workspace_bytes(uint32_t rows, uint32_t V);
-// Bytes of workspace the launch for these rows actually uses (0 on the one-workgroup-per-row path).
+// Bytes of scratch that the no-allocation variant takes for these rows; 0: none, and the launch gets
+// a null workspace (rows <= 49,152 entries, one workgroup per row).
 size_t quantize_workspace_needed(const float* p, uint32_t rows, uint32_t V);
 // The no-allocation variant's workspace: a fixed device array of kScratchParts segment partials
 // (16 bytes each), its address on the current device resolved on first use.

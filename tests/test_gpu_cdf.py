@@ -193,3 +193,19 @@ def test_row_kernel_path_adversarial_and_ragged(nc, v):
     bad[69, :] = 1.0
     _, st = _gpu_cdf(nc, bad)
     assert [r for r in range(70) if st[r]] == [3, 40, 69]
+
+
+@pytest.mark.parametrize("rows,v", [(1, 3), (66, 4097), (70, 32003), (3, 4099), (65, 50001)])
+def test_rows_that_start_on_any_word(nc, rows, v):
+    """Rows of a length that 4 does not divide (their starts and the CDF's fall on every word) and a
+    first row one word past a 16-byte boundary: bit-exact with the oracle."""
+    rng = np.random.default_rng(rows)
+    p = rng.dirichlet(np.full(v, 0.3), size=rows).astype(np.float32)
+    buf = torch.zeros(rows * v + 1, device="cuda:0")
+    q = buf[1:].view(rows, v)
+    q.copy_(torch.from_numpy(p))
+    cdf, st = nc.quantize_cdf24(q)
+    assert not st.any()
+    got = cdf.cpu().numpy().view(np.uint32).astype(np.int64)
+    for r in range(0, rows, max(1, rows // 7)):
+        assert np.array_equal(got[r], quantize_cdf(p[r])), r
