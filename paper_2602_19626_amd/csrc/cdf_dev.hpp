@@ -27,14 +27,14 @@ typedef float f4v __attribute__((ext_vector_type(4)));
 // max(1, floor(p * m)) of the exact real product, for finite p in [0, 1] and m < 2^24.  c, the
 // truncated float product, is the floor or one above it: rounding is monotonic and every integer
 // up to 2^24 is a float, so the rounded product is never below an integer that the exact product
-// reaches.  The fused p * m - c rounds once, so its sign is exact and tells the two apart.  Seven
+// reaches.  The fused p * m - c rounds once, so its sign is exact and tells the two apart.  Eight
 // full-rate instructions for every entry of a row (a 24-bit integer product with its 64-bit shift
-// takes thirteen, the shift at quarter rate).
+// takes thirteen, the shift at quarter rate).  A NaN gives 0, an interval that no coder accepts.
 __device__ __forceinline__ uint32_t floor_count(float p, uint32_t m) {
   const float fm = float(m);
   const float c = truncf(p * fm);
   const float f = __builtin_fmaf(p, fm, -c) < 0.f ? c - 1.f : c;
-  return uint32_t(fmaxf(f, 1.f));
+  return uint32_t(f < 1.f ? 1.f : f);
 }
 
 // (value, index) maximum with the lowest index winning ties.

@@ -189,10 +189,11 @@ __device__ __forceinline__ void row_fetch(const VocabParams& P, const StreamStat
 }
 
 // Probabilities of this thread's 16 entries of segment seg from the fetched vectors, zero at or
-// beyond V.
+// beyond V (kEns: the row may be an ensemble's).
+template <bool kEns = true>
 __device__ __forceinline__ void row_probs(const RowIn& R, const RowVec& v, uint32_t seg, int tid,
                                           float (&p)[4][4], float (&pt)[4][4]) {
-  if (R.mode == M_ENS) {
+  if (kEns && R.mode == M_ENS) {
     // The ensemble also reads P_1..P_K at the thread's 16 entries: every vector is requested
     // (clamped into the row, masked after) before the first is used, rather than one dependent
     // load per entry and order.  p = w0 q + w1 P_1 + ... + wK P_K, added in that order.
@@ -297,8 +298,7 @@ __device__ __forceinline__ void v3_seg(const VocabParams& P, const StreamState& 
     row_fetch(P, S, A, r, s, seg, tid, v);
     R = make_row(P, S, A, r, s, nseg);
   }
-  const int i_pos = !active ? 0 : (A.pos >= 0 ? A.pos + (A.pos_base ? *A.pos_base : 0)
-                                               : S.ncommit[s]);
+  const int i_pos = !active ? 0 : (A.pos >= 0 ? A.pos : S.ncommit[s]);
   const uint32_t key =
       !active ? 0u
               : (A.decode ? (A.targets ? A.targets[r] : A.targets_in[r])
@@ -495,23 +495,22 @@ __device__ __forceinline__ void v5_row(const VocabParams& P, const StreamState& 
                                        const StepArgs& A, int r, int k) {
   const int s = A.rows[r];
   const int32_t* hist = S.hist + (size_t)s * S.maxT;
-  // With the position given (batched encode) the committed token is the known one in hist, so the
-  // count updates need not wait for this step's outcome; the mixer update always reads it.
+  // With the position given (encode) the counts take the known token in hist, whatever the step's
+  // outcome; the mixer update reads the outcome.
   const bool given = A.pos >= 0 && !A.decode;
-  const bool counts = (A.upd & kUpdCounts) != 0, mixer = (A.upd & kUpdMixer) != 0;
-  const Outcome o = (mixer || !given) ? A.out[r] : Outcome{};
-  const int i = k < 0 ? 0 : (A.pos >= 0 ? A.pos + (A.pos_base ? *A.pos_base : 0) : S.ncommit[s]);
+  const Outcome o = A.out[r];
+  const int i = k < 0 ? 0 : (A.pos >= 0 ? A.pos : S.ncommit[s]);
   const int sym = given ? hist[i] : o.sym;
   const bool on = k >= 0 && sym >= 0 && (given || o.sym >= 0);
   __syncthreads();
-  if (on && k == 0 && counts) {
+  if (on && k == 0) {
     if (A.decode) S.hist[(size_t)s * S.maxT + i] = sym;
     if (P.use_ngram || P.ensemble) {
       S.uni[(size_t)s * P.V + sym] += 1;
       S.nseen[s] += 1;
     }
   }
-  if (on && k == 0 && mixer && o.sym >= 0) {
+  if (on && k == 0 && o.sym >= 0) {
     float* lw = S.lw + (size_t)s * kMaxExperts;
     if (o.mode == M_MIX) {
       // exponential weights (section 3.6): log w_j += eta log p_j(t*), then renormalise
@@ -529,7 +528,7 @@ __device__ __forceinline__ void v5_row(const VocabParams& P, const StreamState& 
         if (j <= P.K) lw[j] = lw[j] - P.head_lr * (w[j] - o.r[j]);
     }
   }
-  if (on && counts && (P.use_ngram || P.ensemble) && k >= 1 && k <= P.K) {
+  if (on && (P.use_ngram || P.ensemble) && k >= 1 && k <= P.K) {
     const size_t t = (size_t)s * P.K + (k - 1);
     Ctx ctx{};
     // insert t* as a continuation of the order-k context ending at t_{i-1}
@@ -604,7 +603,7 @@ __device__ __forceinline__ void v5_row(const VocabParams& P, const StreamState& 
     S.next_ctx[(size_t)s * kMaxOrder + (k - 1)] = nid;
   }
   __syncthreads();
-  if (on && k == 0 && counts) S.ncommit[s] = i + 1;
+  if (on && k == 0) S.ncommit[s] = i + 1;
 }
 
 // ---- V6: dense n-gram prediction of the current position ------------------------------------
@@ -730,8 +729,7 @@ __device__ __forceinline__ int slot_last(const FixLds& F, int q, int ln, int tok
 __device__ __forceinline__ void v7_row(const VocabParams& P, const StreamState& S,
                                        const int32_t* rows, const NgPart* parts, int nseg,
                                        StepOut* step_out, const Outcome* out, int r, int tid,
-                                       bool active, FixLds& F, int pos_given,
-                                       const int* pos_base) {
+                                       bool active, FixLds& F) {
   const int nt = kSegThreads;
   const int V = P.V;
   const int s = rows[r];
@@ -743,7 +741,7 @@ __device__ __forceinline__ void v7_row(const VocabParams& P, const StreamState& 
   uint32_t pre_cl = 0, pre_ch = 0;
   float pre_p = 0.f;
   if (active && tid == 0) {
-    pre_pos = pos_given >= 0 ? pos_given + (pos_base ? *pos_base : 0) : S.ncommit[s];
+    pre_pos = S.ncommit[s];
     if (step_out) {
       pre_sym = out[r].sym;
       pre_cl = out[r].cl;
@@ -903,18 +901,676 @@ __global__ __launch_bounds__(kSegThreads) void ngram_fix_kernel(VocabParams P, S
                                                                 const int32_t* rows,
                                                                 const NgPart* parts, int nseg,
                                                                 StepOut* step_out,
-                                                                const Outcome* out, int pos,
-                                                                const int* pos_base) {
+                                                                const Outcome* out) {
   __shared__ FixLds F;
-  v7_row(P, S, rows, parts, nseg, step_out, out, blockIdx.x, threadIdx.x, true, F, pos,
-         pos_base);
+  v7_row(P, S, rows, parts, nseg, step_out, out, blockIdx.x, threadIdx.x, true, F);
+}
+
+// ---- chunks of known tokens (encode, committed prompts) ----------------------------------------
+//
+// Where the tokens of a run of positions are known, neither the n-gram models nor the logits of
+// those positions depend on the coding of any of them; only the bias head and the mixer weights
+// run from position to position.  A chunk of positions is therefore taken apart:
+//   known_advance   updates the tables with the chunk's tokens, one wave per (order, stream), and
+//                   leaves what each position's prediction needs: its contexts' slots and counts;
+//   known_dense,    the n-gram distribution, entropy and mode of every position of the chunk at
+//   known_fix       once;
+//   known_commit    unigram counts;
+//   known_step      one launch per position: probabilities, count partials, the bias step and the
+//                   logsumexp partials of the next position, whose bias is then known;
+//   known_finish    the intervals of every position from the count partials.
+// Every value is computed by the expressions, and reduced in the order, of the step-by-step
+// kernels above, so the coded bits are those of the sequential decode.
+
+// Wave reductions in the lanes' registers (data-parallel primitives: a few cycles a step, where a
+// shuffle goes through LDS).  Integer sums and maxima, so the order does not matter; the result is
+// that of lane 63.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {  // 0 where there is no source lane
+  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false));
+}
+constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118, kBcast15 = 0x142,
+              kBcast31 = 0x143, kWaveShr1 = 0x138, kShl1 = 0x101, kShl2 = 0x102, kShl4 = 0x104, kShl8 = 0x108;
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ float dpp_low(float v) {  // -infinity where there is no source lane
+  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(
+      int(0xFF800000u), int(__float_as_uint(v)), kCtrl, kRows, 0xF, false)));
+}
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+  v += dpp_u32<kShr1, 0xF>(v);
+  v += dpp_u32<kShr2, 0xF>(v);
+  v += dpp_u32<kShr4, 0xF>(v);
+  v += dpp_u32<kShr8, 0xF>(v);
+  v += dpp_u32<kBcast15, 0xA>(v);
+  v += dpp_u32<kBcast31, 0xC>(v);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_max_u64(uint64_t v) {
+  const uint64_t o = uint64_t(dpp_u32<kCtrl, kRows>(uint32_t(v))) |
+                     (uint64_t(dpp_u32<kCtrl, kRows>(uint32_t(v >> 32))) << 32);
+  return o > v ? o : v;
+}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+  v = dpp_max_u64<kShr1, 0xF>(v);
+  v = dpp_max_u64<kShr2, 0xF>(v);
+  v = dpp_max_u64<kShr4, 0xF>(v);
+  v = dpp_max_u64<kShr8, 0xF>(v);
+  v = dpp_max_u64<kBcast15, 0xA>(v);
+  v = dpp_max_u64<kBcast31, 0xC>(v);
+  return uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(v), 63))) |
+         (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(v >> 32), 63))) << 32);
+}
+
+__device__ __forceinline__ float read_lane(float v, int lane) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+
+// The logsumexp partial of a wave's 64 partials by the tree of v1_seg: lane L merges lane L + d for
+// d = 1, 2, 4, ... with the lower lane first.  Lanes whose partner is another tree node's (or
+// missing) hold values that no node of lane 0's tree reads.
+template <int kCtrl>
+__device__ __forceinline__ LsePart dpp_lse(LsePart a) {
+  const LsePart o{__uint_as_float(dpp_u32<kCtrl, 0xF>(__float_as_uint(a.m))),
+                  __uint_as_float(dpp_u32<kCtrl, 0xF>(__float_as_uint(a.s)))};
+  return lse_merge(a, o);
+}
+__device__ __forceinline__ LsePart wave_lse(LsePart p) {
+  p = dpp_lse<kShl1>(p);
+  p = dpp_lse<kShl2>(p);
+  p = dpp_lse<kShl4>(p);
+  p = dpp_lse<kShl8>(p);
+  LsePart q[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) q[k] = LsePart{read_lane(p.m, 16 * k), read_lane(p.s, 16 * k)};
+  return lse_merge(lse_merge(q[0], q[1]), lse_merge(q[2], q[3]));
+}
+
+// row_lse with the lanes sharing the work: the running maxima of the fold are exact whatever the
+// order, so lane k computes the two factors of merge k and only the products and sums are serial.
+__device__ __forceinline__ float lane_row_lse(const LsePart mine, int nseg, int lane) {
+  float run = lane < nseg ? mine.m : -INFINITY;  // inclusive maximum of lanes 0 .. lane
+  run = fmaxf(run, dpp_low<kShr1, 0xF>(run));
+  run = fmaxf(run, dpp_low<kShr2, 0xF>(run));
+  run = fmaxf(run, dpp_low<kShr4, 0xF>(run));
+  run = fmaxf(run, dpp_low<kShr8, 0xF>(run));
+  run = fmaxf(run, dpp_low<kBcast15, 0xA>(run));
+  run = fmaxf(run, dpp_low<kBcast31, 0xC>(run));
+  const float prev = dpp_low<kWaveShr1, 0xF>(run);
+  const bool empty = run == -INFINITY;
+  const float e1 = empty ? 0.f : expf(prev - run);
+  const float e2 = empty ? 0.f : mine.s * expf(mine.m - run);
+  float acc = read_lane(mine.s, 0);
+  for (int k = 1; k < nseg; ++k) acc = acc * read_lane(e1, k) + read_lane(e2, k);
+  return read_lane(run, nseg - 1) + logf(acc);
+}
+
+// The order-k context of position i (tokens i - k .. i - 1) in table t: its pool index or -1, and
+// the empty slot where it would go.  Eight slots of the probe sequence per round of loads, one per
+// lane (ctx_find's sequence and result).
+__device__ __forceinline__ int wave_ctx_find(const StreamState& S, size_t t, const Ctx& c, int k,
+                                             int lane, int* ins) {
+  typedef int32_t i4 __attribute__((ext_vector_type(4)));
+  const i4* keys = reinterpret_cast<const i4*>(S.keys + t * S.cap * 4);
+  const int32_t* kidx = S.kidx + t * S.cap;
+  const uint32_t h = ctx_hash(c, k);
+  for (int p0 = 0; p0 < S.cap; p0 += 8) {
+    const uint32_t at = (h + p0 + (lane & 7)) & uint32_t(S.cap - 1);
+    const int id = kidx[at];
+    const i4 kk = keys[at];
+    bool eq = true;
+#pragma unroll
+    for (int i = 0; i < kMaxOrder; ++i)
+      if (i < k) eq = eq && kk[i] == c.v[i];
+    const uint64_t stop = __ballot(id < 0 || eq) & 0xFF;
+    if (stop) {
+      const int l = __builtin_ctzll(stop);
+      *ins = __builtin_amdgcn_readlane(int(at), l);
+      const int found = __builtin_amdgcn_readlane(id, l);
+      return found < 0 ? -1 : found;
+    }
+  }
+  *ins = -1;
+  return -1;
+}
+
+// One wave per (order k = blockIdx.x + 1, row): the chunk's tokens are inserted one after the other
+// (the update kernel's rules), the current context's slots held one per lane.  Before each token
+// the slots and counts are left in the snapshot of its position.  Bound by two dependent reads per
+// token, the table slot and then the slots of the context found there.
+__global__ __launch_bounds__(64) void known_advance_kernel(VocabParams P, StreamState S,
+                                                           KnownChunk C, int p0) {
+  const int k = blockIdx.x + 1, r = blockIdx.y, lane = threadIdx.x;
+  const int s = C.s0 + r, np = min(C.np, C.left[r]);
+  const size_t t = (size_t)s * P.K + (k - 1);
+  const int32_t* hist = S.hist + (size_t)s * S.maxT;
+  const int most = min(S.maxctx, P.ngram_max_contexts);
+  int nctx = S.nctx[t];
+  int id = -1, ins = -1, n = 0, sum = 0;  // the context of the position
+  int2 slot{-1, 0};                       // this lane's slot of it
+  auto take = [&](int i) {                // the context of position i
+    Ctx c{};
+#pragma unroll
+    for (int q = 0; q < kMaxOrder; ++q)
+      if (q < k) c.v[q] = hist[i - k + q];
+    const int old = id;
+    id = wave_ctx_find(S, t, c, k, lane, &ins);
+    if (id < 0) {
+      n = sum = 0;
+    } else if (id != old) {
+      slot = *reinterpret_cast<const int2*>(S.pool + ((t * S.maxctx + id) * kSlots + lane) * 2);
+      n = S.pool_n[t * S.maxctx + id];
+      sum = S.pool_sum[t * S.maxctx + id];
+    }
+  };
+  if (p0 >= k) take(p0);
+  for (int j = 0; j < np; ++j) {
+    const int i = p0 + j;
+    const size_t at = ((size_t)j * C.B + r) * P.K + (k - 1);
+    C.slots[at * kSlots + lane] = slot;
+    if (lane == 0) C.counts[at] = int2{n, sum};
+    const int tok = hist[i];
+    if (i >= k) {
+      int32_t* sl = S.pool + (t * S.maxctx + max(id, 0)) * kSlots * 2;
+      int put = -1;  // the slot that changes
+      if (id < 0) {
+        if (ins >= 0 && nctx < most) {
+          id = nctx++;
+          sl = S.pool + (t * S.maxctx + id) * kSlots * 2;
+          if (lane < 4) {
+            int v = -1;
+#pragma unroll
+            for (int q = 0; q < kMaxOrder; ++q)
+              if (q == lane && q < k) v = hist[i - k + q];
+            S.keys[(t * S.cap + ins) * 4 + lane] = v;
+          }
+          if (lane == 0) S.kidx[t * S.cap + ins] = id;
+          put = 0;
+          n = sum = 1;
+          if (lane == put) slot = int2{tok, 1};
+        }
+      } else {
+        const uint64_t hit = __ballot(lane < n && slot.x == tok);
+        if (hit) {
+          put = __builtin_ctzll(hit);
+          if (lane == put) slot.y += 1;
+          sum += 1;
+        } else if (n < kSlots) {
+          put = n++;
+          if (lane == put) slot = int2{tok, 1};
+          sum += 1;
+        } else {  // the lowest count, the lowest slot index on ties
+          const uint32_t key = (uint32_t(slot.y) << 6) | uint32_t(lane);
+          uint32_t low = key;
+#pragma unroll
+          for (int d = 1; d < 64; d <<= 1) low = min(low, uint32_t(__shfl_xor(low, d, 64)));
+          put = int(low & 63);
+          sum += 1 - int(low >> 6);
+          if (lane == put) slot = int2{tok, 1};
+        }
+      }
+      if (put >= 0) {
+        if (lane == put) *reinterpret_cast<int2*>(sl + 2 * lane) = slot;
+        if (lane == 0) {
+          S.pool_n[t * S.maxctx + id] = n;
+          S.pool_sum[t * S.maxctx + id] = sum;
+        }
+        // the wave's later reads of these places come after the writes
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      }
+    }
+    if (i + 1 >= k) take(i + 1);
+  }
+  if (lane == 0) {
+    S.nctx[t] = nctx;
+    S.next_ctx[(size_t)s * kMaxOrder + (k - 1)] = id;
+  }
+}
+
+// The n-gram weights of a position from its snapshot (ng_row's expressions).
+__device__ __forceinline__ void known_row(const VocabParams& P, const KnownChunk& C, int j, int r,
+                                          int seen, NgRow& g) {
+  const int2* cnt = C.counts + ((size_t)j * C.B + r) * P.K;
+#pragma unroll
+  for (int k = 0; k < kMaxOrder; ++k) {
+    g.id[k] = -1;
+    const int sum = cnt[min(k, P.K - 1)].y;
+    g.n[k] = k < P.K ? sum : 0;
+    g.present[k] = g.n[k] > 0 ? 1 : 0;
+    g.lam[k] = g.present[k] ? float(g.n[k]) / (float(g.n[k]) + P.ngram_eps) : 0.f;
+  }
+  g.inv_norm = 1.0f / float(seen + P.V);
+}
+
+// The dense distribution of kKnownRun positions of one row over one segment (v6_seg for each): the
+// unigram counts stay in registers and take each position's token.  The tokens of the chunk before
+// the first of these positions are added through LDS.
+constexpr int kKnownRun = 4;
+__global__ __launch_bounds__(kSegThreads) void known_dense_kernel(VocabParams P, StreamState S,
+                                                                  KnownChunk C, int p0) {
+  typedef int32_t i4v __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) int32_t s_u[kSeg];
+  __shared__ NgPart wl[2][kSegWaves];
+  const int seg = blockIdx.x, r = blockIdx.z, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int j0 = blockIdx.y * kKnownRun;
+  const int s = C.s0 + r, V = P.V, np = min(C.np, C.left[r]), nseg = gridDim.x;
+  if (j0 >= np) return;
+  const int32_t* hist = S.hist + (size_t)s * S.maxT + p0;
+  i4v u[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t t0 = seg_index(seg, q, tid, 0);
+    u[q] = t0 < uint32_t(V) ? *reinterpret_cast<const i4v*>(S.uni + (size_t)s * V + t0)
+                            : i4v{0, 0, 0, 0};
+  }
+  if (j0 > 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) reinterpret_cast<i4v*>(s_u)[q * kSegThreads + tid] = i4v{0, 0, 0, 0};
+    __syncthreads();
+    for (int q = tid; q < j0; q += kSegThreads) {
+      const uint32_t off = uint32_t(hist[q]) - uint32_t(seg) * kSeg;
+      if (off < uint32_t(kSeg)) atomicAdd(s_u + off, 1);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u[q] += reinterpret_cast<const i4v*>(s_u)[q * kSegThreads + tid];
+  }
+  const int seen = S.nseen[s];
+  const int j1 = min(j0 + kKnownRun, np);
+  for (int j = j0; j < j1; ++j) {
+    NgRow g;
+    known_row(P, C, j, r, seen + j, g);
+    float h = 0.f, mx = 0.f;
+    float* png = C.png + ((size_t)j * C.B + r) * V;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t t0 = seg_index(seg, q, tid, 0);
+      if (t0 >= uint32_t(V)) continue;
+      f4v out;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float pv = float(u[q][i] + 1) * g.inv_norm;
+#pragma unroll
+        for (int k = 1; k <= kMaxOrder; ++k) {
+          if (k > P.K) break;
+          if (g.present[k - 1]) pv = (1.0f - g.lam[k - 1]) * pv;
+        }
+        out[i] = pv;
+        h = h - pv * log2f(pv);
+        mx = fmaxf(mx, pv);
+      }
+      *reinterpret_cast<f4v*>(png + t0) = out;
+    }
+    h = wave_sum_f(h);
+    mx = wave_max_f(mx);
+    if (lane == 0) wl[j & 1][w] = NgPart{h, mx};
+    __syncthreads();
+    if (tid == 0) {
+      NgPart acc = wl[j & 1][0];
+      for (int k = 1; k < kSegWaves; ++k) {
+        acc.h += wl[j & 1][k].h;
+        acc.mx = fmaxf(acc.mx, wl[j & 1][k].mx);
+      }
+      C.ngp[((size_t)j * C.B + r) * nseg + seg] = acc;
+    }
+    const uint32_t off = uint32_t(hist[j]) - uint32_t(seg) * kSeg;
+    if (off < uint32_t(kSeg) && int((off % kQuarter) >> 2) == tid) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (int(off / kQuarter) == q && int(off & 3) == i) u[q][i] += 1;
+    }
+  }
+}
+
+// The sparse entries, entropy and mode of one position of one row (v7_row), and its token.
+__global__ __launch_bounds__(kSegThreads) void known_fix_kernel(VocabParams P, StreamState S,
+                                                                KnownChunk C, int p0, int nseg) {
+  __shared__ FixLds F;
+  extern __shared__ int32_t s_tok[];  // the chunk's tokens before the position
+  const int j = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+  const int s = C.s0 + r, V = P.V;
+  if (j >= min(C.np, C.left[r])) return;
+  const size_t row = (size_t)j * C.B + r;
+  const int32_t* hist = S.hist + (size_t)s * S.maxT + p0;
+  float* png = C.png + row * V;
+  NgPart pre_part{0.f, 0.f};
+  if (tid < nseg) pre_part = C.ngp[row * nseg + tid];
+  for (int q = tid; q < j; q += kSegThreads) s_tok[q] = hist[q];
+  if (tid == 0) C.tok[row] = hist[j];
+  NgRow g;
+  known_row(P, C, j, r, S.nseen[s] + j, g);
+  const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);  // order - 1 of this wave
+  if (kw < kMaxOrder) {
+    const int kc = min(kw, P.K - 1);
+    const int2 tc = C.slots[(row * P.K + kc) * kSlots + (tid & 63)];
+    const int n = C.counts[row * P.K + kc].x;
+    if ((tid & 63) == 0) F.ln[kw] = kw < P.K ? n : 0;
+    F.lt[kw][tid & 63] = tc.x;
+    F.lc[kw][tid & 63] = tc.y;
+  }
+  __syncthreads();
+  float dh = 0.f, dmx = 0.f;
+  // (one entry per thread: P.K * kSlots <= kSegThreads)
+  if (kw < P.K && (tid & 63) < F.ln[kw]) {
+    const int k = kw + 1, tok = F.lt[kw][tid & 63];
+    int u_tok = S.uni[(size_t)s * V + tok];
+    const float old = png[tok];
+    bool owner = true;
+    for (int k2 = 1; k2 < k && owner; ++k2) owner = slot_last(F, k2 - 1, F.ln[k2 - 1], tok) < 0;
+    if (owner) {
+#pragma unroll 8
+      for (int q = 0; q < j; ++q) u_tok += s_tok[q] == tok ? 1 : 0;
+      float pv = float(u_tok + 1) * g.inv_norm;
+#pragma unroll
+      for (int k2 = 1; k2 <= kMaxOrder; ++k2) {
+        if (k2 > P.K) break;
+        if (g.present[k2 - 1]) {
+          const int at = slot_last(F, k2 - 1, F.ln[k2 - 1], tok);
+          const int cnt = at >= 0 ? F.lc[k2 - 1][at] : 0;
+          const float n = float(g.n[k2 - 1]);
+          pv = g.lam[k2 - 1] * (float(cnt) / n) + (1.0f - g.lam[k2 - 1]) * pv;
+        }
+      }
+      png[tok] = pv;
+      dh = dh + (old * log2f(old) - pv * log2f(pv));
+      dmx = fmaxf(dmx, pv);
+    }
+  }
+  dh = wave_sum_f(dh);
+  dmx = wave_max_f(dmx);
+  if ((tid & 63) == 0) {
+    F.sh[tid >> 6] = dh;
+    F.smx[tid >> 6] = dmx;
+  }
+  if (tid < nseg) {
+    F.sh[kSegWaves + tid] = pre_part.h;
+    F.smx[kSegWaves + tid] = pre_part.mx;
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  float H = 0.f, mx = 0.f;
+  for (int k = 0; k < nseg; ++k) {
+    H += F.sh[kSegWaves + k];
+    mx = fmaxf(mx, F.smx[kSegWaves + k]);
+  }
+  float sh = F.sh[0], smx = F.smx[0];
+  for (int k = 1; k < kSegWaves; ++k) {
+    sh = sh + F.sh[k];
+    smx = fmaxf(smx, F.smx[k]);
+  }
+  H = H + sh;
+  mx = fmaxf(mx, smx);
+  const bool warm = p0 + j < P.warmup;
+  bool skip = false;
+  if (P.use_skip && !warm) {
+    if (P.skip_mode == 1) skip = H < P.skip_bits;
+    if (P.skip_mode == 2) skip = mx >= P.skip_pmax;
+  }
+  C.mode[row] = skip ? M_SKIP : ((warm || !P.use_mixer) ? M_LLM : M_MIX);
+}
+
+// Without the n-gram: every position is the model's.
+__global__ void known_tokens_kernel(StreamState S, KnownChunk C, int p0) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= C.np * C.B) return;
+  const int j = e / C.B, r = e % C.B;
+  if (j >= C.left[r]) return;
+  C.tok[e] = S.hist[(size_t)(C.s0 + r) * S.maxT + p0 + j];
+  C.mode[e] = M_LLM;
+}
+
+// Unigram counts (integer adds, any order) and the committed position of each row.
+__global__ __launch_bounds__(kSegThreads) void known_commit_kernel(VocabParams P, StreamState S,
+                                                                   KnownChunk C, int p0) {
+  const int r = blockIdx.x, s = C.s0 + r, np = min(C.np, C.left[r]);
+  const int32_t* hist = S.hist + (size_t)s * S.maxT + p0;
+  if (P.use_ngram)
+    for (int j = threadIdx.x; j < np; j += blockDim.x)
+      atomicAdd(S.uni + (size_t)s * P.V + hist[j], 1);
+  if (threadIdx.x == 0) {
+    if (P.use_ngram) S.nseen[s] += np;
+    if (np > 0) S.ncommit[s] = p0 + np;
+  }
+}
+
+// The mixer weights after a position: exponential weights (section 3.6), then renormalised.
+__device__ __forceinline__ void mixer_step(const VocabParams& P, int mode, float pt, float png,
+                                           float (&lw)[2]) {
+  if (mode != M_MIX) return;
+  lw[0] = lw[0] + P.mix_eta * logf(pt);
+  lw[1] = lw[1] + P.mix_eta * logf(png);
+  const float mx = fmaxf(lw[0], lw[1]);
+  const float ls = mx + logf(expf(lw[0] - mx) + expf(lw[1] - mx));
+  lw[0] = lw[0] - ls;
+  lw[1] = lw[1] - ls;
+}
+
+// Logsumexp partials of position j over u = z_j + b (v1_seg's reduction): every thread's 16 values.
+__device__ __forceinline__ LsePart known_lse(const float (&u)[4][4]) {
+  float m = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = fmaxf(m, u[q][i]);
+  float sum = 0.f;
+  if (m != -INFINITY)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum += expf(u[q][i] - m);
+  return wave_lse(LsePart{m, sum});
+}
+__device__ __forceinline__ void known_lse_store(const KnownChunk& C, int j, int r, int seg,
+                                                int nseg, const LsePart* wl) {
+  LsePart acc = wl[0];
+  for (int k = 1; k < kSegWaves; ++k) acc = lse_merge(acc, wl[k]);
+  C.lse[((size_t)(j & 1) * C.B + r) * nseg + seg] = acc;
+}
+
+// The chunk's first position: its logsumexp partials.
+__global__ __launch_bounds__(kSegThreads) void known_first_kernel(VocabParams P, StreamState S,
+                                                                  KnownChunk C) {
+  __shared__ LsePart wl[kSegWaves];
+  const int seg = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+  const float* z = C.z + (size_t)r * P.V;
+  const float* b = S.b + (size_t)(C.s0 + r) * P.V;
+  float u[4][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t t0 = seg_index(seg, q, tid, 0);
+    const bool in = t0 < uint32_t(P.V);
+    const f4v zz = *reinterpret_cast<const f4v*>(z + (in ? t0 : 0));
+    const f4v bb = *reinterpret_cast<const f4v*>(b + (in ? t0 : 0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u[q][i] = !in ? -INFINITY : (P.use_head ? zz[i] + bb[i] : zz[i]);
+  }
+  const LsePart part = known_lse(u);
+  if ((tid & 63) == 0) wl[tid >> 6] = part;
+  __syncthreads();
+  if (tid == 0) known_lse_store(C, 0, r, seg, gridDim.x, wl);
+}
+
+// Position j of the chunk, one workgroup per (segment, row); see above for what it leaves.  A chain
+// of np such launches is what a stream's encoding takes, so what counts is the time of one: every
+// load goes out at once, and the reductions stay in registers.  7.0 us a position at one stream
+// (V = 49,152), where logsumexp, count, scan and update were four dependent launches of 21.9 us
+// ordered against the n-gram's three by events: encoding 4,096 tokens took 208.5 ms, now 90.2 ms
+// (the transformer passes run beside the chain and bound it).  64 streams: 21.5 us a position
+// against 39.9 us, bound by memory.
+__global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, StreamState S,
+                                                                 KnownChunk C, int j) {
+  __shared__ LsePart s_lse[kSegWaves];
+  __shared__ uint64_t s_sum[kSegWaves], s_best[kSegWaves];
+  __shared__ uint32_t s_before[kSegWaves];
+  __shared__ int s_bad[kSegWaves];
+  const int seg = blockIdx.x, r = blockIdx.y, nseg = gridDim.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int V = P.V, s = C.s0 + r;
+  const size_t row = (size_t)j * C.B + r;
+  const bool more = j + 1 < C.np;
+  const float* z = C.z + row * V;
+  const float* zn = more ? z + (size_t)C.B * V : z;
+  const float* gp = C.png ? C.png + row * V : z;
+  float* b = S.b + (size_t)s * V;
+  RowVec v;
+  f4v z2[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    // (an index past the end reads the row's start; masked below)
+    const uint32_t t0 = seg_index(seg, q, tid, 0), tc = t0 < uint32_t(V) ? t0 : 0;
+    v.z[q] = *reinterpret_cast<const f4v*>(z + tc);
+    v.b[q] = *reinterpret_cast<const f4v*>(b + tc);
+    v.g[q] = *reinterpret_cast<const f4v*>(gp + tc);
+    z2[q] = *reinterpret_cast<const f4v*>(zn + tc);
+  }
+  const LsePart mine = C.lse[((size_t)(j & 1) * C.B + r) * nseg + min(lane, nseg - 1)];
+  const KnownRec last = C.rec[j > 0 ? row - C.B : row];
+  const float* lws = j > 1 ? C.lw + ((size_t)((j - 1) & 1) * C.B + r) * 2
+                           : S.lw + (size_t)s * kMaxExperts;
+  float lw[2] = {lws[0], lws[1]};
+  const int mode = C.mode[row], tok = C.tok[row];
+  const int mode2 = C.mode[more ? row + C.B : row];
+  const int left = C.left[r];
+  if (j >= left) return;  // the row has ended (uniform over the workgroup)
+  // mixer weights of this position: the last position's outcome, taken by every workgroup alike
+  if (j > 0) {
+    mixer_step(P, last.mode, last.pt, last.png, lw);
+    if (seg == 0 && tid < 2) C.lw[((size_t)(j & 1) * C.B + r) * 2 + tid] = tid ? lw[1] : lw[0];
+  }
+  RowIn R;
+  R.V = V;
+  R.K = P.K;
+  R.mode = mode;
+  R.use_head = P.use_head;
+  R.lse = uses_llm(mode) ? lane_row_lse(mine, nseg, lane) : 0.f;
+  R.w[0] = expf(lw[0]);
+  R.w[1] = expf(lw[1]);
+  float p[4][4], pt[4][4];
+  row_probs<false>(R, v, seg, tid, p, pt);
+  // count partial of the segment, the counts before the token's, and the token's own entry
+  const uint32_t m = P.total - uint32_t(V);
+  uint32_t sum = 0, before = 0;
+  int bad = 0;
+  uint64_t best = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t t = seg_index(seg, q, tid, i);
+      const float x = p[q][i];
+      const uint32_t c = t < uint32_t(V) ? floor_count(x, m) : 0u;
+      sum += c;
+      before += t < uint32_t(tok) ? c : 0u;
+      if (t < uint32_t(V)) {
+        if (!(x >= 0.f && x <= 1.f)) bad = 1;
+        // probabilities are not negative: their bits order them; the lowest index wins ties
+        const uint64_t key = (uint64_t(__float_as_uint(x)) << 32) | (0xFFFFFFFFu - t);
+        best = key > best ? key : best;
+      }
+      if (t == uint32_t(tok)) {
+        KnownRec& o = C.rec[row];
+        o.c = c;
+        o.p = x;
+        o.pt = pt[q][i];
+        o.png = C.png ? v.g[q][i] : 0.f;
+        o.mode = mode;
+      }
+    }
+  // bias-head step on -log ptilde(t*), section 3.7, then the next position's logsumexp with it
+  const bool learn = P.use_head && uses_llm(mode);
+  float u[4][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t t0 = seg_index(seg, q, tid, 0);
+    f4v nb;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float ind = int(t0) + i == tok ? 1.f : 0.f;
+      nb[i] = learn ? v.b[q][i] - P.head_lr * (pt[q][i] - ind) : v.b[q][i];
+      u[q][i] = t0 >= uint32_t(V) ? -INFINITY : (P.use_head ? z2[q][i] + nb[i] : z2[q][i]);
+    }
+    if (learn && t0 < uint32_t(V)) *reinterpret_cast<f4v*>(b + t0) = nb;
+  }
+  // (a thread's 16 counts are below 2^28, so a wave's fit in two sums of 16-bit halves)
+  const uint32_t lo = wave_sum_u32(sum & 0xFFFFu), hi = wave_sum_u32(sum >> 16);
+  before = wave_sum_u32(before);
+  best = wave_max_u64(best);
+  const int any_bad = __any(bad) ? 1 : 0;
+  const bool lse2 = more && j + 1 < left && uses_llm(mode2);
+  const LsePart part = lse2 ? known_lse(u) : LsePart{-INFINITY, 0.f};
+  if (lane == 0) {
+    s_sum[w] = (uint64_t(hi) << 16) + lo;
+    s_before[w] = before;
+    s_best[w] = best;
+    s_bad[w] = any_bad;
+    s_lse[w] = part;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    uint64_t tot = 0, bk = 0;
+    uint32_t bf = 0;
+    int bd = 0;
+#pragma unroll
+    for (int k = 0; k < kSegWaves; ++k) {
+      tot += s_sum[k];
+      bf += s_before[k];
+      bk = s_best[k] > bk ? s_best[k] : bk;
+      bd |= s_bad[k];
+    }
+    SegPartial sp;
+    sp.sum = tot >= 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(tot);
+    sp.maxv = __uint_as_float(uint32_t(bk >> 32));
+    sp.maxi = 0xFFFFFFFFu - uint32_t(bk);
+    sp.bad = bd;
+    static_cast<SegPartial*>(C.segs)[row * nseg + seg] = sp;
+    if (uint32_t(tok) / kSeg == uint32_t(seg)) C.rec[row].before = bf;
+  }
+  if (tid == 64 && lse2) known_lse_store(C, j + 1, r, seg, nseg, s_lse);
+}
+
+// The intervals of the chunk's positions from their count partials, and the mixer weights after
+// each row's last position.  A position whose distribution is invalid raises the flag: the caller
+// then takes the positions one by one, where the models stop at such a position.
+__global__ __launch_bounds__(64) void known_finish_kernel(VocabParams P, StreamState S,
+                                                          KnownChunk C, int p0, int nseg) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= C.np * C.B) return;
+  const int j = e / C.B, r = e % C.B, s = C.s0 + r;
+  const int np = min(C.np, C.left[r]);
+  if (j >= np) return;
+  const KnownRec o = C.rec[e];
+  const uint32_t tok = uint32_t(C.tok[e]), seg = tok / kSeg;
+  const SegPartial* parts = static_cast<const SegPartial*>(C.segs) + (size_t)e * nseg;
+  const RowQuant q = seg_combine(parts, nseg, seg, P.V, P.total);
+  uint32_t cl = q.start + o.before, c = o.c;
+  if (q.argmax / kSeg == seg && q.argmax < tok) cl += uint32_t(q.residual);
+  if (q.argmax == tok) c += uint32_t(q.residual);
+  if (q.status) atomicOr(C.bad, 1);
+  if (C.iv) {
+    const size_t at = (size_t)s * S.maxT + p0 + j;
+    C.iv[2 * at] = cl;
+    C.iv[2 * at + 1] = cl + c;
+    C.ptok[at] = o.p;
+  }
+  if (j == np - 1) {
+    float* out = S.lw + (size_t)s * kMaxExperts;
+    const float* src = j > 0 ? C.lw + ((size_t)(j & 1) * C.B + r) * 2 : out;
+    float lw[2] = {src[0], src[1]};
+    mixer_step(P, o.mode, o.pt, o.png, lw);
+    out[0] = lw[0];
+    out[1] = lw[1];
+  }
 }
 
 // ---- reset -----------------------------------------------------------------------------------
 
-__global__ void state_reset_kernel(VocabParams P, StreamState S, int n, float w_llm) {
-  const int s = blockIdx.x;
-  if (s >= n) return;
+__global__ void state_reset_kernel(VocabParams P, StreamState S, int s0, float w_llm) {
+  const int s = s0 + blockIdx.x;
   const int V = P.V;
   for (int t = threadIdx.x; t < V; t += blockDim.x) {
     S.b[(size_t)s * V + t] = 0.f;
@@ -1202,7 +1858,7 @@ void launch_ensemble_backward(const float* z, float* b, float* theta, const floa
 
 // ---- launchers ------------------------------------------------------------------------------
 
-void launch_vocab_dist(const VocabParams& P, const StreamState& S, const StepArgs& A,
+void launch_vocab_step(const VocabParams& P, const StreamState& S, const StepArgs& A,
                        hipStream_t s) {
   if (A.B <= 0) return;
   const int nseg = int(ceil_div(P.V, kSeg));
@@ -1212,47 +1868,62 @@ void launch_vocab_dist(const VocabParams& P, const StreamState& S, const StepArg
   hipLaunchKernelGGL(vocab_scan_kernel, grid, dim3(kSegThreads), 0, s, P, S, A);
   if (!A.no_update && P.ensemble)
     hipLaunchKernelGGL(ensemble_bias_kernel, grid, dim3(kSegThreads), 0, s, P, S, A);
+  if (!A.no_update)
+    hipLaunchKernelGGL(ngram_update_kernel, dim3(A.B), dim3(64), 0, s, P, S, A);
   NC_HIP(hipGetLastError());
-}
-
-void launch_ngram_update(const VocabParams& P, const StreamState& S, const StepArgs& A,
-                         hipStream_t s) {
-  if (A.B <= 0 || A.no_update || !A.upd) return;
-  hipLaunchKernelGGL(ngram_update_kernel, dim3(A.B), dim3(64), 0, s, P, S, A);
-  NC_HIP(hipGetLastError());
-}
-
-void launch_vocab_step(const VocabParams& P, const StreamState& S, const StepArgs& A,
-                       hipStream_t s) {
-  launch_vocab_dist(P, S, A, s);
-  launch_ngram_update(P, S, A, s);
 }
 
 void launch_ngram_predict(const VocabParams& P, const StreamState& S, const int32_t* rows, int B,
-                          NgPart* parts, StepOut* step_out, const Outcome* out, hipStream_t s,
-                          int pos, const int* pos_base) {
+                          NgPart* parts, StepOut* step_out, const Outcome* out, hipStream_t s) {
   if (B <= 0) return;
   const int nseg = int(ceil_div(P.V, kSeg));
   hipLaunchKernelGGL(ngram_dense_kernel, dim3(nseg, B), dim3(kSegThreads), 0, s, P, S, rows,
                      parts);
   hipLaunchKernelGGL(ngram_fix_kernel, dim3(B), dim3(256), 0, s, P, S, rows, parts, nseg,
-                     step_out, out, pos, pos_base);
+                     step_out, out);
   NC_HIP(hipGetLastError());
 }
 
-__global__ void set_int_kernel(int* p, int v) {
-  if (threadIdx.x == 0) *p = v;
-}
-
-void launch_set_int(int* p, int v, hipStream_t s) {
-  hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(64), 0, s, p, v);
-  NC_HIP(hipGetLastError());
-}
-
-void launch_state_reset(const VocabParams& P, const StreamState& S, int n_streams, float w_llm,
+void launch_known_ngram(const VocabParams& P, const StreamState& S, const KnownChunk& C, int p0,
                         hipStream_t s) {
+  if (C.B <= 0 || C.np <= 0) return;
+  const int nseg = int(ceil_div(P.V, kSeg));
+  if (P.use_ngram) {
+    hipLaunchKernelGGL(known_advance_kernel, dim3(P.K, C.B), dim3(64), 0, s, P, S, C, p0);
+    hipLaunchKernelGGL(known_dense_kernel, dim3(nseg, ceil_div(C.np, kKnownRun), C.B),
+                       dim3(kSegThreads), 0, s, P, S, C, p0);
+    hipLaunchKernelGGL(known_fix_kernel, dim3(C.np, C.B), dim3(kSegThreads),
+                       C.np * sizeof(int32_t), s, P, S, C, p0, nseg);
+  } else {
+    hipLaunchKernelGGL(known_tokens_kernel, dim3(ceil_div(C.np * C.B, 256)), dim3(256), 0, s, S, C,
+                       p0);
+  }
+  hipLaunchKernelGGL(known_commit_kernel, dim3(C.B), dim3(kSegThreads), 0, s, P, S, C, p0);
+  NC_HIP(hipGetLastError());
+}
+
+void launch_known_steps(const VocabParams& P, const StreamState& S, const KnownChunk& C,
+                        hipStream_t s) {
+  if (C.B <= 0 || C.np <= 0) return;
+  const dim3 grid(ceil_div(P.V, kSeg), C.B);
+  hipLaunchKernelGGL(known_first_kernel, grid, dim3(kSegThreads), 0, s, P, S, C);
+  for (int j = 0; j < C.np; ++j)
+    hipLaunchKernelGGL(known_step_kernel, grid, dim3(kSegThreads), 0, s, P, S, C, j);
+  NC_HIP(hipGetLastError());
+}
+
+void launch_known_finish(const VocabParams& P, const StreamState& S, const KnownChunk& C, int p0,
+                         hipStream_t s) {
+  if (C.B <= 0 || C.np <= 0) return;
+  hipLaunchKernelGGL(known_finish_kernel, dim3(ceil_div(C.np * C.B, 64)), dim3(64), 0, s, P, S, C,
+                     p0, int(ceil_div(P.V, kSeg)));
+  NC_HIP(hipGetLastError());
+}
+
+void launch_state_reset(const VocabParams& P, const StreamState& S, int s0, int n_streams,
+                        float w_llm, hipStream_t s) {
   if (n_streams <= 0) return;
-  hipLaunchKernelGGL(state_reset_kernel, dim3(n_streams), dim3(256), 0, s, P, S, n_streams, w_llm);
+  hipLaunchKernelGGL(state_reset_kernel, dim3(n_streams), dim3(256), 0, s, P, S, s0, w_llm);
   NC_HIP(hipGetLastError());
 }
 

@@ -76,10 +76,9 @@ struct nc_ctx {
   int prec = P_F32, att = P_F32;
   int dev = 0;
   hipStream_t st = nullptr;
-  // batched encode: the n-gram update and prediction of the next position run on st2 beside the
-  // current position's distribution on st (events ev_dist[parity], ev_pred order them)
-  hipStream_t st2 = nullptr;
-  hipEvent_t ev_dist[2] = {nullptr, nullptr}, ev_pred = nullptr;
+  // chunks of known tokens: the transformer and output layer run on st, the n-gram side on st2 and
+  // the position-by-position chain on st3, on two sets of chunk buffers in turn
+  hipStream_t st2 = nullptr, st3 = nullptr;
   int d = 0, hq = 0, hk = 0, hd = 0, F = 0, V = 0, nl = 0, R = 0;
   // weights
   std::vector<void*> allocs;
@@ -121,7 +120,26 @@ struct nc_ctx {
   size_t spin_bytes = 0;
   // step buffers
   DevBuf<float> z;
-  DevBuf<float> zseg;  // encode: logits of a chunk of positions [pos][stream slot][V]
+  DevBuf<float> zseg;  // tuner: output-layer scratch
+  // buffers of a chunk of known tokens (KnownChunk), and the events that order its streams
+  struct KnownBufs {
+    DevBuf<float> z, png, lw;
+    DevBuf<int2> slots, counts;
+    DevBuf<NgPart> ngp;
+    DevBuf<int32_t> tok, mode, left;
+    DevBuf<LsePart> lse;
+    DevBuf<SegPartial> segs;
+    DevBuf<KnownRec> rec;
+    hipEvent_t ngram = nullptr, logits = nullptr, done = nullptr;
+  } kb[2];
+  DevBuf<int32_t> kbad;  // set by a chunk with an invalid distribution
+  // staged inputs of the passes over known tokens, two in turn
+  struct StageSlot {
+    DevBuf<uint8_t> d;
+    void* h = nullptr;
+    size_t bytes = 0;
+    hipEvent_t up = nullptr, done = nullptr;
+  } slots[2];
   DevBuf<int32_t> steprows, arows;
   DevBuf<uint32_t> targets;
   DevBuf<LsePart> lsep;
@@ -169,17 +187,21 @@ struct nc_ctx {
     }
   };
   std::map<GraphKey, hipGraphExec_t> graphs;
-  // captured chunks of the batched encode's per-position steps, by (positions, active rows, the
-  // state buffers' addresses); a replay reads its first position from posbase
-  std::map<std::vector<const void*>, hipGraphExec_t> egraphs;
-  DevBuf<int32_t> posbase;
+  // captured position chains of known-token chunks, by (positions, rows, first stream, the
+  // buffers' addresses), and how often each shape has been used
+  struct ChainGraph {
+    uint64_t uses = 0;
+    hipGraphExec_t ex = nullptr;
+  };
+  std::map<std::vector<const void*>, ChainGraph> egraphs;
 
   ~nc_ctx();
 };
 
 nc_ctx::~nc_ctx() {
   if (dev >= 0) (void)hipSetDevice(dev);
-  if (st) (void)hipStreamSynchronize(st);
+  for (hipStream_t q : {st, st2, st3})
+    if (q) (void)hipStreamSynchronize(q);
   for (void* p : allocs) (void)hipFree(p);
   DevBuf<float>* fb[] = {&yb, &xss, &aws, &xinv, &hinv, &amax, &rope, &b, &png, &pk, &lw, &Hd, &pmaxd, &hlast, &x, &ptok, &z, &zseg,
                          &dbgp, &dbgpt};
@@ -212,10 +234,28 @@ nc_ctx::~nc_ctx() {
     (void)hipEventDestroy(pr.first.first);
     (void)hipEventDestroy(pr.first.second);
   }
-  for (hipEvent_t e : {ev_dist[0], ev_dist[1], ev_pred})
-    if (e) (void)hipEventDestroy(e);
+  for (KnownBufs& k : kb) {
+    for (DevBuf<float>* q : {&k.z, &k.png, &k.lw}) q->release();
+    for (DevBuf<int2>* q : {&k.slots, &k.counts}) q->release();
+    for (DevBuf<int32_t>* q : {&k.tok, &k.mode, &k.left}) q->release();
+    k.ngp.release();
+    k.lse.release();
+    k.segs.release();
+    k.rec.release();
+    for (hipEvent_t e : {k.ngram, k.logits, k.done})
+      if (e) (void)hipEventDestroy(e);
+  }
+  kbad.release();
+  for (StageSlot& q : slots) {
+    q.d.release();
+    if (q.h) (void)hipHostFree(q.h);
+    for (hipEvent_t e : {q.up, q.done})
+      if (e) (void)hipEventDestroy(e);
+  }
   for (auto& g : graphs) (void)hipGraphExecDestroy(g.second);
-  for (auto& g : egraphs) (void)hipGraphExecDestroy(g.second);
+  for (auto& g : egraphs)
+    if (g.second.ex) (void)hipGraphExecDestroy(g.second.ex);
+  if (st3) (void)hipStreamDestroy(st3);
   if (st2) (void)hipStreamDestroy(st2);
   if (st) (void)hipStreamDestroy(st);
 }
@@ -266,6 +306,7 @@ void sync(nc_ctx* c) {
   const auto t0 = std::chrono::steady_clock::now();
   NC_HIP(hipStreamSynchronize(c->st));
   NC_HIP(hipStreamSynchronize(c->st2));
+  NC_HIP(hipStreamSynchronize(c->st3));
   c->stats.wait_seconds +=
       std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   prof_flush(c);
@@ -750,7 +791,11 @@ bool profiling(const nc_ctx* c) {
 void graphs_clear(nc_ctx* c) {
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.second);
   c->graphs.clear();
-  for (auto& g : c->egraphs) (void)hipGraphExecDestroy(g.second);
+}
+
+void chain_graphs_clear(nc_ctx* c) {
+  for (auto& g : c->egraphs)
+    if (g.second.ex) (void)hipGraphExecDestroy(g.second.ex);
   c->egraphs.clear();
 }
 
@@ -883,15 +928,6 @@ StreamState make_state(nc_ctx* c) {
   return S;
 }
 
-// The state with the n-gram distribution and mode of parity p (the pipelined encode alternates
-// them by position; every other path uses parity 0).
-StreamState state_par(nc_ctx* c, int p) {
-  StreamState S = c->S;
-  S.png = c->png.p + (size_t)p * c->S_alloc * c->V;
-  S.mode = c->moded.p + (size_t)p * c->S_alloc;
-  return S;
-}
-
 bool ngram_on(const nc_ctx* c) {
   return (c->cfg.features & (NC_F_NGRAM | NC_F_ENSEMBLE)) != 0;
 }
@@ -903,6 +939,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
   NC_CHECK(n >= 1 && n <= c->cfg.max_streams, NC_E_INVALID, "n_streams must be in [1, %d]",
            c->cfg.max_streams);
   NC_CHECK(maxT >= 1, NC_E_INVALID, "max_tokens must be >= 1");
+  sync(c);  // an earlier call that failed may have left work on the streams
   const int K = c->cfg.ngram_order;
   const int V = c->V;
   if (n > c->S_alloc || maxT > c->T_alloc) {
@@ -911,7 +948,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
     while (cap < 2 * (Ta + 1)) cap <<= 1;
     const int maxctx = std::min(Ta, c->cfg.ngram_max_contexts);
     c->b.alloc((size_t)Sa * V);
-    c->png.alloc((size_t)2 * Sa * V);  // two parities (pipelined encode), parity 0 otherwise
+    c->png.alloc((size_t)Sa * V);
     if (c->cfg.features & NC_F_ENSEMBLE) c->pk.alloc((size_t)Sa * K * V);
     c->lw.alloc((size_t)Sa * kMaxExperts);
     c->Hd.alloc(Sa);
@@ -922,7 +959,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
     c->nseen.alloc(Sa);
     c->hist.alloc((size_t)Sa * Ta);
     c->ncommit.alloc(Sa);
-    c->moded.alloc((size_t)2 * Sa);
+    c->moded.alloc(Sa);
     c->next_ctx.alloc((size_t)Sa * kMaxOrder);
     c->nctx.alloc((size_t)Sa * K);
     if (ngram_on(c)) {
@@ -954,7 +991,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
   NC_HIP(hipMemsetAsync(c->vc.p, 0, c->vc.n, c->st));
   NC_HIP(hipMemsetAsync(c->hlast.p, 0, c->hlast.n * 4, c->st));
   NC_HIP(hipMemsetAsync(c->hinv.p, 0, c->hinv.n * 4, c->st));
-  launch_state_reset(c->vp, c->S, c->S_alloc, c->cfg.mix_w_llm, c->st);
+  launch_state_reset(c->vp, c->S, 0, c->S_alloc, c->cfg.mix_w_llm, c->st);
   ensure_step(c, std::max(n, 1));
   if (ngram_on(c)) {
     std::vector<int32_t> ids(n);
@@ -980,7 +1017,6 @@ StepArgs step_args(nc_ctx* c, int B, bool decode) {
   A.out = c->outc.p;
   A.step_out = c->sout.p;
   A.pos = -1;
-  A.upd = kUpdCounts | kUpdMixer;
   A.lse = 1;
   return A;
 }
@@ -1000,101 +1036,354 @@ void vocab_commit_step(nc_ctx* c, const StepArgs& A) {
   }
 }
 
-// One position of the batched encode, every row at position pos, in two streams:
-//   st:  the distribution of pos (n-gram parity pos % 2), its interval and bias step, and the
-//        mixer update, which needs the step's outcome;
-//   st2: the count updates with the known token t_pos, then the n-gram prediction of pos + 1
-//        into the other parity, which the distribution of pos - 1 was the last to read.
-// st waits for the prediction of pos (ev_pred); st2 waits for the distribution of pos - 1
-// (ev_dist of its parity; at pos 0 for everything st has queued).  Every kernel computes what the
-// sequential step computes, so the coded bytes are the same.
-// kpos >= 0: the kernels see position kpos + *A.pos_base (a step captured into a graph); the
-// first step of a capture forks st2 from st inside the capture, and its predecessors are complete
-// before the graph starts.
-void encode_step_pipelined(nc_ctx* c, StepArgs A, int pos, int kpos = -1,
-                           bool capture_first = false) {
-  const double V = c->V;
-  const int par = pos & 1;
-  const StreamState Sp = state_par(c, par), Sn = state_par(c, par ^ 1);
-  A.pos = kpos >= 0 ? kpos : pos;
-  if (pos > 0 && !capture_first) NC_HIP(hipStreamWaitEvent(c->st, c->ev_pred, 0));
-  prof_begin(c, NC_K_VOCAB);
-  launch_vocab_dist(c->vp, Sp, A, c->st);
-  A.upd = kUpdMixer;
-  launch_ngram_update(c->vp, Sp, A, c->st);
-  prof_end(c, NC_K_VOCAB, A.B * V * 4.0 * (2 + 2 + 2 + 2 + 1), A.B * V * 12.0);
-  NC_HIP(hipEventRecord(c->ev_dist[par], c->st));
-  NC_HIP(hipStreamWaitEvent(c->st2, c->ev_dist[(pos > 0 && !capture_first) ? par ^ 1 : par], 0));
-  A.upd = kUpdCounts;
-  launch_ngram_update(c->vp, Sn, A, c->st2);
-  prof_begin(c, NC_K_NGRAM, c->st2);
-  launch_ngram_predict(c->vp, Sn, A.rows, A.B, c->ngp.p, nullptr, nullptr, c->st2, A.pos + 1,
-                       A.pos_base);
-  prof_end(c, NC_K_NGRAM, A.B * V * 4.0 * 2, A.B * V * 8.0, c->st2);
-  NC_HIP(hipEventRecord(c->ev_pred, c->st2));
+// ---- passes over known tokens ---------------------------------------------------------------
+
+// Output-layer rows of a chunk that runs beside the next one's output layer.
+nc_ctx::KnownBufs& known_bufs(nc_ctx* c, int par, int np, int B) {
+  nc_ctx::KnownBufs& k = c->kb[par];
+  const size_t n = size_t(np) * B, V = c->V, K = c->cfg.ngram_order;
+  const size_t nseg = ceil_div(V, kSeg);
+  k.z.alloc(n * V);
+  if (ngram_on(c)) {
+    k.png.alloc(n * V);
+    k.slots.alloc(n * K * kSlots);
+    k.counts.alloc(n * K);
+    k.ngp.alloc(n * nseg);
+  }
+  k.lw.alloc(size_t(2) * B * 2);
+  k.tok.alloc(n);
+  k.mode.alloc(n);
+  k.left.alloc(B);
+  k.lse.alloc(size_t(2) * B * nseg);
+  k.segs.alloc(n * nseg + 16);
+  k.rec.alloc(n);
+  return k;
 }
 
-// Positions p0 .. p0 + np - 1 of the pipelined encode (B rows each, logits in zseg rows
-// (i - p0) * B), captured on the first use of the shape and replayed afterwards: one launch
-// instead of about ten launches and event calls per position.  p0 is even, so the parity
-// buffers alternate as in the direct path; the kernels compute exactly what they compute there.
-void encode_chunk_graph(nc_ctx* c, int p0, int np, int B) {
-  c->posbase.alloc(1);
-  const StreamState S = c->S;
-  std::vector<const void*> key{reinterpret_cast<const void*>(size_t(np)),
-                               reinterpret_cast<const void*>(size_t(B)),
-                               reinterpret_cast<const void*>(size_t(c->n_streams)),
-                               c->zseg.p, c->iv.p, c->ptok.p, c->steprows.p, c->lsep.p, c->segp.p,
-                               c->ngp.p, c->outc.p, c->posbase.p, S.b, S.png, S.uni, S.hist,
-                               S.pool, S.keys, S.lw, S.mode,
-                               reinterpret_cast<const void*>(size_t(c->S_alloc)),
-                               reinterpret_cast<const void*>(size_t(c->T_alloc)),
-                               reinterpret_cast<const void*>(size_t(S.cap)),
-                               reinterpret_cast<const void*>(size_t(S.maxctx))};
-  // everything queued before the chunk, on both streams, precedes the replay
-  NC_HIP(hipStreamWaitEvent(c->st, c->ev_pred, 0));
-  launch_set_int(c->posbase.p, p0, c->st);
-  auto it = c->egraphs.find(key);
-  if (it == c->egraphs.end()) {
-    if (c->egraphs.size() >= 64) {
-      for (auto& g : c->egraphs) (void)hipGraphExecDestroy(g.second);
-      c->egraphs.clear();
-    }
-    hipGraph_t g = nullptr;
-    NC_HIP(hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal));
+// Inputs of a pass over known tokens: uploaded on st without waiting for the passes before, which
+// read the other slot.
+const uint8_t* upload_slot(nc_ctx* c, int slot, const Stage& s) {
+  nc_ctx::StageSlot& q = c->slots[slot];
+  const size_t n = std::max<size_t>(s.h.size(), 256);
+  const auto t0 = std::chrono::steady_clock::now();
+  NC_HIP(hipEventSynchronize(q.done));  // the slot's last pass has been consumed
+  c->stats.wait_seconds +=
+      std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  if (n > q.bytes) {
+    if (q.h) NC_HIP(hipHostFree(q.h));
+    q.h = nullptr;
+    q.bytes = 0;
+    NC_HIP(hipHostMalloc(&q.h, n * 2, hipHostMallocDefault));
+    q.bytes = n * 2;
+  }
+  q.d.alloc(q.bytes);
+  std::memcpy(q.h, s.h.data(), s.h.size());
+  NC_HIP(hipMemcpyAsync(q.d.p, q.h, s.h.size(), hipMemcpyHostToDevice, c->st));
+  NC_HIP(hipEventRecord(q.up, c->st));
+  return q.d.p;
+}
+
+// The chunk's position chain on st3, replayed from a captured graph from its shape's second use on
+// (one launch in place of one per position; the kernels and their arguments are the same).
+void known_chain(nc_ctx* c, const KnownChunk& C) {
+  if ((c->cfg.features & NC_F_EAGER) || profiling(c) || C.np < 2) {
+    launch_known_steps(c->vp, c->S, C, c->st3);
+    return;
+  }
+  auto num = [](size_t v) { return reinterpret_cast<const void*>(v); };
+  const std::vector<const void*> key{num(C.np), num(C.B), num(C.s0), C.left, C.z, C.png, C.tok,
+                                     C.mode, C.lse, C.lw, C.segs, C.rec, c->S.b, c->S.lw};
+  if (c->egraphs.size() >= 64 && !c->egraphs.count(key)) {
+    NC_HIP(hipStreamSynchronize(c->st3));
+    chain_graphs_clear(c);
+  }
+  nc_ctx::ChainGraph& g = c->egraphs[key];
+  if (g.uses++ == 0) {
+    launch_known_steps(c->vp, c->S, C, c->st3);
+    return;
+  }
+  if (!g.ex) {
+    hipGraph_t graph = nullptr;
+    NC_HIP(hipStreamBeginCapture(c->st3, hipStreamCaptureModeThreadLocal));
     try {
-      for (int k = 0; k < np; ++k) {
-        StepArgs A = step_args(c, B, false);
-        A.z = c->zseg.p + size_t(k) * c->n_streams * size_t(c->V);
-        A.step_out = nullptr;
-        A.iv = c->iv.p;
-        A.ptok = c->ptok.p;
-        A.pos_base = c->posbase.p;
-        encode_step_pipelined(c, A, p0 + k, k, k == 0);
-      }
-      NC_HIP(hipStreamWaitEvent(c->st, c->ev_pred, 0));  // st2 joins the capture
+      launch_known_steps(c->vp, c->S, C, c->st3);
     } catch (...) {
       hipGraph_t tmp = nullptr;
-      (void)hipStreamEndCapture(c->st, &tmp);
+      (void)hipStreamEndCapture(c->st3, &tmp);
       if (tmp) (void)hipGraphDestroy(tmp);
       throw;
     }
-    NC_HIP(hipStreamEndCapture(c->st, &g));
+    NC_HIP(hipStreamEndCapture(c->st3, &graph));
     hipGraphExec_t ex = nullptr;
-    const hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
+    const hipError_t e = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(graph);
     NC_HIP(e);
-    it = c->egraphs.emplace(key, ex).first;
+    g.ex = ex;
     c->stats.graph_captures += 1;
   }
-  NC_HIP(hipGraphLaunch(it->second, c->st));
+  NC_HIP(hipGraphLaunch(g.ex, c->st3));
   c->stats.graph_replays += 1;
-  // Events recorded inside a capture order the graph's own nodes only; a later direct step waits
-  // on these (the chunk's last distribution and prediction), so they are recorded again after
-  // the whole replay.
-  NC_HIP(hipEventRecord(c->ev_pred, c->st));
-  NC_HIP(hipEventRecord(c->ev_dist[0], c->st));
-  NC_HIP(hipEventRecord(c->ev_dist[1], c->st));
+}
+
+// Chunks of one call: which buffer set is next.
+struct KnownRun {
+  int chunk = 0;
+};
+
+// Positions p0 .. p0 + np - 1 of streams s0 .. s0 + B - 1 (stream s0 + r has left[r] of them).  The
+// n-gram side first: it depends on the tokens only and runs on st2 beside the transformer pass.
+KnownChunk known_begin(nc_ctx* c, KnownRun& run, const nc_ctx::StageSlot& slot, size_t off_left,
+                       int s0, int B, int np, int p0, bool intervals) {
+  const int par = run.chunk++ & 1;
+  nc_ctx::KnownBufs& k = known_bufs(c, par, np, B);
+  KnownChunk C{};
+  C.B = B;
+  C.np = np;
+  C.s0 = s0;
+  C.left = k.left.p;
+  C.z = k.z.p;
+  C.png = ngram_on(c) ? k.png.p : nullptr;
+  C.slots = k.slots.p;
+  C.counts = k.counts.p;
+  C.ngp = k.ngp.p;
+  C.tok = k.tok.p;
+  C.mode = k.mode.p;
+  C.lse = k.lse.p;
+  C.lw = k.lw.p;
+  C.segs = k.segs.p;
+  C.rec = k.rec.p;
+  C.iv = intervals ? c->iv.p : nullptr;
+  C.ptok = intervals ? c->ptok.p : nullptr;
+  C.bad = c->kbad.p;
+  NC_HIP(hipStreamWaitEvent(c->st2, k.done, 0));  // the set's last chunk has been consumed
+  NC_HIP(hipStreamWaitEvent(c->st2, slot.up, 0));
+  NC_HIP(hipMemcpyAsync(k.left.p, slot.d.p + off_left, size_t(B) * 4, hipMemcpyDeviceToDevice,
+                        c->st2));
+  prof_begin(c, NC_K_NGRAM, c->st2);
+  launch_known_ngram(c->vp, c->S, C, p0, c->st2);
+  prof_end(c, NC_K_NGRAM, double(np) * B * c->V * 4.0 * 2, double(np) * B * c->V * 8.0, c->st2);
+  NC_HIP(hipEventRecord(k.ngram, c->st2));
+  return C;
+}
+
+// The chunk's logits from rows ar[j * B + r] of the pass just run, then its chain.
+void known_end(nc_ctx* c, const KnownRun& run, const KnownChunk& C, const int32_t* ar, int p0) {
+  nc_ctx::KnownBufs& k = c->kb[(run.chunk - 1) & 1];
+  NC_HIP(hipStreamWaitEvent(c->st, k.done, 0));
+  run_lm_head(c, c->yb.p, c->xinv.p, ar, C.np * C.B, k.z.p);
+  NC_HIP(hipEventRecord(k.logits, c->st));
+  NC_HIP(hipStreamWaitEvent(c->st3, k.ngram, 0));
+  NC_HIP(hipStreamWaitEvent(c->st3, k.logits, 0));
+  // per row: z read twice (for its logsumexp beside the position before, and for its own step),
+  // b read and written, p_ng read
+  const double V = c->V, n = double(C.np) * C.B;
+  prof_begin(c, NC_K_VOCAB, c->st3);
+  known_chain(c, C);
+  prof_end(c, NC_K_VOCAB, n * V * 4.0 * 5, n * V * 12.0, c->st3);
+  launch_known_finish(c->vp, c->S, C, p0, c->st3);
+  NC_HIP(hipEventRecord(k.done, c->st3));
+}
+
+// Transformer rows of x positions [a, a + C) of every stream with a token there (teacher forcing);
+// off[k]: the pass row of stream k's position a.
+std::vector<RowMeta> known_rows(const std::vector<const int32_t*>& tok,
+                                const std::vector<size_t>& len, size_t a, size_t C,
+                                std::vector<int>& off) {
+  std::vector<RowMeta> rows;
+  for (size_t k = 0; k < len.size() && len[k] > a; ++k) {
+    off[k] = int(rows.size());
+    for (size_t j = a; j < std::min(len[k], a + C); ++j)
+      rows.push_back(RowMeta{int(k), int(j), j == 0 ? kBOS : tok[k][j - 1], 0});
+  }
+  return rows;
+}
+
+// Encode from reset streams whose tokens are in hist (lengths not increasing): intervals and
+// probabilities of every position into iv and ptok, in chunks of known tokens.  False if some
+// distribution was invalid; nothing is then to be used.
+bool encode_known(nc_ctx* c, const std::vector<const int32_t*>& tok,
+                  const std::vector<size_t>& len) {
+  const size_t C = c->cfg.slide, maxn = len.empty() ? 0 : len[0];
+  const int n = int(len.size());
+  NC_HIP(hipMemsetAsync(c->kbad.p, 0, 4, c->st));
+  NC_HIP(hipStreamSynchronize(c->st));
+  KnownRun run;
+  for (size_t a = 0; a < maxn; a += C) {
+    std::vector<int> off(n, 0);
+    PassPlan plan = plan_pass(c, known_rows(tok, len, a, C, off));
+    const size_t seg_len = std::min(C, maxn - a);
+    // The output layer depends only on the teacher-forced pass, so it runs once per chunk of
+    // positions (up to kEncodeHeadRows rows, one per position and stream active at its start).
+    struct Piece {
+      size_t i0;
+      int np, B;
+      size_t off_ar, off_left;
+    };
+    std::vector<Piece> pieces;
+    Stage stg;
+    stage_pass(stg, plan);
+    for (size_t i0 = 0; i0 < seg_len;) {
+      int B = 0;
+      while (B < n && len[B] > a + i0) ++B;
+      const int np = int(std::min(seg_len - i0, size_t(std::max(1, kEncodeHeadRows / B))));
+      std::vector<int32_t> ar(size_t(np) * B, 0), left(B);
+      for (int k = 0; k < B; ++k) {
+        left[k] = int(std::min<size_t>(np, len[k] - (a + i0)));
+        for (int j = 0; j < left[k]; ++j) ar[size_t(j) * B + k] = off[k] + int(i0) + j;
+      }
+      const size_t off_ar = stg.put(ar.data(), ar.size() * 4);
+      pieces.push_back(Piece{i0, np, B, off_ar, stg.put(left.data(), left.size() * 4)});
+      i0 += np;
+    }
+    const int slot = int((a / C) & 1);
+    const uint8_t* dst = upload_slot(c, slot, stg);
+    for (size_t q = 0; q < pieces.size(); ++q) {
+      const Piece& pc = pieces[q];
+      const int p0 = int(a + pc.i0);
+      const KnownChunk K = known_begin(c, run, c->slots[slot], pc.off_left, 0, pc.B, pc.np, p0,
+                                       true);
+      if (q == 0) run_pass(c, plan, dst);
+      known_end(c, run, K, reinterpret_cast<const int32_t*>(dst + pc.off_ar), p0);
+    }
+    NC_HIP(hipEventRecord(c->slots[slot].done, c->st3));
+  }
+  sync(c);
+  int32_t bad = 0;
+  d2h(c, &bad, c->kbad.p, 1);
+  return bad == 0;
+}
+
+// The same, one coding step per position (the ensemble head, and streams with an invalid
+// distribution): every position's counts take its known token.
+void encode_steps(nc_ctx* c, const std::vector<const int32_t*>& tok,
+                  const std::vector<size_t>& len) {
+  const size_t C = c->cfg.slide, maxn = len.empty() ? 0 : len[0];
+  const int n = int(len.size());
+  std::vector<int32_t> ids(n);
+  std::iota(ids.begin(), ids.end(), 0);
+  set_steprows(c, ids.data(), ids.size());
+  const bool given = ngram_on(c) && !(c->cfg.features & NC_F_ENSEMBLE);
+  nc_ctx::KnownBufs& k = c->kb[0];
+  for (size_t a = 0; a < maxn; a += C) {
+    std::vector<int> off(n, 0);
+    PassPlan plan = plan_pass(c, known_rows(tok, len, a, C, off));
+    const size_t seg_len = std::min(C, maxn - a);
+    std::vector<int32_t> ar(seg_len * n, 0);
+    std::vector<int> active(seg_len, 0);
+    for (size_t i = 0; i < seg_len; ++i)
+      for (int s = 0; s < n && len[s] > a + i; ++s) {
+        ar[i * n + s] = off[s] + int(i);
+        active[i] = s + 1;
+      }
+    Stage stg;
+    stage_pass(stg, plan);
+    const size_t off_ar = stg.put(ar.data(), ar.size() * 4);
+    const uint8_t* dst = upload_stage(c, stg);
+    run_pass(c, plan, dst);
+    const int32_t* seg_ar = reinterpret_cast<const int32_t*>(dst + off_ar);
+    const int pc = std::max(1, std::min(int(seg_len), kEncodeHeadRows / n));
+    k.z.alloc(size_t(pc) * n * c->V);
+    for (size_t i0 = 0; i0 < seg_len; i0 += pc) {
+      const int np = int(std::min(size_t(pc), seg_len - i0));
+      run_lm_head(c, c->yb.p, c->xinv.p, seg_ar + i0 * n, np * n, k.z.p);
+      for (size_t i = i0; i < i0 + np; ++i) {
+        StepArgs A = step_args(c, active[i], false);
+        A.z = k.z.p + (i - i0) * n * size_t(c->V);
+        A.step_out = nullptr;
+        A.iv = c->iv.p;
+        A.ptok = c->ptok.p;
+        if (given) A.pos = int(a + i);
+        vocab_commit_step(c, A);
+      }
+    }
+  }
+  sync(c);
+}
+
+// Commit tokens[done .. n) of stream s one by one, exactly as the encoder's steps do.
+void commit_steps(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
+  auto& h = c->hhist[s];
+  for (size_t j = h.size(); j < n; ++j) {
+    NC_HIP(hipMemcpyAsync(c->hist.p + (size_t)s * c->T_alloc + j, tokens + j, 4,
+                          hipMemcpyHostToDevice, c->st));
+    catch_up_now(c, s, int(j));
+    run_lm_head(c, c->hlast.p, c->hinv.p, c->steprows.p, 1, c->z.p);
+    StepArgs A = step_args(c, 1, false);
+    A.step_out = nullptr;
+    vocab_commit_step(c, A);
+    h.push_back(tokens[j]);
+  }
+}
+
+// Stream s alone back to its reset state (reset_streams for one stream).
+void reset_stream(nc_ctx* c, int s) {
+  if (ngram_on(c)) {
+    const size_t per = size_t(c->cfg.ngram_order) * c->S.cap;
+    NC_HIP(hipMemsetAsync(c->kidx.p + s * per, 0xFF, per * 4, c->st));
+  }
+  const size_t kv = size_t(c->kv_stride) * prec_bytes(c->att);
+  for (int l = 0; l < c->nl; ++l)
+    for (uint8_t* p : {c->kc.p, c->vc.p})
+      NC_HIP(hipMemsetAsync(p + l * layer_kv_bytes(c) + s * kv, 0, kv, c->st));
+  launch_state_reset(c->vp, c->S, s, 1, c->cfg.mix_w_llm, c->st);
+  if (ngram_on(c))
+    launch_ngram_predict(c->vp, c->S, c->steprows.p, 1, c->ngp.p, nullptr, nullptr, c->st);
+  sync(c);
+  c->hhist[s].clear();
+  c->appended[s] = 0;
+}
+
+// Commit tokens[done .. n) of stream s (steprows holds s).  The tokens are known, so the positions'
+// logits come from passes of up to `slide` rows and their coding steps run as chunks of known
+// tokens: one launch per token in place of a transformer pass.  The passes also append position n,
+// whose distribution the caller asks for.  Bits are those of commit_steps, which takes over
+// (from a reset stream) if a distribution is invalid: its models stop at such a position.
+void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
+  auto& h = c->hhist[s];
+  if (c->cfg.features & NC_F_ENSEMBLE) return commit_steps(c, s, tokens, n);
+  // a position that is in the cache already has its output-layer operand in hlast only
+  if (c->appended[s] > int(h.size())) commit_steps(c, s, tokens, h.size() + 1);
+  if (h.size() == n) return;
+  const int first = int(h.size()), C = c->cfg.slide;
+  h2d(c, c->hist.p + (size_t)s * c->T_alloc + first, tokens + first, n - first);
+  NC_HIP(hipMemsetAsync(c->kbad.p, 0, 4, c->st));
+  sync(c);
+  KnownRun run;
+  for (int a = c->appended[s]; a <= int(n); a += C) {
+    const int e = std::min(int(n), a + C - 1);  // pass rows: positions a .. e
+    const int q0 = std::max(a, first), q1 = std::min(e, int(n) - 1), np = q1 - q0 + 1;
+    std::vector<RowMeta> rows;
+    for (int j = a; j <= e; ++j) rows.push_back(RowMeta{s, j, j == 0 ? kBOS : tokens[j - 1], 0});
+    PassPlan plan = plan_pass(c, std::move(rows));
+    Stage stg;
+    stage_pass(stg, plan);
+    std::vector<int32_t> ar(std::max(np, 0));
+    std::iota(ar.begin(), ar.end(), q0 - a);
+    const int32_t left = np;
+    const size_t off_ar = stg.put(ar.data(), ar.size() * 4), off_left = stg.put(&left, 4);
+    const int slot = run.chunk & 1;
+    const uint8_t* dst = upload_slot(c, slot, stg);
+    if (np > 0) {
+      const KnownChunk K = known_begin(c, run, c->slots[slot], off_left, s, 1, np, q0, false);
+      run_pass(c, plan, dst);
+      known_end(c, run, K, reinterpret_cast<const int32_t*>(dst + off_ar), q0);
+    } else {
+      run_pass(c, plan, dst);
+    }
+    // the slot is free once st and st3 are past the pass
+    NC_HIP(hipEventRecord(c->slots[slot].done, np > 0 ? c->st3 : c->st));
+  }
+  sync(c);
+  h.insert(h.end(), tokens + first, tokens + n);
+  c->appended[s] = int(n) + 1;
+  int32_t bad = 0;
+  d2h(c, &bad, c->kbad.p, 1);
+  if (bad) {
+    reset_stream(c, s);
+    return commit_steps(c, s, tokens, n);
+  }
+  if (ngram_on(c))
+    launch_ngram_predict(c->vp, c->S, c->steprows.p, 1, c->ngp.p, nullptr, nullptr, c->st);
 }
 
 void check_config(const nc_config* cfg) {
@@ -1145,8 +1434,14 @@ nc_status nc_create(const nc_config* cfg, const float* w, nc_ctx** out) {
     NC_HIP(hipGetDevice(&c->dev));
     NC_HIP(hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking));
     NC_HIP(hipStreamCreateWithFlags(&c->st2, hipStreamNonBlocking));
-    for (hipEvent_t* e : {&c->ev_dist[0], &c->ev_dist[1], &c->ev_pred})
-      NC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
+    NC_HIP(hipStreamCreateWithFlags(&c->st3, hipStreamNonBlocking));
+    for (auto& k : c->kb)
+      for (hipEvent_t* e : {&k.ngram, &k.logits, &k.done})
+        NC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
+    for (auto& q : c->slots)
+      for (hipEvent_t* e : {&q.up, &q.done})
+        NC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
+    c->kbad.alloc(1);
     // the attention chunk counters start at zero; every launch leaves them at zero
     c->actr.alloc(attention_counters(int(kAttnParallelItems)));
     NC_HIP(hipMemsetAsync(c->actr.p, 0, c->actr.n * sizeof(int32_t), c->st));
@@ -1326,17 +1621,7 @@ nc_status nc_probs_for_context(nc_ctx* c, uint32_t s, const int32_t* tokens, siz
                i);
     const int32_t sid = int32_t(s);
     set_steprows(c, &sid, 1);
-    // commit the new tokens one by one, exactly as the encoder does
-    for (size_t j = h.size(); j < n; ++j) {
-      NC_HIP(hipMemcpyAsync(c->hist.p + (size_t)s * c->T_alloc + j, tokens + j, 4,
-                            hipMemcpyHostToDevice, c->st));
-      catch_up_now(c, int(s), int(j));
-      run_lm_head(c, c->hlast.p, c->hinv.p, c->steprows.p, 1, c->z.p);
-      StepArgs A = step_args(c, 1, false);
-      A.step_out = nullptr;
-      vocab_commit_step(c, A);
-      h.push_back(tokens[j]);
-    }
+    if (n > h.size()) commit_tokens(c, int(s), tokens, n);
     // distribution of position n
     catch_up_now(c, int(s), int(n));
     run_lm_head(c, c->hlast.p, c->hinv.p, c->steprows.p, 1, c->z.p);
@@ -1420,94 +1705,43 @@ nc_status nc_encode_stream(nc_ctx* c, uint32_t ns, const int32_t* const* tokens,
     }
     NC_CHECK(cap_ok, NC_E_CAPACITY, "an output buffer is below nc_encode_bound");
     const auto t0 = std::chrono::steady_clock::now();
-    reset_streams(c, n, int(maxn) + 1);
-    c->stats = nc_stats{};
-    // streams by decreasing length: the active ones at position i are a prefix
+    // streams by decreasing length take the device's stream slots in that order, so that the
+    // active ones at any position are a prefix of the slots
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(),
                      [&](int a, int b) { return n_tokens[a] > n_tokens[b]; });
-    for (int s = 0; s < n; ++s) {
-      if (!n_tokens[s]) continue;
-      NC_HIP(hipMemcpyAsync(c->hist.p + (size_t)s * c->T_alloc, tokens[s], n_tokens[s] * 4,
-                            hipMemcpyHostToDevice, c->st));
+    std::vector<const int32_t*> tok(n);
+    std::vector<size_t> len(n);
+    for (int k = 0; k < n; ++k) {
+      tok[k] = tokens[order[k]];
+      len[k] = n_tokens[order[k]];
     }
-    sync(c);
-    set_steprows(c, order.data(), order.size());
-    if (ngram_on(c))
-      launch_ngram_predict(c->vp, c->S, c->steprows.p, n, c->ngp.p, nullptr, nullptr, c->st);
-    const int C = c->cfg.slide;
-    // the n-gram chain of position i + 1 can run beside the distribution of position i when no
-    // ensemble experts (P_1..P_K, single-buffered) are involved
-    const bool pipe = ngram_on(c) && !(c->cfg.features & NC_F_ENSEMBLE);
-    for (size_t a = 0; a < maxn; a += C) {
-      // prefill: x positions [a, a + C) of every stream still active (teacher forcing)
-      std::vector<RowMeta> rows;
-      std::vector<int> off(n, -1);
-      for (int k = 0; k < n; ++k) {
-        const int s = order[k];
-        if (n_tokens[s] <= a) break;
-        off[k] = int(rows.size());
-        for (size_t j = a; j < std::min(n_tokens[s], a + C); ++j)
-          rows.push_back(RowMeta{s, int(j), j == 0 ? kBOS : tokens[s][j - 1], 0});
-      }
-      PassPlan plan = plan_pass(c, std::move(rows));
-      const size_t seg_len = std::min((size_t)C, maxn - a);
-      std::vector<int32_t> ar(seg_len * n, 0);
-      std::vector<int> active(seg_len, 0);
-      for (size_t i = 0; i < seg_len; ++i)
-        for (int k = 0; k < n; ++k)
-          if (n_tokens[order[k]] > a + i) {
-            ar[i * n + k] = off[k] + int(i);
-            active[i] = k + 1;
-          }
-      Stage stg;
-      stage_pass(stg, plan);
-      const size_t off_ar = stg.put(ar.data(), ar.size() * 4);
-      const uint8_t* dst = upload_stage(c, stg);
-      run_pass(c, plan, dst);
-      const int32_t* seg_ar = reinterpret_cast<const int32_t*>(dst + off_ar);
-      // The output layer depends only on the teacher-forced pass, not on the online models, so it
-      // runs once per chunk of positions (up to kEncodeHeadRows rows, one per (position, stream
-      // slot)); every position's vocabulary step then reads its B rows of the chunk.
-      const int pc = std::max(1, std::min(int(seg_len), kEncodeHeadRows / n));
-      c->zseg.alloc(size_t(pc) * n * c->V);
-      for (size_t i0 = 0; i0 < seg_len; i0 += pc) {
-        const int np = int(std::min(size_t(pc), seg_len - i0));
-        run_lm_head(c, c->yb.p, c->xinv.p, seg_ar + i0 * n, np * n, c->zseg.p);
-        bool uniform = true;
-        for (size_t i = i0; i < i0 + np; ++i) uniform = uniform && active[i] == active[i0];
-        const size_t p0 = a + i0;
-        if (pipe && uniform && p0 > 0 && p0 % 2 == 0 && np > 1 &&
-            !(c->cfg.features & NC_F_EAGER) && !profiling(c)) {
-          encode_chunk_graph(c, int(p0), np, active[i0]);
-          continue;
-        }
-        for (size_t i = i0; i < i0 + np; ++i) {
-          StepArgs A = step_args(c, active[i], false);
-          A.z = c->zseg.p + (i - i0) * n * size_t(c->V);
-          A.step_out = nullptr;
-          A.iv = c->iv.p;
-          A.ptok = c->ptok.p;
-          if (pipe)
-            encode_step_pipelined(c, A, int(a + i));
-          else
-            vocab_commit_step(c, A);
-        }
-      }
+    // the ensemble's experts P_1..P_K are held for one position only: it codes step by step
+    bool known = !(c->cfg.features & NC_F_ENSEMBLE);
+    for (;; known = false) {
+      reset_streams(c, n, int(maxn) + 1);
+      c->stats = nc_stats{};
+      for (int k = 0; k < n; ++k)
+        if (len[k])
+          NC_HIP(hipMemcpyAsync(c->hist.p + (size_t)k * c->T_alloc, tok[k], len[k] * 4,
+                                hipMemcpyHostToDevice, c->st));
+      sync(c);
+      if (known ? encode_known(c, tok, len) : (encode_steps(c, tok, len), true)) break;
     }
-    if (pipe) NC_HIP(hipStreamWaitEvent(c->st, c->ev_pred, 0));
-    sync(c);
     // host coder, one thread per stream
+    std::vector<size_t> rank(n);
+    for (int k = 0; k < n; ++k) rank[order[k]] = k;
     std::vector<std::vector<uint32_t>> ivs(n);
     std::vector<std::vector<float>> pts(n);
     for (int s = 0; s < n; ++s) {
       ivs[s].resize(n_tokens[s] * 2);
       pts[s].resize(n_tokens[s]);
       if (!n_tokens[s]) continue;
-      NC_HIP(hipMemcpy(ivs[s].data(), c->iv.p + (size_t)s * c->T_alloc * 2, n_tokens[s] * 8,
+      const size_t k = rank[s];
+      NC_HIP(hipMemcpy(ivs[s].data(), c->iv.p + k * c->T_alloc * 2, n_tokens[s] * 8,
                        hipMemcpyDeviceToHost));
-      NC_HIP(hipMemcpy(pts[s].data(), c->ptok.p + (size_t)s * c->T_alloc, n_tokens[s] * 4,
+      NC_HIP(hipMemcpy(pts[s].data(), c->ptok.p + k * c->T_alloc, n_tokens[s] * 4,
                        hipMemcpyDeviceToHost));
     }
     std::vector<std::vector<uint8_t>> bufs(n);

@@ -101,41 +101,63 @@ struct StepArgs {
   float* dbg_p;
   float* dbg_pt;
   uint32_t* dbg_cdf;
-  // Batched encode: every row is at position pos (>= 0), known to the host, and the update kernel
-  // takes the committed token from hist; -1: the position is S.ncommit[stream].  With pos_base
-  // (a device int; a step captured into a graph that is replayed for every chunk of positions)
-  // the position is pos + *pos_base.
+  // Encode step by step: every row is at position pos (>= 0), known to the host, and the update
+  // kernel takes the committed token from hist; -1: the position is S.ncommit[stream].
   int pos;
-  const int* pos_base;
-  // Updates run by the n-gram update kernel: kUpdCounts (token history, unigram and n-gram
-  // counts, next contexts, ncommit) and / or kUpdMixer (mixer weights or ensemble gate, which
-  // need the step's outcome).
-  int upd;
   // 0: no row of the step uses the model's logits (every mode is skip), so the logsumexp pass is
   // not launched
   int lse;
 };
-constexpr int kUpdCounts = 1, kUpdMixer = 2;
+
+// A position of a chunk of known tokens: the token's count and the counts before it in its segment,
+// its coding, bias-head and n-gram probabilities, and the position's mode.
+struct KnownRec {
+  uint32_t before, c;
+  float p, pt, png;
+  int32_t mode;
+};
+
+// A chunk of np positions p0 .. p0 + np - 1 whose tokens are in hist, for rows r < B, row r being
+// stream s0 + r; row r has only the first left[r] of them.  Arrays per (position j, row r) are
+// indexed j * B + r.  The buffers belong to the chunk until its last kernel has run.
+struct KnownChunk {
+  int B, np, s0;
+  const int32_t* left;  // [B]
+  const float* z;       // [np * B][V] logits
+  float* png;           // [np * B][V] n-gram distributions, or null (no n-gram)
+  int2* slots;          // [np * B][K][kSlots] slots of the order-k context (token, count)
+  int2* counts;         // [np * B][K] slots used, sum of counts (0: no such context)
+  NgPart* ngp;          // [np * B][nseg]
+  int32_t* tok;         // [np * B]
+  int32_t* mode;        // [np * B]
+  LsePart* lse;         // [2][B][nseg], by the parity of j
+  float* lw;            // [2][B][2] mixer log-weights entering position j >= 1, by its parity
+  void* segs;           // SegPartial [np * B][nseg] (16 more are readable past the last)
+  KnownRec* rec;        // [np * B]
+  uint32_t* iv;         // [S][maxT][2] intervals, or null
+  float* ptok;          // [S][maxT]
+  int32_t* bad;         // set if a position's distribution is invalid
+};
+// The n-gram side of a chunk: table updates, every position's distribution and mode, counts.
+void launch_known_ngram(const VocabParams& P, const StreamState& S, const KnownChunk& C, int p0,
+                        hipStream_t s);
+// The chunk's positions one after the other: probabilities, count partials, bias head, mixer.
+void launch_known_steps(const VocabParams& P, const StreamState& S, const KnownChunk& C,
+                        hipStream_t s);
+// Intervals of the chunk's positions; the mixer weights after it.
+void launch_known_finish(const VocabParams& P, const StreamState& S, const KnownChunk& C, int p0,
+                         hipStream_t s);
 
 // V1-V3, V4 for the ensemble and the V5 n-gram / mixer update (unless A.no_update)
 void launch_vocab_step(const VocabParams& P, const StreamState& S, const StepArgs& A,
                        hipStream_t s);
 // n-gram distribution, entropy and mode of the current position of each row's stream; with
 // step_out, also packs the step's outcome and the next mode for the host (decode).
-// pos: the rows' position (>= 0, batched encode) or -1 (S.ncommit).
 void launch_ngram_predict(const VocabParams& P, const StreamState& S, const int32_t* rows, int B,
-                          NgPart* parts, StepOut* step_out, const Outcome* out, hipStream_t s,
-                          int pos = -1, const int* pos_base = nullptr);
-// *p = v (one thread): the position base of a replayed encode graph
-void launch_set_int(int* p, int v, hipStream_t s);
-// Only the step's distribution, interval and bias step (V1-V3, V4 for the ensemble), and only
-// the n-gram update kernel with the updates in A.upd.
-void launch_vocab_dist(const VocabParams& P, const StreamState& S, const StepArgs& A,
-                       hipStream_t s);
-void launch_ngram_update(const VocabParams& P, const StreamState& S, const StepArgs& A,
-                         hipStream_t s);
-void launch_state_reset(const VocabParams& P, const StreamState& S, int n_streams, float w_llm,
-                        hipStream_t s);
+                          NgPart* parts, StepOut* step_out, const Outcome* out, hipStream_t s);
+// streams s0 .. s0 + n_streams - 1
+void launch_state_reset(const VocabParams& P, const StreamState& S, int s0, int n_streams,
+                        float w_llm, hipStream_t s);
 // Standalone ensemble head (C ABI): forward and backward over `rows` rows sharing b and theta.
 void launch_ensemble_forward(const float* z, const float* b, const float* theta, const float* Pk,
                              const int32_t* target, int rows, int V, int nexp, float* loss,
