@@ -136,7 +136,23 @@ __device__ __forceinline__ float block_ssq16(float x) {
 __device__ __forceinline__ float inv_from_ssq(const float* ssq, int K, float eps) {
   const int nb = K / 16;
   float t = 0.f;
-  for (int b = 0; b < nb; ++b) t += ssq[b];
+  int b = 0;
+  if (nb % 4 == 0) {
+    // (rows of 16-byte multiples: sixteen blocks' sums requested together)
+    const v4f* q = reinterpret_cast<const v4f*>(ssq);
+    for (; b < nb; b += 16) {
+      v4f v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = q[min(b / 4 + u, nb / 4 - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (b + 4 * u < nb) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t += v[u][e];
+        }
+    }
+  }
+  for (; b < nb; ++b) t += ssq[b];
   return 1.0f / sqrtf(t / float(K) + eps);
 }
 
@@ -314,9 +330,13 @@ struct Frag<P_F32> {
       for (int e = 0; e < 4; ++e) f[4 * q + e] = k < K ? v[e] : 0.f;
     }
   }
+  static constexpr int STEPS = 16;
+  __device__ static void step(v4f& acc, const T& a, const T& b, int t) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], acc, 0, 0, 0);
+  }
   __device__ static void mma(v4f& acc, const T& a, const T& b) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], acc, 0, 0, 0);
+    for (int t = 0; t < STEPS; ++t) step(acc, a, b, t);
   }
 };
 template <>
@@ -342,11 +362,14 @@ struct Frag<P_BF16> {
       f[t] = k < K ? v : v4i{0, 0, 0, 0};
     }
   }
+  static constexpr int STEPS = 2;
+  __device__ static void step(v4f& acc, const T& a, const T& b, int t) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[t]),
+                                                  __builtin_bit_cast(v8bf, b[t]), acc, 0, 0, 0);
+  }
   __device__ static void mma(v4f& acc, const T& a, const T& b) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[t]),
-                                                    __builtin_bit_cast(v8bf, b[t]), acc, 0, 0, 0);
+    for (int t = 0; t < STEPS; ++t) step(acc, a, b, t);
   }
 };
 template <>
@@ -372,10 +395,13 @@ struct Frag<P_FP8> {
       f[t] = k < K ? v : 0;
     }
   }
+  static constexpr int STEPS = 2;
+  __device__ static void step(v4f& acc, const T& a, const T& b, int t) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a[t], b[t], acc, 0, 0, 0);
+  }
   __device__ static void mma(v4f& acc, const T& a, const T& b) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a[t], b[t], acc, 0, 0, 0);
+    for (int t = 0; t < STEPS; ++t) step(acc, a, b, t);
   }
 };
 
@@ -412,304 +438,265 @@ __device__ __forceinline__ void amax_flush(float* dst, float v, int lane) {
   if (lane == 0) atomic_max_abs(dst, v);
 }
 
-// ---- tile kernel (many rows): LDS-staged 64-wide K parts ----
+// Column blocks of an epilogue group: a RoPE pair {b, b + hd/32} for QKV (a single block when hd =
+// 16), a gate/up block pair for the SiLU-gated MLP, two adjacent blocks otherwise.
+__host__ __device__ __forceinline__ int group_block(int epi, int hd, int gi, int j) {
+  if (epi == E_QKV && hd > 16) {
+    const int nb = hd / 16, half = nb / 2;  // blocks per head
+    return (gi / half) * nb + gi % half + j * half;
+  }
+  return 2 * gi + j;
+}
 
-template <int P, int AM, int EPI, int WM, int WN, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_kernel(const GemmArgs a) {
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  constexpr int BM = WM * WAVES_M, BN = WN * WAVES_N;
+// ---- tile kernel (many rows) ----
+//
+// WVM x WVN waves, each RB x CB blocks of 16 x 16 outputs; the workgroup's operand rows of one
+// 64-wide K part are staged in LDS.  Parts go global -> registers -> LDS ahead of their MFMAs:
+// while part s is multiplied, the loads of the parts after it are in flight, with one barrier per
+// part.  Tiles are ordered so that the
+// workgroups of one XCD (dispatch is round-robin over the 8 XCDs) take consecutive tiles of the
+// same A rows, which then stay in that XCD's L2 while every column tile reads them.  A tile's
+// column blocks are taken in epilogue groups (group_block), so a wave holds both halves of a RoPE
+// pair, and both of a gate/up pair, in one lane.
+//
+// Every residual value and gain of a lane is loaded before its first store, so the loads overlap
+// instead of each waiting behind the previous output's store.
+template <int P, int AM, int EPI, int RB, int CB, int WVM, int WVN, bool kDeep>
+__global__ __launch_bounds__(64 * WVM * WVN, 2) void gemm_tile_kernel(
+    const GemmArgs a, int tiles_m, int tiles_n) {
+  constexpr int NT = 64 * WVM * WVN;
+  constexpr int BM = 16 * RB * WVM, BN = 16 * CB * WVN;
   constexpr int ES = PT<P>::ES;
   constexpr int ROWB = KP * ES + 16;  // padded LDS row (bytes)
-  constexpr int RB = WM / 16, CB = WN / 16;
-  constexpr int CPR = KP * ES / 16;  // 16-byte chunks per LDS row
-  __shared__ __align__(16) uint8_t lds_a[BM * ROWB];
-  __shared__ __align__(16) uint8_t lds_b[BN * ROWB];
+  constexpr int TILEB = (BM + BN) * ROWB;
+  constexpr int CPR = KP * ES / 16;                          // 16-byte chunks per staged row
+  constexpr int NCH = ((BM + BN) * CPR + NT - 1) / NT;       // chunks per thread
+  constexpr bool kEven = (BM + BN) * CPR % NT == 0;
+  static_assert(CB % 2 == 0 || EPI == E_RESID || EPI == E_STORE, "column groups are block pairs");
+  // (QKV: the epilogue keeps the tile rows' metadata and RoPE entries there)
+  constexpr int QKVB = EPI == E_QKV ? BM * int(sizeof(RowMeta) + 32 * 8) : 0;
+  __shared__ __align__(16) uint8_t lds[2 * TILEB > QKVB ? 2 * TILEB : QKVB];
   __shared__ float s_inv[BM];
   __shared__ int s_arow[BM];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int K = a.K;
+  const int wm = wave / WVN, wn = wave % WVN;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int K = a.K, S = (K + KP - 1) / KP;
+  const int hd = EPI == E_QKV ? a.hd : 64;
 
+  // XCD-aware tile order (a bijection of [0, tiles)): XCD x owns a contiguous range of tiles
+  const int nt = tiles_m * tiles_n, q8 = nt / 8, r8 = nt % 8;
+  const int bx = blockIdx.x, xcd = bx % 8;
+  const int t = xcd * q8 + min(xcd, r8) + bx / 8;
+  const int m0 = (t / tiles_n) * BM, cb0 = (t % tiles_n) * (BN / 16);
+  // first column of the tile's block j
+  auto col0 = [&](int j) {
+    const int jb = cb0 + j;
+    return 16 * (EPI == E_QKV ? group_block(EPI, hd, jb >> 1, jb & 1) : jb);
+  };
+
+  // rows past M repeat row M - 1 and columns past N column N - 1 (never stored)
   for (int r = tid; r < BM; r += NT) {
-    const int m = m0 + r;
-    s_arow[r] = m < a.M ? (a.a_rows ? a.a_rows[m] : m) : -1;
+    const int m = min(m0 + r, a.M - 1);
+    s_arow[r] = a.a_rows ? a.a_rows[m] : m;
   }
   __syncthreads();
-  for (int r = tid; r < BM; r += NT)
-    s_inv[r] = (AM == A_NORM && s_arow[r] >= 0) ? a_row_inv(a, s_arow[r]) : 1.f;
+  for (int r = tid; r < BM; r += NT) s_inv[r] = AM == A_NORM ? a_row_inv(a, s_arow[r]) : 1.f;
+
+  // global -> register staging of one K part; each thread's row addresses are resolved once.  The
+  // loads of a part are the same number on every path, and parts past the last repeat it: a load
+  // under a branch of its own would make the number in flight path-dependent, and the wait for one
+  // part would drain the parts behind it.  (Only a part that K ends in clamps its loads into the
+  // rows and zeroes the entries beyond K: a wave that has its SIMD to itself pays for every
+  // instruction between its MFMAs.)
+  constexpr int NBUF = kDeep ? 2 : 1;
+  constexpr int CE = 16 / ES;  // entries per chunk
+  v4i rg[NBUF][NCH];
+  const uint8_t* src[NCH];
+  int dst[NCH];
+#pragma unroll
+  for (int u = 0; u < NCH; ++u) {
+    const int c = min(tid + u * NT, (BM + BN) * CPR - 1), r = c / CPR, k = (c % CPR) * CE;
+    dst[u] = r * ROWB + (c % CPR) * 16;
+    if (r < BM) {
+      src[u] = static_cast<const uint8_t*>(a.A) + ((long long)s_arow[r] * K + k) * ES;
+    } else {
+      const int rr = r - BM, n = min(col0(rr / 16) + rr % 16, a.N - 1);
+      src[u] = static_cast<const uint8_t*>(a.W) + ((long long)n * K + k) * ES;
+    }
+  }
+  // entries of chunk u's row from its own first on (its position in the row is implied by dst)
+  auto room = [&](int u) { return K - ((min(tid + u * NT, (BM + BN) * CPR - 1)) % CPR) * CE; };
+  auto fetch = [&](int q, int s) {
+    const int k0 = min(s, S - 1) * KP;
+    if (k0 + KP <= K) {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u)
+        rg[q][u] = *reinterpret_cast<const v4i*>(src[u] + (long long)k0 * ES);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u)
+        rg[q][u] = *reinterpret_cast<const v4i*>(src[u] + (long long)min(k0, room(u) - CE) * ES);
+    }
+    // parts' loads stay in order, so that waiting for one leaves the later ones in flight
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto stage = [&](int q, int s, uint8_t* buf) {
+    const int k0 = min(s, S - 1) * KP;
+    __builtin_amdgcn_sched_barrier(0);  // no wait for these loads before the MFMAs
+    if (k0 + KP > K) {
+#pragma unroll
+      for (int u = 0; u < NCH; ++u)
+        if (k0 >= room(u)) rg[q][u] = v4i{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int u = 0; u < NCH; ++u)
+      if (kEven || tid + u * NT < (BM + BN) * CPR) *reinterpret_cast<v4i*>(buf + dst[u]) = rg[q][u];
+  };
 
   v4f tot[RB][CB];
 #pragma unroll
   for (int i = 0; i < RB; ++i)
 #pragma unroll
     for (int j = 0; j < CB; ++j) tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-  const int fr = lane & 15, fg = lane >> 4;
-  const uint8_t* A8 = static_cast<const uint8_t*>(a.A);
-  const uint8_t* W8 = static_cast<const uint8_t*>(a.W);
-  for (int k0 = 0; k0 < K; k0 += KP) {
-    for (int c = tid; c < BM * CPR; c += NT) {
-      const int r = c / CPR, kc = c % CPR;
-      const int k = k0 + kc * (16 / ES);
-      const int ar = s_arow[r];
-      v4i v = {0, 0, 0, 0};
-      if (ar >= 0 && k < K) v = *reinterpret_cast<const v4i*>(A8 + ((long long)ar * K + k) * ES);
-      *reinterpret_cast<v4i*>(lds_a + r * ROWB + kc * 16) = v;
-    }
-    for (int c = tid; c < BN * CPR; c += NT) {
-      const int r = c / CPR, kc = c % CPR;
-      const int k = k0 + kc * (16 / ES);
-      const int n = n0 + r;
-      v4i v = {0, 0, 0, 0};
-      if (n < a.N && k < K) v = *reinterpret_cast<const v4i*>(W8 + ((long long)n * K + k) * ES);
-      *reinterpret_cast<v4i*>(lds_b + r * ROWB + kc * 16) = v;
-    }
-    __syncthreads();
-    typename Frag<P>::T af[RB], bf[CB];
+  const int ra = (wm * RB * 16 + fr) * ROWB, rb = (BM + wn * CB * 16 + fr) * ROWB;
+  fetch(0, 0);
+  if constexpr (kDeep) {
+    // Few tiles (a wave has its SIMD to itself): nothing else hides a wave's own waits.  Two parts'
+    // loads are in flight, and with kAhead (BF16 / FP8) the fragments of part s + 1 are read while
+    // part s is multiplied, part s + 2 then written to the buffer whose fragments are all in
+    // registers.  (FP32's fragments are four times as large and its MFMAs four times as long: there
+    // it gains 3% at 512 rows and loses 12% at 16,384.)
+    constexpr bool kAhead = P != P_F32;
+    typename Frag<P>::T fa[2][RB], fb[2][CB];
+    auto frags = [&](int q, const uint8_t* buf) {
 #pragma unroll
-    for (int i = 0; i < RB; ++i) Frag<P>::load(af[i], lds_a + (wm * WM + i * 16 + fr) * ROWB, fg);
+      for (int j = 0; j < CB; ++j) Frag<P>::load(fb[q][j], buf + rb + j * 16 * ROWB, fg);
 #pragma unroll
-    for (int j = 0; j < CB; ++j) Frag<P>::load(bf[j], lds_b + (wn * WN + j * 16 + fr) * ROWB, fg);
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < CB; ++j) {
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        Frag<P>::mma(acc, af[i], bf[j]);
-        tot[i][j] += acc;
-      }
-    __syncthreads();
-  }
-
-  const float deq = (P == P_FP8) ? a.a_scale * a.w_scale : 1.0f;
-  constexpr int PATT = P == P_F32 ? P_F32 : P_BF16;
-  // output value of accumulator (i, j, e): (sum of parts) * deq * row scale
-  auto val = [&](int i, int j, int e) {
-    return tot[i][j][e] * deq * s_inv[wm * WM + i * 16 + fg * 4 + e];
-  };
-
-  if constexpr (EPI == E_STORE || EPI == E_RESID) {
-    // residual values and gains are loaded before the first store (see the wide kernel)
-    float xo[RB][CB][4], gn[CB];
-    if constexpr (EPI == E_RESID) {
-#pragma unroll
-      for (int j = 0; j < CB; ++j) {
-        const int n = n0 + wn * WN + j * 16 + fr;
-        gn[j] = (a.y_out && n < a.N) ? a.y_gain[n] : 0.f;
-      }
+      for (int i = 0; i < RB; ++i) Frag<P>::load(fa[q][i], buf + ra + i * 16 * ROWB, fg);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int q) {
+      v4f acc[RB][CB];
 #pragma unroll
       for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int j = 0; j < CB; ++j)
+        for (int j = 0; j < CB; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int m = m0 + wm * WM + i * 16 + fg * 4 + e;
-            const int n = n0 + wn * WN + j * 16 + fr;
-            xo[i][j][e] = (m < a.M && n < a.N) ? a.out_f32[(long long)m * a.ldo + n] : 0.f;
-          }
-    }
-    float ymax = 0.f;
+      for (int t = 0; t < Frag<P>::STEPS; ++t)
 #pragma unroll
-    for (int i = 0; i < RB; ++i)
+        for (int i = 0; i < RB; ++i)
 #pragma unroll
-      for (int j = 0; j < CB; ++j)
+          for (int j = 0; j < CB; ++j) Frag<P>::step(acc[i][j], fa[q][i], fb[q][j], t);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int m = m0 + wm * WM + i * 16 + fg * 4 + e;
-          const int n = n0 + wn * WN + j * 16 + fr;
-          const bool ok = m < a.M && n < a.N;
-          if constexpr (EPI == E_RESID) {
-            float xn = 0.f;
-            if (ok) {
-              xn = xo[i][j][e] + val(i, j, e);
-              a.out_f32[(long long)m * a.ldo + n] = xn;
-            }
-            ymax = fmaxf(ymax, resid_out_g<P>(a, m, n, xn, fr, ok, gn[j]));
-          } else if (ok) {
-            a.out_f32[(long long)m * a.ldo + n] = val(i, j, e);
-          }
-        }
-    if constexpr (EPI == E_RESID) amax_flush(a.y_amax, ymax, lane);
-  } else if constexpr (EPI == E_GLU) {
-    // W rows are interleaved in 16-row groups (gate, up, gate, up, ...)
-    float omax = 0.f;
+      for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < CB; j += 2)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int m = m0 + wm * WM + i * 16 + fg * 4 + e;
-          const int nb = n0 + wn * WN + j * 16;
-          const int col = (nb / 32) * 16 + fr;
-          if (m < a.M && col < a.N / 2)
-            omax = fmaxf(omax, emit_glu<P>(a, m, col, val(i, j, e), val(i, j + 1, e)));
-        }
-    amax_flush(a.out_amax, omax, lane);
-  } else if constexpr (EPI == E_QKV) {
-    __shared__ float ct[BM][BN + 1];
-#pragma unroll
-    for (int i = 0; i < RB; ++i)
-#pragma unroll
-      for (int j = 0; j < CB; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          ct[wm * WM + i * 16 + fg * 4 + e][wn * WN + j * 16 + fr] = val(i, j, e);
-    __syncthreads();
-    const int nqk = (a.Hq + a.Hk) * a.hd;
-    for (int c = tid; c < BM * BN; c += NT) {
-      const int r = c / BN, cn = c % BN;
-      const int m = m0 + r, n = n0 + cn;
-      if (m >= a.M || n >= a.N) continue;
-      const float partner = n < nqk ? ct[r][rope_partner(a, n) - n0] : 0.f;
-      emit_qkv_prec(a, PATT, m, n, ct[r][cn], partner);
-    }
-  }
-}
-
-// ---- wide tile kernel (prefill): 128x128 tiles, four 64x64 waves, double-buffered LDS ----
-//
-// For bf16 / fp8 with many rows.  Each K part is staged global -> registers -> LDS one part ahead
-// of the MFMAs, so one barrier per part suffices.  Tiles are ordered so that the workgroups of
-// one XCD (dispatch is round-robin over the 8 XCDs) take consecutive tiles of the same A rows,
-// which then stay in that XCD's L2 while every column tile reads them.  The QKV epilogue needs
-// both RoPE halves of a head in one wave: a wave's 64 columns are 64-aligned, so for hd = 64 the
-// partner of block j is block j ^ 2 and for hd = 32 block j ^ 1, in the same lane.
-
-constexpr int WBM = 128, WBN = 128, WTHREADS = 256;
-
-template <int P, int AM, int EPI>
-__global__ __launch_bounds__(WTHREADS, 2) void gemm_wide_kernel(const GemmArgs a, int tiles_m,
-                                                                int tiles_n) {
-  constexpr int ES = PT<P>::ES;
-  constexpr int ROWB = KP * ES + 16;
-  constexpr int TILEB = (WBM + WBN) * ROWB;
-  constexpr int CPR = KP * ES / 16;           // 16-byte chunks per staged row
-  constexpr int NB16 = WBN * CPR / WTHREADS;  // chunks per thread (A and W alike)
-  __shared__ __align__(16) uint8_t lds[2 * TILEB];
-  __shared__ float s_inv[WBM];
-  __shared__ int s_arow[WBM];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int fr = lane & 15, fg = lane >> 4;
-  const int K = a.K, S = (K + KP - 1) / KP;
-
-  // XCD-aware tile order (a bijection of [0, tiles)): XCD x owns a contiguous range of tiles
-  const int nt = tiles_m * tiles_n, q = nt / 8, r8 = nt % 8;
-  const int bx = blockIdx.x, xcd = bx % 8, slot = bx / 8;
-  const int t = xcd * q + min(xcd, r8) + slot;
-  const int m0 = (t / tiles_n) * WBM, n0 = (t % tiles_n) * WBN;
-
-  for (int r = tid; r < WBM; r += WTHREADS) {
-    const int m = m0 + r;
-    s_arow[r] = m < a.M ? (a.a_rows ? a.a_rows[m] : m) : -1;
-  }
-  __syncthreads();
-  for (int r = tid; r < WBM; r += WTHREADS)
-    s_inv[r] = (AM == A_NORM && s_arow[r] >= 0) ? a_row_inv(a, s_arow[r]) : 1.f;
-
-  // global -> register staging of one K part; each thread's row addresses are resolved once
-  v4i ra[NB16], rb[NB16];
-  const uint8_t* pa[NB16];
-  const uint8_t* pw[NB16];
-  int kc16[NB16];
-  {
-    const uint8_t* A8 = static_cast<const uint8_t*>(a.A);
-    const uint8_t* W8 = static_cast<const uint8_t*>(a.W);
-#pragma unroll
-    for (int u = 0; u < NB16; ++u) {
-      const int c = tid + u * WTHREADS, r = c / CPR;
-      kc16[u] = (c % CPR) * (16 / ES);
-      const int ar = s_arow[r], n = n0 + r;
-      pa[u] = ar >= 0 ? A8 + ((long long)ar * K + kc16[u]) * ES : nullptr;
-      pw[u] = n < a.N ? W8 + ((long long)n * K + kc16[u]) * ES : nullptr;
-    }
-  }
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < NB16; ++u) {
-      const bool kin = k0 + kc16[u] < K;
-      ra[u] = (pa[u] && kin) ? *reinterpret_cast<const v4i*>(pa[u] + k0 * ES) : v4i{0, 0, 0, 0};
-      rb[u] = (pw[u] && kin) ? *reinterpret_cast<const v4i*>(pw[u] + k0 * ES) : v4i{0, 0, 0, 0};
-    }
-  };
-  auto stage = [&](uint8_t* buf) {
-#pragma unroll
-    for (int u = 0; u < NB16; ++u) {
-      const int c = tid + u * WTHREADS;
-      *reinterpret_cast<v4i*>(buf + (c / CPR) * ROWB + (c % CPR) * 16) = ra[u];
-      *reinterpret_cast<v4i*>(buf + WBM * ROWB + (c / CPR) * ROWB + (c % CPR) * 16) = rb[u];
-    }
-  };
-
-  v4f tot[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tot[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-
-  fetch(0);
-  stage(lds);
-  __syncthreads();
-  for (int s = 0; s < S; ++s) {
-    if (s + 1 < S) fetch((s + 1) * KP);
-    const uint8_t* la = lds + (s & 1) * TILEB;
-    const uint8_t* lb = la + WBM * ROWB;
-    typename Frag<P>::T bf[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) Frag<P>::load(bf[j], lb + (wn * 64 + j * 16 + fr) * ROWB, fg);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      typename Frag<P>::T af;
-      Frag<P>::load(af, la + (wm * 64 + i * 16 + fr) * ROWB, fg);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        Frag<P>::mma(acc, af, bf[j]);
-        tot[i][j] += acc;
+        for (int j = 0; j < CB; ++j) tot[i][j] += acc[i][j];
+    };
+    // (two parts an iteration and no exit between them, so that the loads in flight are the same
+    // on every path)
+    fetch(1, 1);
+    stage(0, 0, lds);
+    if constexpr (kAhead) {
+      stage(1, 1, lds + TILEB);
+      __syncthreads();
+      frags(0, lds);
+      __syncthreads();
+      fetch(0, 2);
+      fetch(1, 3);
+      // register set s % 2 holds part s + 2, and fragment set s % 2 part s
+      for (int s = 0; s + 1 < S; s += 2) {
+        frags(1, lds + TILEB);
+        multiply(0);
+        stage(0, s + 2, lds);
+        fetch(0, s + 4);
+        __syncthreads();
+        frags(0, lds);
+        multiply(1);
+        stage(1, s + 3, lds + TILEB);
+        fetch(1, s + 5);
+        __syncthreads();
+      }
+      if (S & 1) multiply(0);
+    } else {
+      __syncthreads();
+      fetch(0, 2);
+      // register set (s + 1) % 2 holds part s + 1
+      for (int s = 0; s + 1 < S; s += 2) {
+        frags(0, lds);
+        multiply(0);
+        stage(1, s + 1, lds + TILEB);
+        fetch(1, s + 3);
+        __syncthreads();
+        frags(0, lds + TILEB);
+        multiply(0);
+        stage(0, s + 2, lds);
+        fetch(0, s + 4);
+        __syncthreads();
+      }
+      if (S & 1) {
+        frags(0, lds);
+        multiply(0);
       }
     }
-    if (s + 1 < S) stage(lds + ((s + 1) & 1) * TILEB);
     __syncthreads();
+  } else {
+    stage(0, 0, lds);
+    __syncthreads();
+    for (int s = 0; s < S; ++s) {
+      fetch(0, s + 1);
+      const uint8_t* buf = lds + (s & 1) * TILEB;
+      typename Frag<P>::T bf[CB];
+#pragma unroll
+      for (int j = 0; j < CB; ++j) Frag<P>::load(bf[j], buf + rb + j * 16 * ROWB, fg);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        typename Frag<P>::T af;
+        Frag<P>::load(af, buf + ra + i * 16 * ROWB, fg);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+          v4f acc = {0.f, 0.f, 0.f, 0.f};
+          Frag<P>::mma(acc, af, bf[j]);
+          tot[i][j] += acc;
+        }
+      }
+      stage(0, s + 1, lds + ((s + 1) & 1) * TILEB);
+      __syncthreads();
+    }
   }
 
   const float deq = (P == P_FP8) ? a.a_scale * a.w_scale : 1.0f;
-  const int mw = m0 + wm * 64, nw = n0 + wn * 64;
-  auto val = [&](int i, int j, int e) {
-    return tot[i][j][e] * deq * s_inv[wm * 64 + i * 16 + fg * 4 + e];
-  };
+  const int rw = wm * RB * 16, jw = wn * CB;  // the wave's first tile row and column block
+  // output value of accumulator (i, j, e): (sum of parts) * deq * row scale
+  auto val = [&](int i, int j, int e) { return tot[i][j][e] * deq * s_inv[rw + i * 16 + fg * 4 + e]; };
   if constexpr (EPI == E_RESID) {
-    // every residual value and gain of the lane is loaded before the first store, so the loads
-    // overlap instead of each waiting behind the previous output's store
-    float xo[4][4][4], gn[4];
+    float xo[RB][CB][4], gn[CB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = nw + j * 16 + fr;
+    for (int j = 0; j < CB; ++j) {
+      const int n = col0(jw + j) + fr;
       gn[j] = (a.y_out && n < a.N) ? a.y_gain[n] : 0.f;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = mw + i * 16 + fg * 4 + e;
+        const int m = m0 + rw + i * 16 + fg * 4 + e;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = nw + j * 16 + fr;
+        for (int j = 0; j < CB; ++j) {
+          const int n = col0(jw + j) + fr;
           xo[i][j][e] = (m < a.M && n < a.N) ? a.out_f32[(long long)m * a.ldo + n] : 0.f;
         }
       }
     float ymax = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = mw + i * 16 + fg * 4 + e;
+        const int m = m0 + rw + i * 16 + fg * 4 + e;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = nw + j * 16 + fr;
+        for (int j = 0; j < CB; ++j) {
+          const int n = col0(jw + j) + fr;
           const bool ok = m < a.M && n < a.N;
           float xn = 0.f;
           if (ok) {
@@ -722,28 +709,30 @@ __global__ __launch_bounds__(WTHREADS, 2) void gemm_wide_kernel(const GemmArgs a
     amax_flush(a.y_amax, ymax, lane);
   } else if constexpr (EPI == E_STORE) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = mw + i * 16 + fg * 4 + e;
+        const int m = m0 + rw + i * 16 + fg * 4 + e;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = nw + j * 16 + fr;
+        for (int j = 0; j < CB; ++j) {
+          const int n = col0(jw + j) + fr;
           if (m < a.M && n < a.N) a.out_f32[(long long)m * a.ldo + n] = val(i, j, e);
         }
       }
   } else if constexpr (EPI == E_GLU) {
+    // W rows are interleaved in 16-row groups (gate, up, gate, up, ...)
     float omax = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = mw + i * 16 + fg * 4 + e;
+        const int m = m0 + rw + i * 16 + fg * 4 + e;
         if (m >= a.M) continue;
 #pragma unroll
-        for (int j = 0; j < 4; j += 2) {
-          const int col = ((nw + j * 16) / 32) * 16 + fr;
-          if (col < a.N / 2) omax = fmaxf(omax, emit_glu<P>(a, m, col, val(i, j, e), val(i, j + 1, e)));
+        for (int j = 0; j < CB; j += 2) {
+          const int col = ((cb0 + jw + j) / 2) * 16 + fr;
+          if (col < a.N / 2)
+            omax = fmaxf(omax, emit_glu<P>(a, m, col, val(i, j, e), val(i, j + 1, e)));
         }
       }
     amax_flush(a.out_amax, omax, lane);
@@ -751,70 +740,68 @@ __global__ __launch_bounds__(WTHREADS, 2) void gemm_wide_kernel(const GemmArgs a
     // the staging LDS is free after the last part's barrier: stage the tile rows' metadata and,
     // when the tile holds q/k columns, their RoPE table rows, so that the epilogue issues no
     // dependent global loads
-    const int nqk = (a.Hq + a.Hk) * a.hd;
-    const int px = a.hd == 64 ? 2 : 1;
-    const int h2 = a.hd / 2;
+    const int nqk = (a.Hq + a.Hk) * a.hd, h2 = a.hd / 2;
     RowMeta* s_rm = reinterpret_cast<RowMeta*>(lds);
-    float* s_rope = reinterpret_cast<float*>(lds + WBM * sizeof(RowMeta));
-    const bool rope = n0 < nqk;
-    for (int r = tid; r < WBM; r += WTHREADS)
+    float* s_rope = reinterpret_cast<float*>(lds + BM * sizeof(RowMeta));
+    for (int r = tid; r < BM; r += NT)
       s_rm[r] = m0 + r < a.M ? a.rows[m0 + r] : RowMeta{0, 0, 0, 0};
     __syncthreads();
-    if (rope) {
-      for (int t = tid; t < WBM * h2; t += WTHREADS) {
-        const int r = t / h2, i = t % h2;
-        if (m0 + r < a.M) {
-          const float2 cs = *reinterpret_cast<const float2*>(a.rope +
-                                                            ((long long)s_rm[r].pos * h2 + i) * 2);
-          *reinterpret_cast<float2*>(s_rope + (r * h2 + i) * 2) = cs;
-        }
+    if (col0(0) < nqk) {
+      for (int q = tid; q < BM * h2; q += NT) {
+        const int r = q / h2, i = q % h2;
+        if (m0 + r < a.M)
+          *reinterpret_cast<float2*>(s_rope + (r * h2 + i) * 2) = *reinterpret_cast<const float2*>(
+              a.rope + ((long long)s_rm[r].pos * h2 + i) * 2);
       }
       __syncthreads();
     }
-    // the partner block j ^ px must be a compile-time index, or the accumulators would be
-    // addressed dynamically and leave the registers
-    auto emit_all = [&](auto pxc) {
-      constexpr int PX = decltype(pxc)::value;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rl = wm * 64 + i * 16 + fg * 4;  // tile row of e = 0
-        const int m = m0 + rl;
-        if (m >= a.M) continue;
-        RowMeta rm[4];
-        bool ok[4];
-        const float* rr[4];
+    for (int i = 0; i < RB; ++i) {
+      const int rl = rw + i * 16 + fg * 4;  // tile row of e = 0
+      const int m = m0 + rl;
+      RowMeta rm[4];
+      bool ok[4];
+      const float* rr[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ok[e] = m + e < a.M;
+        rm[e] = s_rm[rl + e];
+        rr[e] = s_rope + (rl + e) * h2 * 2;
+      }
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        const int n = col0(jw + j) + fr;
+        float v[4], pr[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          ok[e] = m + e < a.M;
-          rm[e] = s_rm[rl + e];
-          rr[e] = s_rope + (rl + e) * h2 * 2;
+          v[e] = val(i, j, e);
+          // the other half of the head: the pair's other block, or (hd = 16) the lane 8 further
+          const float other = val(i, j ^ 1, e), across = __shfl_xor(v[e], 8, 64);
+          pr[e] = n < nqk ? (a.hd == 16 ? across : other) : 0.f;
         }
+        if (m >= a.M || n >= a.N) continue;
+        if constexpr (P == P_F32) {
+          const int i2 = (n % a.hd) % h2;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = nw + j * 16 + fr;
-          if (n >= a.N) continue;
-          float v[4], pr[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = val(i, j, e);
-            pr[e] = n < nqk ? val(i, j ^ PX, e) : 0.f;
-          }
+          for (int e = 0; e < 4; ++e)
+            if (ok[e])
+              emit_qkv_core(a, P_F32, m + e, n, v[e], pr[e], rm[e],
+                            n < nqk ? *reinterpret_cast<const float2*>(rr[e] + 2 * i2)
+                                    : float2{1.f, 0.f});
+        } else {
           emit_qkv4_rows(a, n, rm, ok, rr, v, pr, m);
         }
       }
-    };
-    if (px == 2)
-      emit_all(std::integral_constant<int, 2>{});
-    else
-      emit_all(std::integral_constant<int, 1>{});
+    }
   }
 }
 
-template <int P, int AM, int EPI>
-static void gemm_wide(const GemmArgs& a, hipStream_t s) {
-  const int tm = (a.M + WBM - 1) / WBM, tn = (a.N + WBN - 1) / WBN;
-  hipLaunchKernelGGL((gemm_wide_kernel<P, AM, EPI>), dim3(tm * tn), dim3(WTHREADS), 0, s, a, tm,
-                     tn);
+template <int P, int AM, int EPI, int RB, int CB, int WVM, int WVN, bool kDeep>
+static void gemm_tile(const GemmArgs& a, hipStream_t s) {
+  constexpr int BM = 16 * RB * WVM, BN = 16 * CB * WVN;
+  const int tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
+  hipLaunchKernelGGL((gemm_tile_kernel<P, AM, EPI, RB, CB, WVM, WVN, kDeep>), dim3(tm * tn),
+                     dim3(64 * WVM * WVN), 0, s, a, tm, tn);
 }
 
 // ---- split kernel (few rows): one workgroup per (epilogue group, chunk of mb 16-row blocks) ----
@@ -831,13 +818,6 @@ constexpr int SPLIT_WAVES = 16;
 constexpr int SPLIT_ROWS = 64;
 constexpr int kSsqPre = 4;    // staged block sums of squares held per thread during the parts
 constexpr int kSsqStage = 64;  // staged only for K <= 16 * kSsqStage
-// Fixed rule (used without tuning): the split kernel below SKINNY_ROWS rows, the 64 x 64 tile
-// kernel below WIDE_ROWS, the 128 x 128 wide kernel (BF16 / FP8) above; at a few hundred rows the
-// wide kernel has too few tiles to fill the chip (the tuner measured the split kernel 3-6x faster
-// there).
-constexpr int SKINNY_ROWS = 512;
-constexpr int WIDE_ROWS = 4096;
-
 // inv[a_rows[m]] = the RMSNorm scale of row a_rows[m] (for the output layer)
 __global__ void row_rms_kernel(const GemmArgs a, float* __restrict__ inv) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
@@ -851,17 +831,9 @@ __host__ __device__ __forceinline__ int group_size(int epi, int hd) {
   return epi == E_RESID ? 1 : 2;
 }
 
-// Block j of group gi: QKV pairs blocks (b, b + half) within a head, the others take 2 gi + j.
-__device__ __forceinline__ int group_block(int epi, int hd, int gi, int j) {
-  if (epi == E_QKV) {
-    const int nb = hd / 16;  // blocks per head
-    if (nb == 1) return gi;
-    const int half = nb / 2;
-    const int head = gi / half, r = gi % half;
-    return head * nb + r + j * half;
-  }
-  if (epi == E_RESID) return gi;
-  return 2 * gi + j;
+// Block j of group gi, where a group may be a single block.
+__device__ __forceinline__ int split_block(int epi, int hd, int gi, int j) {
+  return group_size(epi, hd) == 1 ? gi : group_block(epi, hd, gi, j);
 }
 
 template <int P, int AM, int EPI, int MB>
@@ -900,7 +872,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
       // both blocks are loaded whenever the group size is not known at compile time (QKV with
       // hd = 16 uses one), so that the count of loads does not depend on it
       if (EPI == E_RESID && j >= 1) break;
-      const int n = use ? min(group_block(EPI, a.hd, gi, j) * 16 + fr, N - 1) : 0;
+      const int n = use ? min(split_block(EPI, a.hd, gi, j) * 16 + fr, N - 1) : 0;
       Frag<P>::load_clamped(bf[q][j], W8 + (long long)n * K * ES, k0, K, fg);
     }
   };
@@ -998,7 +970,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
   auto qkv_cs = [&]() {
     if constexpr (EPI == E_QKV) {
       const int t = threadIdx.x;
-      const int n = group_block(EPI, a.hd, gi, (t >> 4) % gs) * 16 + (t & 15);
+      const int n = split_block(EPI, a.hd, gi, (t >> 4) % gs) * 16 + (t & 15);
       pre_cs = rope_cs(a, pre_rm.pos, n);
     }
   };
@@ -1083,7 +1055,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
     const int nqk = (a.Hq + a.Hk) * a.hd;
     for (int t = threadIdx.x; t < M * gs * 16; t += blockDim.x) {
       const int m = t / (gs * 16), j = (t >> 4) % gs, c = t & 15;
-      const int n = group_block(EPI, a.hd, gi, j) * 16 + c;
+      const int n = split_block(EPI, a.hd, gi, j) * 16 + c;
       if (n >= N) continue;
       const bool first = t == int(threadIdx.x);
       const float v = sum(m, j, c);
@@ -1757,14 +1729,6 @@ __global__ void convert_kernel(const float* __restrict__ src, void* __restrict__
 
 // ---- launchers ------------------------------------------------------------------------------
 
-template <int P, int AM, int EPI, int WM, int WN, int WVM, int WVN>
-static void gemm_go(const GemmArgs& a, hipStream_t s) {
-  constexpr int BM = WM * WVM, BN = WN * WVN;
-  const dim3 grid((a.N + BN - 1) / BN, (a.M + BM - 1) / BM);
-  hipLaunchKernelGGL((gemm_kernel<P, AM, EPI, WM, WN, WVM, WVN>), grid, dim3(64 * WVM * WVN), 0, s,
-                     a);
-}
-
 constexpr size_t kSplitLdsMax = 144 * 1024;  // of the 160 KiB LDS of a gfx950 CU
 
 template <int P, int AM, int EPI, int MB>
@@ -1834,13 +1798,28 @@ static bool tile_valid(int prec, int epi, const GemmArgs& a, const GemmTile& t) 
   }
 }
 
-// The fixed rule used when no measured choice is given.
+// The fixed rule used when no measured choice is given, from the number of tiles that a shape gives
+// (256 CUs of four SIMDs).  Times per launch at the 135M shape, microseconds:
+//  - split up to 32 rows, and while 64 x 32 tiles are fewer than 128 (half the CUs): FP32 QKV at 256
+//    rows (120 tiles) 16.8 against 22.4, gate/up at 128 rows (192 tiles) 22.1 against 18.5; output
+//    layer at 64 rows (1,536 tiles) 92 against 53.
+//  - then 64 x 32 tiles while larger ones leave SIMDs idle: FP32 O projection at 512 / 4,096 rows
+//    16.3 / 43.3 against 23.5 / 52.6 with 64 x 64; BF16 at 1,024 rows 12.1 against 14.0, but at 4,096
+//    rows (576 tiles of 64 x 64) 21.7 against 20.2.
+//  - 128 x 128 in BF16 / FP8 from 384 tiles on: gate/up at 4,096 rows 45.7 against 55.2, output layer
+//    at 512 rows 73 against 102; for the residual GEMMs, whose N = 576 fills 4.5 of 5 column tiles,
+//    from 1,024 on (down projection at 16,384 rows, 640 tiles, 93 against 77; at 32,768 rows
+//    146 against 157).
 static GemmTile default_tile(int prec, int epi, const GemmArgs& a) {
   const int S = split_parts(a);
   const GemmTile sp{T_SPLIT, split_mb(a, epi), S < SPLIT_WAVES ? S : SPLIT_WAVES};
-  if (a.M < SKINNY_ROWS && split_lds(a, epi, sp.mb) <= kSplitLdsMax) return sp;
-  if (a.M >= WIDE_ROWS && wide_ok(prec, epi, a)) return GemmTile{T_WIDE, 0, 0};
-  return GemmTile{a.M <= 64 ? T_TILE_S : T_TILE_M, 0, 0};
+  auto tiles = [&](long long bm, long long bn) {
+    return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn);
+  };
+  if ((a.M <= 32 || tiles(64, 32) < 128) && split_lds(a, epi, sp.mb) <= kSplitLdsMax) return sp;
+  if (tiles(128, 128) >= (epi == E_RESID ? 1024 : 384) && wide_ok(prec, epi, a))
+    return GemmTile{T_WIDE, 0, 0};
+  return GemmTile{tiles(64, 64) < (prec == P_F32 ? 1024 : 512) ? T_TILE_S : T_TILE_M, 0, 0};
 }
 
 bool gemm_tile_fits(int prec, int epi, const GemmArgs& a, const GemmTile& t) {
@@ -1874,19 +1853,12 @@ static void gemm_shape(const GemmArgs& a, hipStream_t s, GemmTile t) {
   if (t.kind == T_AUTO) t = default_tile(P, EPI, a);
   if (t.kind == T_SPLIT) return gemm_split<P, AM, EPI>(a, s, t.mb, t.waves);
   if constexpr (P != P_F32) {
-    if (t.kind == T_WIDE) return gemm_wide<P, AM, EPI>(a, s);
+    if (t.kind == T_WIDE) return gemm_tile<P, AM, EPI, 4, 4, 2, 2, false>(a, s);
   }
-  if constexpr (EPI == E_GLU) {
-    if (t.kind == T_TILE_S)
-      gemm_go<P, AM, EPI, 16, 32, 1, 2>(a, s);
-    else
-      gemm_go<P, AM, EPI, 32, 32, 2, 2>(a, s);
-  } else {
-    if (t.kind == T_TILE_S)
-      gemm_go<P, AM, EPI, 16, 16, 1, 4>(a, s);
-    else
-      gemm_go<P, AM, EPI, 32, 32, 2, 2>(a, s);
-  }
+  if (t.kind == T_TILE_S)
+    gemm_tile<P, AM, EPI, 1, 2, 4, 1, true>(a, s);
+  else
+    gemm_tile<P, AM, EPI, 2, 2, 2, 2, true>(a, s);
 }
 
 template <int P>

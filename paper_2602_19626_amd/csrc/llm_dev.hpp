@@ -93,9 +93,9 @@ struct AttnArgs {
 enum GemmKind {
   T_AUTO = 0,    // the fixed size rule
   T_SPLIT = 1,   // a workgroup per (epilogue group, mb row blocks); waves deal the K parts
-  T_TILE_S = 2,  // LDS-staged tiles, small (16 x 64, or 16 x 64 gate/up pairs)
+  T_TILE_S = 2,  // LDS-staged tiles, 64 x 32
   T_TILE_M = 3,  // LDS-staged tiles, 64 x 64
-  T_WIDE = 4,    // 128 x 128 tiles with XCD-aware order (BF16 / FP8 only)
+  T_WIDE = 4,    // LDS-staged tiles, 128 x 128 (BF16 / FP8 only)
 };
 struct GemmTile {
   int kind = T_AUTO;
