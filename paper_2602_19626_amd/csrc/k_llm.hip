@@ -122,14 +122,22 @@ constexpr int KP = 64;
 // ssq[b] = sum of x^2 over the block by one fixed tree (block_ssq16); the scale adds the block
 // sums in block order.  Prefill and decode kernels therefore derive bitwise equal scales.
 
+// The value of the lane n further (cyclically) in the same sixteen lanes, by a register rotation.
+template <int n>
+__device__ __forceinline__ float lane_ror16(float v) {
+  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(
+      0, int(__float_as_uint(v)), 0x120 + n, 0xF, 0xF, true)));
+}
+
 // Block sum of squares of 16 values held by 16 consecutive lanes (lane % 16 = column); every lane
-// of the group returns the same bits.
+// of the group returns the same bits: the tree of partners c ^ 8, c ^ 4, c ^ 2, c ^ 1 (after each
+// step the values repeat with half the period, so rotating by 8, 4, 2, 1 fetches the partner's).
 __device__ __forceinline__ float block_ssq16(float x) {
   float v = x * x;
-  v += __shfl_xor(v, 8, 64);
-  v += __shfl_xor(v, 4, 64);
-  v += __shfl_xor(v, 2, 64);
-  v += __shfl_xor(v, 1, 64);
+  v += lane_ror16<8>(v);
+  v += lane_ror16<4>(v);
+  v += lane_ror16<2>(v);
+  v += lane_ror16<1>(v);
   return v;
 }
 
@@ -138,18 +146,18 @@ __device__ __forceinline__ float inv_from_ssq(const float* ssq, int K, float eps
   float t = 0.f;
   int b = 0;
   if (nb % 4 == 0) {
-    // (rows of 16-byte multiples: sixteen blocks' sums requested together)
+    // (rows of 16-byte multiples: 48 blocks' sums requested together)
     const v4f* q = reinterpret_cast<const v4f*>(ssq);
-    for (; b < nb; b += 16) {
-      v4f v[4];
+    for (; b < nb; b += 48) {
+      v4f v[12];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = q[min(b / 4 + u, nb / 4 - 1)];
+      for (int u = 0; u < 12; ++u) v[u] = q[min(b / 4 + u, nb / 4 - 1)];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (b + 4 * u < nb) {
+      for (int u = 0; u < 12; ++u) {
+        const bool in = b + 4 * u < nb;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) t += v[u][e];
-        }
+        for (int e = 0; e < 4; ++e) t = in ? t + v[u][e] : t;
+      }
     }
   }
   for (; b < nb; ++b) t += ssq[b];
@@ -163,15 +171,8 @@ __device__ __forceinline__ float a_row_inv(const GemmArgs& a, int ar) {
 
 // ---- epilogue emitters ----
 
-// RoPE table entry (cos, sin) used by column n of a q/k head at position pos
-__device__ __forceinline__ float2 rope_cs(const GemmArgs& a, int pos, int n) {
-  const int h2 = a.hd / 2, within = n % a.hd;
-  const int i = within < h2 ? within : within - h2;
-  return *reinterpret_cast<const float2*>(a.rope + ((long long)pos * h2 + i) * 2);
-}
-
 // q/k/v output (m, n) = v (partner: the RoPE partner column's value) with the row's metadata rm
-// and, for q/k columns, its RoPE entry cs = rope_cs(a, rm.pos, n)
+// and, for q/k columns, its RoPE entry cs (cos, sin)
 __device__ __forceinline__ void emit_qkv_core(const GemmArgs& a, int prec_att, int m, int n,
                                               float v, float partner, const RowMeta& rm,
                                               float2 cs) {
@@ -204,14 +205,7 @@ __device__ __forceinline__ void emit_qkv_core(const GemmArgs& a, int prec_att, i
     PT<P_BF16>::store(base, idx, v, 1.f);
 }
 
-__device__ __forceinline__ void emit_qkv_prec(const GemmArgs& a, int prec_att, int m, int n,
-                                              float v, float partner) {
-  const RowMeta rm = a.rows[m];
-  const float2 cs = n < (a.Hq + a.Hk) * a.hd ? rope_cs(a, rm.pos, n) : float2{1.f, 0.f};
-  emit_qkv_core(a, prec_att, m, n, v, partner, rm, cs);
-}
-
-// emit_qkv_prec for rows m .. m + 3 of one column (BF16 attention operands), element for element
+// emit_qkv_core for rows m .. m + 3 of one column (BF16 attention operands), element for element
 // the same arithmetic, with the rows' metadata rm and RoPE table rows rr (cos, sin pairs of
 // position rm[e].pos, in global memory or LDS) supplied by the caller; V^T gets one 8-byte store
 // when the rows are 4 consecutive ring slots of one stream.
@@ -283,12 +277,6 @@ __device__ __forceinline__ float emit_glu(const GemmArgs& a, int m, int col, flo
   return fabsf(h);
 }
 
-// Column of the partner of q/k column n for RoPE (the same head, the other half).
-__device__ __forceinline__ int rope_partner(const GemmArgs& a, int n) {
-  const int h2 = a.hd / 2;
-  return (n % a.hd) < h2 ? n + h2 : n - h2;
-}
-
 // ---- operand fragments (from LDS or global, row-major with K contiguous) ----
 
 template <int P>
@@ -308,19 +296,9 @@ struct Frag<P_F32> {
 #pragma unroll
     for (int t = 0; t < 16; ++t) f[t] = 0.f;
   }
-  // straight from a global row (entries k0 + 16 g + 0..15, zero at or beyond K)
-  __device__ static void load_raw(T& f, const uint8_t* row, int k0, int K, int g) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = k0 + 16 * g + 4 * q;
-      const v4f v = k < K ? *reinterpret_cast<const v4f*>(row + (long long)k * 4)
-                          : v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) f[4 * q + e] = v[e];
-    }
-  }
-  // as load_raw, but the load itself is unconditional (its offset clamped into the row), so that
-  // no branch separates it from the loads issued around it
+  // straight from a global row: entries k0 + 16 g + 0..15, zero at or beyond K.  The load itself is
+  // unconditional (its offset clamped into the row), so that no branch separates it from the loads
+  // issued around it
   __device__ static void load_clamped(T& f, const uint8_t* row, int k0, int K, int g) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -347,13 +325,6 @@ struct Frag<P_BF16> {
     for (int t = 0; t < 2; ++t) f[t] = *reinterpret_cast<const v4i*>(row + (32 * t + 8 * g) * 2);
   }
   __device__ static void zero(T& f) { f[0] = f[1] = v4i{0, 0, 0, 0}; }
-  __device__ static void load_raw(T& f, const uint8_t* row, int k0, int K, int g) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int k = k0 + 32 * t + 8 * g;
-      f[t] = k < K ? *reinterpret_cast<const v4i*>(row + (long long)k * 2) : v4i{0, 0, 0, 0};
-    }
-  }
   __device__ static void load_clamped(T& f, const uint8_t* row, int k0, int K, int g) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -380,13 +351,6 @@ struct Frag<P_FP8> {
     for (int t = 0; t < 2; ++t) f[t] = *reinterpret_cast<const long*>(row + 32 * t + 8 * g);
   }
   __device__ static void zero(T& f) { f[0] = f[1] = 0; }
-  __device__ static void load_raw(T& f, const uint8_t* row, int k0, int K, int g) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int k = k0 + 32 * t + 8 * g;
-      f[t] = k < K ? *reinterpret_cast<const long*>(row + k) : 0;
-    }
-  }
   __device__ static void load_clamped(T& f, const uint8_t* row, int k0, int K, int g) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -804,20 +768,31 @@ static void gemm_tile(const GemmArgs& a, hipStream_t s) {
                      dim3(64 * WVM * WVN), 0, s, a, tm, tn);
 }
 
-// ---- split kernel (few rows): one workgroup per (epilogue group, chunk of mb 16-row blocks) ----
+// ---- split kernel (few rows) ----
 //
-// A group is the set of 16-column blocks one epilogue needs together: a RoPE pair of blocks
-// {b, b + hd/32} for QKV (a single block when hd = 16), a gate/up block pair for the SiLU-gated
-// MLP, two adjacent blocks for plain stores, one block for residual adds.  A chunk holds mb
-// (1-4) blocks of 16 rows.  Wave w of nw takes K parts w, w + nw, ...: for a part it issues the
-// loads of the chunk's A fragments and the group's W fragments together, runs every (row block,
-// column block) MFMA chain from zero and leaves the partial in LDS.  After one barrier the workgroup adds each output's partials in part order and
-// applies the epilogue.  No cross-workgroup communication is needed.
+// One workgroup per (group of 16 columns, or 32 for plain stores, and mb (1-4) blocks of 16 rows).
+// Wave w of nw takes K parts w, w + nw, ...: it loads the part's weights and operand rows, runs
+// every MFMA chain from zero and leaves the partials in LDS; after one barrier the workgroup adds
+// each output's partials in part order and applies the epilogue.  No communication between
+// workgroups.  A normed GEMM has one more wave, which derives the rows' RMSNorm scales meanwhile.
+//
+// A group of a RoPE GEMM is eight columns i .. i + 7 of a head's first half and their partners
+// i + hd/2 ..., one of the gated MLP eight gate columns and their eight up columns, so both halves
+// of a pair are eight lanes apart.  (Pairs of whole blocks give half as many workgroups, each with
+// twice the weights and chains.)
+//
+// One-row launches at the 135M shape, BF16 / FP32, before in brackets: QKV 4.6 (6.1) / 4.6 (8.2) us,
+// gate/up 4.1 (5.1) / 4.6 (7.6), O and down on average 5.3 (5.4) / 5.9 (7.3).
+//
+// What a decode step's GEMM waits for is a chain: weights from HBM, the MFMA chains, the sum and the
+// epilogue.  FP32 weights go through LDS (kStage): a load instruction then covers four rows of 256
+// bytes, eight cache lines; taken straight in fragment order it touches 32, and a CU's vector cache
+// takes about one a cycle: with nine waves' fragments queued there, a one-row gate/up spent 8,000 of
+// its 14,400 cycles before the first MFMA.
 
 constexpr int SPLIT_WAVES = 16;
 constexpr int SPLIT_ROWS = 64;
-constexpr int kSsqPre = 4;    // staged block sums of squares held per thread during the parts
-constexpr int kSsqStage = 64;  // staged only for K <= 16 * kSsqStage
+
 // inv[a_rows[m]] = the RMSNorm scale of row a_rows[m] (for the output layer)
 __global__ void row_rms_kernel(const GemmArgs a, float* __restrict__ inv) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
@@ -826,211 +801,211 @@ __global__ void row_rms_kernel(const GemmArgs a, float* __restrict__ inv) {
   inv[ar] = inv_from_ssq(a.ssq + (long long)ar * (a.K / 16), a.K, a.eps);
 }
 
-__host__ __device__ __forceinline__ int group_size(int epi, int hd) {
-  if (epi == E_QKV) return hd == 16 ? 1 : 2;
-  return epi == E_RESID ? 1 : 2;
+// 16-column blocks per split group.  With several row blocks the gated MLP takes a gate and an up
+// block in BF16 / FP8: half as many workgroups then read the operand rows (64 rows BF16: 5.8 us
+// against 6.8; FP32, where the chains weigh more, 25 rows: 9.8 us against 7.3).
+__host__ __device__ __forceinline__ constexpr int group_size(int prec, int epi, int mb) {
+  return epi == E_STORE || (epi == E_GLU && mb > 1 && prec != P_F32) ? 2 : 1;
 }
 
-// Block j of group gi, where a group may be a single block.
-__device__ __forceinline__ int split_block(int epi, int hd, int gi, int j) {
-  return group_size(epi, hd) == 1 ? gi : group_block(epi, hd, gi, j);
+// log2 of head_dim (16, 32 or 64)
+__device__ __forceinline__ int log2_hd(int hd) { return 31 - __builtin_clz(hd); }
+
+// The column of lane c (0..15) in block j of split group gi.
+__device__ __forceinline__ int split_col(int epi, int gs, int hd, int gi, int j, int c) {
+  if (epi == E_QKV) {
+    const int lg = log2_hd(hd), head = gi >> (lg - 4), i = (gi & ((hd >> 4) - 1)) * 8 + (c & 7);
+    return head * hd + i + (c >> 3) * (hd >> 1);
+  }
+  if (epi == E_GLU && gs == 1) return ((gi >> 1) * 2 + (c >> 3)) * 16 + (gi & 1) * 8 + (c & 7);
+  return (gi * gs + j) * 16 + c;
 }
 
-template <int P, int AM, int EPI, int MB>
-__global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const GemmArgs a) {
+// Floats of a part's slot in LDS: its staged weights (kStage), then its partials in their place.
+__host__ __device__ __forceinline__ constexpr int split_slot(int prec, int epi, int mb,
+                                                             bool stage) {
+  const int gs = group_size(prec, epi, mb), part = gs * mb * 256, w = stage ? gs * 1024 : 0;
+  return part > w ? part : w;
+}
+
+template <int P, int AM, int EPI, int MB, bool kStage>
+__global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const GemmArgs a, int nw) {
+  static_assert(!kStage || P == P_F32, "only FP32 weights are staged");
   constexpr int ES = PT<P>::ES;
-  extern __shared__ float lds[];  // partials [part][block j][row block][16 rows][16 cols], inv[64]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  constexpr int GS = group_size(P, EPI, MB);
+  constexpr int SLOT = split_slot(P, EPI, MB, kStage);
+  extern __shared__ __align__(16) float lds[];  // [part][SLOT], then the rows' scales [64]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int fr = lane & 15, fg = lane >> 4;
   const int K = a.K, N = a.N;
   const int S = (K + KP - 1) / KP;
   const int gi = blockIdx.x, r0 = blockIdx.y * MB * 16;
   const int M = min(a.M - r0, MB * 16);
-  const int gs = group_size(EPI, a.hd);
-  float* s_inv = lds + S * gs * MB * 256;
-  float* s_ssq = s_inv + SPLIT_ROWS;  // [row][K / 16] when staged
+  float* s_inv = lds + S * SLOT;
   const uint8_t* A8 = static_cast<const uint8_t*>(a.A);
   const uint8_t* W8 = static_cast<const uint8_t*>(a.W);
-  // only the output layer gathers its A rows (launch_gemm checks this); elsewhere the row of
-  // output m is r0 + m and the prologue has no gather loads
+  // only the output layer gathers its A rows (launch_gemm checks this)
   const int32_t* const a_rows = EPI == E_STORE ? a.a_rows : nullptr;
-  // Every load of the prologue and of the parts is issued unconditionally (indices clamped into
-  // range; values past the end are masked afterwards or never stored).  A load skipped by a
-  // branch would make the count of loads in flight path-dependent, and the wait for an earlier
-  // load would then have to drain every later one: the operands' loads would wait for the weight
-  // loads issued before them, one memory round trip after the other.  For the same reason a wave
-  // without parts still issues the first part's loads, of a few bytes at the start of the
-  // operands.
-  constexpr int NBUF = EPI == E_RESID ? 2 : 1;
-  typename Frag<P>::T bf[NBUF][2], af[NBUF][MB];
-  const bool real = wave < S;  // wave-uniform
-  // columns past N repeat column N - 1 (never stored); K entries past K are zero in both operands
-  auto load_w = [&](int s, int q, bool use) {
-    const int k0 = use ? s * KP : 0;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      // both blocks are loaded whenever the group size is not known at compile time (QKV with
-      // hd = 16 uses one), so that the count of loads does not depend on it
-      if (EPI == E_RESID && j >= 1) break;
-      const int n = use ? min(split_block(EPI, a.hd, gi, j) * 16 + fr, N - 1) : 0;
-      Frag<P>::load_clamped(bf[q][j], W8 + (long long)n * K * ES, k0, K, fg);
-    }
-  };
-  // This lane's A row of each row block (rows past M repeat row M - 1; their outputs are never
-  // stored), resolved once for every part.
-  int arow[MB];
-#pragma unroll
-  for (int rb = 0; rb < MB; ++rb) arow[rb] = r0 + min(rb * 16 + fr, M - 1);
-  // (a wave without parts reads the start of its first A row: with gathered rows, output row
-  // indices are not A row indices, and the output layer may have more output rows than A rows)
-  auto load_a = [&](int s, int q, bool use) {
-    const int k0 = use ? s * KP : 0;
-#pragma unroll
-    for (int rb = 0; rb < MB; ++rb)
-      Frag<P>::load_clamped(af[q][rb], A8 + (long long)(use ? arow[rb] : arow[0]) * K * ES, k0, K,
-                            fg);
-  };
-  // Issue order of the first part: the output layer's weights go out ahead of its gathered rows
-  // (the first wait for those also covers the weights, issued just before); elsewhere the row
-  // statistics go first, so that the row scales can be prepared while the weights and operand
-  // rows are still in flight.
-  if constexpr (EPI == E_STORE) load_w(real ? wave : 0, 0, real);
-  if (a_rows) {
-#pragma unroll
-    for (int rb = 0; rb < MB; ++rb) arow[rb] = a_rows[arow[rb]];
-  }
-  // A row of output row r0 + t for the given row scales, t = threadIdx.x < M (all in wave 0):
-  // lane t holds it as arow[t / 16], with no load of its own
-  int ar_t = arow[0];
-#pragma unroll
-  for (int rb = 1; rb < MB; ++rb) ar_t = (lane >> 4) == rb ? arow[rb] : ar_t;
-  // Row scales of a normed GEMM: their inputs (the block sums of squares, or the given scales)
-  // are loaded before the parts' operands are consumed, so that their latency overlaps the
-  // parts' loads instead of following the last MFMA.
-  const int nb16 = K / 16;
-  const int nss = (AM == A_NORM && !a.inv) ? M * nb16 : 0;
-  const bool staged = nss > 0 && nb16 <= kSsqStage && nss <= kSsqPre * int(blockDim.x);
-  float pre[kSsqPre];
-  float pre_inv = 1.f;
-  if (staged) {
-#pragma unroll
-    for (int k = 0; k < kSsqPre; ++k) {
-      const int i = min(int(threadIdx.x) + k * int(blockDim.x), nss - 1);
-      const int m = i / nb16;
-      const int ar = a_rows ? a_rows[r0 + m] : r0 + m;
-      pre[k] = a.ssq[(long long)ar * nb16 + (i - m * nb16)];
-    }
-  }
-  // (the residual GEMMs, whose waves may own two parts, request both at the top of their loop)
-  if constexpr (EPI != E_STORE && NBUF == 1) load_w(real ? wave : 0, 0, real);
-  // The inputs of this thread's first epilogue item are fetched now as well: the row metadata of
-  // a q/k/v output (its RoPE entry follows once the metadata is in), or the residual value and
-  // gain of a residual output.
-  RowMeta pre_rm{0, 0, 0, 0};
+
+  // The inputs of this thread's first epilogue item (row t / 16, column t % 16) are requested first:
+  // the row metadata of a q/k/v output, or the residual value and gain.
+  int pre_stream = 0, pre_pos = 0, pre_slot = 0;
   float2 pre_cs{1.f, 0.f};
   float pre_x = 0.f, pre_g = 0.f;
+  const int em = min(int(threadIdx.x) >> 4, M - 1);
+  const int en = split_col(EPI, GS, EPI == E_QKV ? a.hd : 64, gi, 0, threadIdx.x & 15);
   if constexpr (EPI == E_QKV) {
-    pre_rm = a.rows[r0 + min(int(threadIdx.x) / (gs * 16), M - 1)];
+    const v4i rm = *reinterpret_cast<const v4i*>(a.rows + r0 + em);  // stream, pos, tok, slot
+    pre_stream = rm[0];
+    pre_pos = rm[1];
+    pre_slot = rm[3];
   } else if constexpr (EPI == E_RESID) {
-    const int t = threadIdx.x;
-    const int m = min(t >> 4, M - 1), n = min(gi * 16 + (t & 15), N - 1);
-    const float* xp = a.out_f32 + (long long)(r0 + m) * a.ldo + n;
+    const int n = min(en, N - 1);
+    const float* xp = a.out_f32 + (long long)(r0 + em) * a.ldo + n;
     pre_x = *xp;
     pre_g = *(a.y_out ? a.y_gain + n : xp);  // (unused without y_out)
   }
-  if constexpr (NBUF == 1) load_a(real ? wave : 0, 0, real);
-  if constexpr (AM == A_NORM) {
-    // only wave 0 uses it (and only with given scales); the other waves read the start of a
-    // weight row they load anyway rather than all hitting one line
-    const float* ip = a.inv ? a.inv + ar_t : a.ssq;
-    if (wave != 0) ip = reinterpret_cast<const float*>(W8 + (long long)min(gi * 16, N - 1) * K * ES);
-    pre_inv = *ip;
-  }
-  // a later part: weights and operand rows together
-  auto load_part = [&](int s, int q) {
-    load_w(s, q, true);
-    load_a(s, q, true);
-  };
-  auto compute_part = [&](int s, int q) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (j >= gs) break;
-#pragma unroll
-      for (int rb = 0; rb < MB; ++rb) {
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-        Frag<P>::mma(acc, af[q][rb], bf[q][j]);
-        float* dst = lds + (((s * gs + j) * MB + rb) << 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dst[(fg * 4 + e) * 16 + fr] = acc[e];
-      }
+
+  if (AM == A_NORM && wave == nw) {
+    // the rows' scales, one row per lane
+    if (lane < M) {
+      const int ar = a_rows ? a_rows[r0 + lane] : r0 + lane;
+      s_inv[lane] = a_row_inv(a, ar);
     }
-  };
-  // the RoPE entry of this thread's first q/k output (its metadata was requested first); every
-  // thread loads one (a valid table entry for any column), the epilogue uses those of q/k outputs
-  auto qkv_cs = [&]() {
-    if constexpr (EPI == E_QKV) {
-      const int t = threadIdx.x;
-      const int n = split_block(EPI, a.hd, gi, (t >> 4) % gs) * 16 + (t & 15);
-      pre_cs = rope_cs(a, pre_rm.pos, n);
-    }
-  };
-  // the chunk's row scales into s_inv (read after the barrier that follows the parts)
-  auto row_scales = [&]() {
-    if (staged) {
-#pragma unroll
-      for (int k = 0; k < kSsqPre; ++k) {
-        const int i = threadIdx.x + k * int(blockDim.x);
-        if (i < nss) s_ssq[i] = pre[k];
-      }
-      __syncthreads();
-      for (int m = threadIdx.x; m < M; m += blockDim.x)
-        s_inv[m] = inv_from_ssq(s_ssq + m * nb16, K, a.eps);
-    } else if (AM == A_NORM && a.inv) {
-      if (int(threadIdx.x) < M) s_inv[threadIdx.x] = pre_inv;
-      for (int m = threadIdx.x + blockDim.x; m < M; m += blockDim.x)
-        s_inv[m] = a.inv[a_rows ? a_rows[r0 + m] : r0 + m];
-    } else {
-      for (int m = threadIdx.x; m < M; m += blockDim.x)
-        s_inv[m] = AM == A_NORM ? a_row_inv(a, a_rows ? a_rows[r0 + m] : r0 + m) : 1.f;
-    }
-  };
-  // parts wave, wave + nw, ...
-  if constexpr (NBUF == 2) {
-    // both parts' loads go out before either is consumed (a first part loaded ahead of the loop
-    // would be waited for before the second part's loads were issued)
-    for (int s = wave; s < S; s += 2 * nw) {
-      load_part(s, 0);
-      if (s + nw < S) load_part(s + nw, NBUF - 1);
-      compute_part(s, 0);
-      if (s + nw < S) compute_part(s + nw, NBUF - 1);
-    }
-    qkv_cs();
-    row_scales();
   } else {
-    // The first part's operands are in flight (issued above) while the row scales and the RoPE
-    // entries are prepared.  Every wave reaches the scales' barrier.
-    row_scales();
-    qkv_cs();
-    for (int s = wave; s < S; s += nw) {
-      if (s != wave) load_part(s, 0);
-      compute_part(s, 0);
+    // This lane's A row of each row block (rows past M repeat row M - 1; never stored).
+    int arow[MB];
+#pragma unroll
+    for (int rb = 0; rb < MB; ++rb) {
+      arow[rb] = r0 + min(rb * 16 + fr, M - 1);
+      if (a_rows) arow[rb] = a_rows[arow[rb]];
     }
+    // W rows of this lane: fragment row fr, or when staged rows 4 q + fg, chunk fr of the part
+    // (columns past N repeat column N - 1; never stored)
+    constexpr int WR = kStage ? 4 : 1;
+    const uint8_t* wrow[GS][WR];
+#pragma unroll
+    for (int j = 0; j < GS; ++j)
+#pragma unroll
+      for (int q = 0; q < WR; ++q) {
+        const int c = kStage ? 4 * q + fg : fr;
+        const int n = min(split_col(EPI, GS, EPI == E_QKV ? a.hd : 64, gi, j, c), N - 1);
+        wrow[j][q] = W8 + (long long)n * K * ES;
+      }
+    // two parts of a wave are requested together where their registers allow
+    constexpr bool kTwo = GS == 1 && MB <= 2;
+    constexpr int NB = kTwo ? 2 : 1;
+    typename Frag<P>::T bf[NB][GS], af[NB][MB];
+    v4f wv[NB][GS][WR];  // staged: the part's weights as loaded
+    // every load of a part is issued unconditionally (clamped into its row; entries at or beyond K
+    // are zeroed), so that the number in flight is the same on every path
+    auto load = [&](int q, int s) {
+      const int k0 = s * KP;
+      if constexpr (kStage) {
+        const int k = k0 + 4 * fr;
+#pragma unroll
+        for (int j = 0; j < GS; ++j)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const v4f v = *reinterpret_cast<const v4f*>(wrow[j][u] + min(k, K - 4) * 4);
+            wv[q][j][u] = v;
+          }
+      } else {
+#pragma unroll
+        for (int j = 0; j < GS; ++j) Frag<P>::load_clamped(bf[q][j], wrow[j][0], k0, K, fg);
+      }
+#pragma unroll
+      for (int rb = 0; rb < MB; ++rb)
+        Frag<P>::load_clamped(af[q][rb], A8 + (long long)arow[rb] * K * ES, k0, K, fg);
+    };
+    auto part = [&](int q, int s) {
+      float* slot = lds + s * SLOT;
+      if constexpr (kStage) {
+        // Rows of 256 bytes; chunk c of row r lies at chunk c ^ r, so that neither the writes
+        // (sixteen chunks of a row) nor the reads (one chunk of sixteen rows) meet in a bank.
+        // Only this wave uses the slot before the barrier.
+        const bool in = s * KP + 4 * fr < K;
+#pragma unroll
+        for (int j = 0; j < GS; ++j)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int r = 4 * u + fg;
+            *reinterpret_cast<v4f*>(slot + j * 1024 + r * 64 + ((fr ^ r) & 15) * 4) =
+                in ? wv[q][j][u] : v4f{0.f, 0.f, 0.f, 0.f};
+          }
+#pragma unroll
+        for (int j = 0; j < GS; ++j)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const v4f v = *reinterpret_cast<const v4f*>(slot + j * 1024 + fr * 64 +
+                                                        (((4 * fg + u) ^ fr) & 15) * 4);
+            if constexpr (P == P_F32) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) bf[q][j][4 * u + e] = v[e];
+            }
+          }
+      }
+      v4f acc[GS][MB];
+#pragma unroll
+      for (int j = 0; j < GS; ++j)
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) {
+          acc[j][rb] = v4f{0.f, 0.f, 0.f, 0.f};
+          Frag<P>::mma(acc[j][rb], af[q][rb], bf[q][j]);
+        }
+#pragma unroll
+      for (int j = 0; j < GS; ++j)
+#pragma unroll
+        for (int rb = 0; rb < MB; ++rb) {
+          float* dst = slot + ((j * MB + rb) << 8);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[(fg * 4 + e) * 16 + fr] = acc[j][rb][e];
+        }
+    };
+    for (int s = wave; s < S; s += NB * nw) {
+      load(0, s);
+      if (kTwo && s + nw < S) {
+        load(NB - 1, s + nw);
+        part(0, s);
+        part(NB - 1, s + nw);
+      } else {
+        part(0, s);
+      }
+    }
+  }
+  // the RoPE entry of this thread's first q/k output (its metadata was requested first)
+  if constexpr (EPI == E_QKV) {
+    const int h2 = a.hd >> 1, i = (gi & ((a.hd >> 4) - 1)) * 8 + (threadIdx.x & 7);
+    pre_cs = *reinterpret_cast<const float2*>(a.rope + ((long long)pre_pos * h2 + i) * 2);
   }
   __syncthreads();
   const float deq = (P == P_FP8) ? a.a_scale * a.w_scale : 1.0f;
-  // output (row m of the chunk, block j, column c) = (partials summed in part order) * deq * scale
+  // output (row m of the chunk, block j, lane c) = (partials summed in part order) * deq * scale
   auto sum = [&](int m, int j, int c) {
+    const float* src = lds + ((j * MB + (m >> 4)) << 8) + (m & 15) * 16 + c;
     float v = 0.f;
-    for (int s = 0; s < S; ++s) v += lds[(((s * gs + j) * MB + (m >> 4)) << 8) + (m & 15) * 16 + c];
-    return v * deq * s_inv[m];
+    int s = 0;
+    for (; s + 8 <= S; s += 8) {  // eight LDS reads at a time
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = src[(s + u) * SLOT];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v += x[u];
+    }
+    for (; s < S; ++s) v += src[s * SLOT];
+    return v * deq * (AM == A_NORM ? s_inv[m] : 1.f);
   };
   if constexpr (EPI == E_GLU) {
+    // one block: lanes 0-7 of sixteen hold the gate columns, lanes 8-15 their up columns
     float omax = 0.f;
-    for (int t = threadIdx.x; t < M * 16; t += blockDim.x) {
-      const int m = t >> 4, c = t & 15;
-      const int col = gi * 16 + c;
-      if (col < N / 2)
-        omax = fmaxf(omax, emit_glu<P>(a, r0 + m, col, sum(m, 0, c), sum(m, 1, c)));
+    for (int t0 = 0; t0 < M * 16; t0 += blockDim.x) {
+      const int t = t0 + threadIdx.x;
+      const int m = min(t >> 4, M - 1), c = t & 15;
+      const float v = sum(m, 0, c);
+      const float up = GS == 2 ? sum(m, GS - 1, c) : lane_ror16<8>(v);
+      const int col = GS == 2 ? gi * 16 + c : gi * 8 + (c & 7);
+      if (t < M * 16 && (GS == 2 || c < 8) && col < N / 2)
+        omax = fmaxf(omax, emit_glu<P>(a, r0 + m, col, v, up));
     }
     amax_flush(a.out_amax, omax, lane);
   } else if constexpr (EPI == E_RESID) {
@@ -1051,25 +1026,46 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
       ymax = fmaxf(ymax, resid_out_g<P>(a, r0 + m, n, xn, c, ok, g));
     }
     amax_flush(a.y_amax, ymax, lane);
+  } else if constexpr (EPI == E_STORE) {
+    for (int t = threadIdx.x; t < M * 32; t += blockDim.x) {
+      const int m = t >> 5, j = (t >> 4) & 1, c = t & 15;
+      const int n = (2 * gi + j) * 16 + c;
+      if (n < N) a.out_f32[(long long)(r0 + m) * a.ldo + n] = sum(m, j, c);
+    }
   } else {
-    const int nqk = (a.Hq + a.Hk) * a.hd;
-    for (int t = threadIdx.x; t < M * gs * 16; t += blockDim.x) {
-      const int m = t / (gs * 16), j = (t >> 4) % gs, c = t & 15;
-      const int n = split_block(EPI, a.hd, gi, j) * 16 + c;
-      if (n >= N) continue;
-      const bool first = t == int(threadIdx.x);
-      const float v = sum(m, j, c);
-      const long long row = r0 + m;
-      if constexpr (EPI == E_STORE) {
-        a.out_f32[row * a.ldo + n] = v;
-      } else {
-        float partner = 0.f;
-        if (n < nqk) partner = a.hd == 16 ? sum(m, 0, c ^ 8) : sum(m, 1 - j, c);
-        if (first)
-          emit_qkv_core(a, P == P_F32 ? P_F32 : P_BF16, int(row), n, v, partner, pre_rm, pre_cs);
-        else
-          emit_qkv_prec(a, P == P_F32 ? P_F32 : P_BF16, int(row), n, v, partner);
+    // the group's head: a q head, a k head or a v head (head_dim is a power of two)
+    const int lg = log2_hd(a.hd), hd = a.hd, h2 = hd >> 1;
+    const int head = gi >> (lg - 4);
+    for (int t0 = 0; t0 < M * 16; t0 += blockDim.x) {
+      const int t = t0 + threadIdx.x;
+      const int m = min(t >> 4, M - 1), c = t & 15;
+      float v = sum(m, 0, c);
+      const float partner = lane_ror16<8>(v);  // the other half of the RoPE pair
+      if (t >= M * 16) continue;
+      const int i = (gi & ((hd >> 4) - 1)) * 8 + (c & 7), within = i + (c >> 3) * h2;
+      if (t0 > 0) {
+        const v4i rm = *reinterpret_cast<const v4i*>(a.rows + r0 + m);
+        pre_stream = rm[0];
+        pre_slot = rm[3];
+        pre_cs = *reinterpret_cast<const float2*>(a.rope + ((long long)rm[1] * h2 + i) * 2);
       }
+      if (head < a.Hq + a.Hk) {
+        const float2 cs = pre_cs;
+        v = c < 8 ? v * cs.x - partner * cs.y : v * cs.x + partner * cs.y;
+      }
+      void* base = a.q_out;
+      long long idx = (long long)(r0 + m) * a.Hq * hd + head * hd + within;
+      if (head >= a.Hq) {
+        const bool is_k = head < a.Hq + a.Hk;
+        const int kvh = head - a.Hq - (is_k ? 0 : a.Hk);
+        const long long sb = (long long)pre_stream * a.kv_stride + (long long)kvh * a.ring * hd;
+        base = is_k ? a.k_cache : a.vt_cache;
+        idx = sb + (is_k ? (long long)pre_slot * hd + within : (long long)within * a.ring + pre_slot);
+      }
+      if constexpr (P == P_F32)
+        PT<P_F32>::store(base, idx, v, 1.f);
+      else
+        PT<P_BF16>::store(base, idx, v, 1.f);
     }
   }
 }
@@ -1731,47 +1727,67 @@ __global__ void convert_kernel(const float* __restrict__ src, void* __restrict__
 
 constexpr size_t kSplitLdsMax = 144 * 1024;  // of the 160 KiB LDS of a gfx950 CU
 
-template <int P, int AM, int EPI, int MB>
-static void launch_split(dim3 grid, dim3 block, size_t lds, const GemmArgs& a, hipStream_t s) {
+template <int P, int AM, int EPI, int MB, bool kStage>
+static void launch_split(dim3 grid, int waves, size_t lds, const GemmArgs& a, hipStream_t s) {
   static bool raised = false;  // allow more than the default 64 KiB of dynamic LDS, once
   if (!raised) {
-    NC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_split_kernel<P, AM, EPI, MB>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, int(kSplitLdsMax)));
+    NC_HIP(hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&gemm_split_kernel<P, AM, EPI, MB, kStage>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, int(kSplitLdsMax)));
     raised = true;
   }
-  hipLaunchKernelGGL((gemm_split_kernel<P, AM, EPI, MB>), grid, block, lds, s, a);
+  // a normed GEMM's row scales have a wave of their own
+  const int extra = AM == A_NORM ? 1 : 0, nw = std::min(waves, SPLIT_WAVES - extra);
+  hipLaunchKernelGGL((gemm_split_kernel<P, AM, EPI, MB, kStage>), grid, dim3(64 * (nw + extra)),
+                     lds, s, a, nw);
+}
+
+static int split_groups(const GemmArgs& a, int prec, int epi, int mb) {
+  const int w = 16 * group_size(prec, epi, mb);
+  return (a.N + w - 1) / w;
 }
 
 // Row blocks (16 rows each) per workgroup: GEMMs with few column groups cut M finer, so that
 // more workgroups share the work and each one's chain of loads, MFMAs and epilogue is shorter.
-static int split_mb(const GemmArgs& a, int epi) {
-  const int nblk = (a.N + 15) / 16, gs = group_size(epi, a.hd);
-  const int ngroups = (nblk + gs - 1) / gs;
-  const int cap = ngroups < 64 ? 1 : ngroups < 128 ? 2 : SPLIT_ROWS / 16;
+static int split_mb(const GemmArgs& a, int prec, int epi) {
+  const int ngroups = split_groups(a, prec, epi, SPLIT_ROWS / 16);
+  const int cap = ngroups < 64 ? 1 : ngroups < 256 ? 2 : SPLIT_ROWS / 16;
   return std::min((a.M + 15) / 16, cap);
 }
 
 static int split_parts(const GemmArgs& a) { return (a.K + KP - 1) / KP; }
 
-static size_t split_lds(const GemmArgs& a, int epi, int mb) {
-  const int nb16 = a.K / 16;
-  const size_t ssq = (epi != E_RESID && nb16 <= kSsqStage) ? size_t(mb) * 16 * nb16 : 0;
-  return (size_t(split_parts(a)) * group_size(epi, a.hd) * mb * 256 + SPLIT_ROWS + ssq) *
-         sizeof(float);
+static size_t split_lds(const GemmArgs& a, int prec, int epi, int mb, bool stage) {
+  return (size_t(split_parts(a)) * split_slot(prec, epi, mb, stage) + SPLIT_ROWS) * sizeof(float);
+}
+
+// The shapes that are accepted: S partials of mb 16 x 16 blocks per column block, for the pair of
+// blocks that an epilogue works on, with the rows' block sums, in kSplitLdsMax.  (The kernel needs
+// no more than that.)
+static bool split_fits(const GemmArgs& a, int epi, int mb) {
+  const int nb16 = a.K / 16, pair = epi == E_RESID || (epi == E_QKV && a.hd == 16) ? 1 : 2;
+  const size_t ssq = epi != E_RESID && nb16 <= 64 ? size_t(mb) * 16 * nb16 : 0;
+  return (size_t(split_parts(a)) * pair * mb * 256 + SPLIT_ROWS + ssq) * sizeof(float) <=
+         kSplitLdsMax;
+}
+
+template <int P, int AM, int EPI, int MB>
+static void gemm_split_mb(const GemmArgs& a, hipStream_t s, int waves) {
+  const dim3 grid(split_groups(a, P, EPI, MB), (a.M + 16 * MB - 1) / (16 * MB));
+  if constexpr (P == P_F32 && MB <= 2) {  // (more row blocks would spill)
+    const size_t lds = split_lds(a, P, EPI, MB, true);
+    if (lds <= kSplitLdsMax) return launch_split<P, AM, EPI, MB, true>(grid, waves, lds, a, s);
+  }
+  launch_split<P, AM, EPI, MB, false>(grid, waves, split_lds(a, P, EPI, MB, false), a, s);
 }
 
 template <int P, int AM, int EPI>
 static void gemm_split(const GemmArgs& a, hipStream_t s, int mb, int waves) {
-  const int nblk = (a.N + 15) / 16;
-  const int gs = group_size(EPI, a.hd);
-  const int ngroups = (nblk + gs - 1) / gs;
-  const dim3 grid(ngroups, (a.M + 16 * mb - 1) / (16 * mb)), block(64 * waves);
-  const size_t lds = split_lds(a, EPI, mb);
   switch (mb) {
-    case 1: launch_split<P, AM, EPI, 1>(grid, block, lds, a, s); break;
-    case 2: launch_split<P, AM, EPI, 2>(grid, block, lds, a, s); break;
-    case 3: launch_split<P, AM, EPI, 3>(grid, block, lds, a, s); break;
-    default: launch_split<P, AM, EPI, 4>(grid, block, lds, a, s); break;
+    case 1: return gemm_split_mb<P, AM, EPI, 1>(a, s, waves);
+    case 2: return gemm_split_mb<P, AM, EPI, 2>(a, s, waves);
+    case 3: return gemm_split_mb<P, AM, EPI, 3>(a, s, waves);
+    default: return gemm_split_mb<P, AM, EPI, 4>(a, s, waves);
   }
 }
 
@@ -1790,7 +1806,7 @@ static bool tile_valid(int prec, int epi, const GemmArgs& a, const GemmTile& t) 
     case T_AUTO: return true;
     case T_SPLIT:
       return t.mb >= 1 && t.mb <= SPLIT_ROWS / 16 && t.waves >= 1 && t.waves <= SPLIT_WAVES &&
-             split_lds(a, epi, t.mb) <= kSplitLdsMax;
+             split_fits(a, epi, t.mb);
     case T_TILE_S:
     case T_TILE_M: return true;
     case T_WIDE: return wide_ok(prec, epi, a);
@@ -1812,11 +1828,11 @@ static bool tile_valid(int prec, int epi, const GemmArgs& a, const GemmTile& t) 
 //    146 against 157).
 static GemmTile default_tile(int prec, int epi, const GemmArgs& a) {
   const int S = split_parts(a);
-  const GemmTile sp{T_SPLIT, split_mb(a, epi), S < SPLIT_WAVES ? S : SPLIT_WAVES};
+  const GemmTile sp{T_SPLIT, split_mb(a, prec, epi), S < SPLIT_WAVES ? S : SPLIT_WAVES};
   auto tiles = [&](long long bm, long long bn) {
     return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn);
   };
-  if ((a.M <= 32 || tiles(64, 32) < 128) && split_lds(a, epi, sp.mb) <= kSplitLdsMax) return sp;
+  if ((a.M <= 32 || tiles(64, 32) < 128) && split_fits(a, epi, sp.mb)) return sp;
   if (tiles(128, 128) >= (epi == E_RESID ? 1024 : 384) && wide_ok(prec, epi, a))
     return GemmTile{T_WIDE, 0, 0};
   return GemmTile{tiles(64, 64) < (prec == P_F32 ? 1024 : 512) ? T_TILE_S : T_TILE_M, 0, 0};
