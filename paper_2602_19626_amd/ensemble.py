@@ -8,21 +8,10 @@ nc_ensemble_forward / nc_ensemble_backward; the gradients are reduced over rows 
 """
 from __future__ import annotations
 
-import ctypes as C
-
 import torch
 
+from . import _dev_ptr, _stream_ptr
 from ._lib import check, lib
-
-
-def _ptr(t, dtype, name):
-    if not (t.is_cuda and t.dtype == dtype and t.is_contiguous()):
-        raise TypeError(f"{name} must be a contiguous {dtype} tensor on a HIP device")
-    return C.c_void_p(t.data_ptr())
-
-
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 def _forward(z, b, theta, P, target):
@@ -32,24 +21,24 @@ def _forward(z, b, theta, P, target):
     loss = torch.empty(rows, dtype=torch.float32, device=z.device)
     lse = torch.empty_like(loss)
     resp = torch.empty((rows, nexp), dtype=torch.float32, device=z.device)
-    Pp = _ptr(P, torch.float32, "P") if nexp > 1 else None
+    Pp = _dev_ptr(P, torch.float32, "P") if nexp > 1 else None
     check(lib().nc_ensemble_forward_lse(
-        _ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
-        _ptr(theta, torch.float32, "theta"), Pp, _ptr(target, torch.int32, "target"), rows, vocab,
-        nexp, _ptr(loss, torch.float32, "loss"), _ptr(resp, torch.float32, "resp"),
-        _ptr(lse, torch.float32, "lse"), _stream()))
+        _dev_ptr(z, torch.float32, "z"), _dev_ptr(b, torch.float32, "b"),
+        _dev_ptr(theta, torch.float32, "theta"), Pp, _dev_ptr(target, torch.int32, "target"),
+        rows, vocab, nexp, _dev_ptr(loss, torch.float32, "loss"), _dev_ptr(resp, torch.float32, "resp"),
+        _dev_ptr(lse, torch.float32, "lse"), _stream_ptr()))
     return loss, resp, lse
 
 
 def _backward(z, b, theta, resp, lse, target, gl, lr, gb, gth):
     rows, vocab = z.shape
-    opt = lambda t, name: None if t is None else _ptr(t, torch.float32, name)
+    opt = lambda t, name: None if t is None else _dev_ptr(t, torch.float32, name)
     check(lib().nc_ensemble_backward_lse(
-        _ptr(z, torch.float32, "z"), _ptr(b, torch.float32, "b"),
-        _ptr(theta, torch.float32, "theta"), _ptr(resp, torch.float32, "resp"),
-        _ptr(lse, torch.float32, "lse"), _ptr(target, torch.int32, "target"),
-        opt(gl, "grad_loss"), rows, vocab, theta.shape[0], C.c_float(lr), opt(gb, "grad_b"),
-        opt(gth, "grad_theta"), _stream()))
+        _dev_ptr(z, torch.float32, "z"), _dev_ptr(b, torch.float32, "b"),
+        _dev_ptr(theta, torch.float32, "theta"), _dev_ptr(resp, torch.float32, "resp"),
+        _dev_ptr(lse, torch.float32, "lse"), _dev_ptr(target, torch.int32, "target"),
+        opt(gl, "grad_loss"), rows, vocab, theta.shape[0], float(lr), opt(gb, "grad_b"),
+        opt(gth, "grad_theta"), _stream_ptr()))
 
 
 class EnsembleHead(torch.autograd.Function):
