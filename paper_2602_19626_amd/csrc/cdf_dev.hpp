@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "wave_dev.hpp"
+
 namespace nc {
 
 constexpr int kSegThreads = 256;
@@ -45,29 +47,13 @@ __device__ __forceinline__ void argmax_merge(float& v, uint32_t& i, float v2, ui
   }
 }
 
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
+// Key of (value, index) for valid probabilities: the larger value, then the lower index (the bits of
+// floats that are not negative order them; -0 counts as 0).
+__device__ __forceinline__ uint64_t max_key(float v, uint32_t i) {
+  return (uint64_t(__float_as_uint(v + 0.f)) << 32) | (0xFFFFFFFFu - i);
 }
-__device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
-  return v;
-}
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
-__device__ __forceinline__ void wave_argmax(float& v, uint32_t& i) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const float v2 = __shfl_xor(v, d, 64);
-    const uint32_t i2 = __shfl_xor(i, d, 64);
-    argmax_merge(v, i, v2, i2);
-  }
-}
+__device__ __forceinline__ float key_value(uint64_t k) { return __uint_as_float(uint32_t(k >> 32)); }
+__device__ __forceinline__ uint32_t key_index(uint64_t k) { return 0xFFFFFFFFu - uint32_t(k); }
 
 // Per-(row, segment) reduction result.
 struct SegPartial {
@@ -98,13 +84,10 @@ __device__ __forceinline__ uint32_t seg_index(uint32_t seg, int j, int tid, int 
 
 struct SegLds {
   uint64_t u64[kSegWaves];
-  float f[kSegWaves];
-  float f2[kSegWaves];
-  uint32_t u32[kSegWaves];
+  uint64_t best[kSegWaves];
   int flag[kSegWaves];
   uint32_t cols[kSegWaves * 4];
   SegPartial parts[kMaxSegs];
-  uint32_t bcast[8];
 };
 
 // First pass: reduce one segment of probabilities p[j][i] (already zero at or beyond V); tid is
@@ -113,9 +96,8 @@ __device__ __forceinline__ SegPartial seg_reduce(const float (&p)[4][4], uint32_
                                                  uint32_t m, SegLds& L, int tid) {
   const int lane = tid & 63, w = tid >> 6;
   int bad = 0;
-  uint64_t sum = 0;
-  float best = -1.f;
-  uint32_t besti = 0xFFFFFFFFu;
+  uint32_t sum = 0;  // (valid probabilities: at most 16 times 2^24)
+  uint64_t best = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -125,33 +107,31 @@ __device__ __forceinline__ SegPartial seg_reduce(const float (&p)[4][4], uint32_
       if (idx < V) {
         if (!(x >= 0.f && x <= 1.f)) bad = 1;  // also catches NaN
         sum += floor_count(x, m);
-        if (x > best) {  // increasing index order per thread: strict > keeps the first
-          best = x;
-          besti = idx;
-        }
+        const uint64_t k = max_key(x, idx);
+        best = k > best ? k : best;
       }
     }
-  sum = wave_sum_u64(sum);
-  wave_argmax(best, besti);
+  const uint64_t wsum = wave_sum_u64(sum);
+  best = wave_max_u64(best);
   const int wbad = __any(bad) ? 1 : 0;
   if (lane == 0) {
-    L.u64[w] = sum;
-    L.f[w] = best;
-    L.u32[w] = besti;
+    L.u64[w] = wsum;
+    L.best[w] = best;
     L.flag[w] = wbad;
   }
   __syncthreads();
   SegPartial r;
   uint64_t tot = 0;
-  r.maxv = -1.f;
-  r.maxi = 0xFFFFFFFFu;
+  best = 0;
   r.bad = 0;
 #pragma unroll
   for (int k = 0; k < kSegWaves; ++k) {
     tot += L.u64[k];
-    argmax_merge(r.maxv, r.maxi, L.f[k], L.u32[k]);
+    best = L.best[k] > best ? L.best[k] : best;
     r.bad |= L.flag[k];
   }
+  r.maxv = key_value(best);
+  r.maxi = key_index(best);
   r.sum = tot >= 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(tot);
   return r;
 }
@@ -212,12 +192,7 @@ __device__ __forceinline__ void seg_scan(const float (&p)[4][4], uint32_t seg, u
       c[j][i] = idx < V ? corrected_count(p[j][i], idx, q) : 0u;
       s += c[j][i];
     }
-    uint32_t v = s;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(v, d, 64);
-      if (lane >= d) v += y;
-    }
+    const uint32_t v = wave_scan_u32(s);
     if (lane == 63) L.cols[w * 4 + j] = v;
     excl[j] = v - s;
   }

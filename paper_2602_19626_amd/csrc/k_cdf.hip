@@ -116,8 +116,7 @@ __global__ __launch_bounds__(kRowThreads, 6) void cdf24_row_kernel(const float* 
                                                                    uint32_t* __restrict__ cdf,
                                                                    int32_t* __restrict__ status) {
   __shared__ uint64_t s_sum[kRowWaves];
-  __shared__ float s_best[kRowWaves];
-  __shared__ uint32_t s_bi[kRowWaves];
+  __shared__ uint64_t s_best[kRowWaves];
   __shared__ int s_bad[kRowWaves];
   __shared__ uint32_t s_wt[kRowWaves][kRowBlocks];
   __shared__ uint32_t s_bt[kRowBlocks];
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(kRowThreads, 6) void cdf24_row_kernel(const float* 
   const f4v* p4 = reinterpret_cast<const f4v*>(p) + tid;
   const uint32_t m = total - V;
   // pass 1 (V % 4 == 0: a group of four is either whole or past the end)
-  uint64_t sum = 0;
+  uint32_t sum = 0;  // (valid probabilities: at most 96 times 2^24)
   float best = -1.f;
   uint32_t bi = 0xFFFFFFFFu;
   int bad = 0;
@@ -162,13 +161,12 @@ __global__ __launch_bounds__(kRowThreads, 6) void cdf24_row_kernel(const float* 
       sum += c4;
     }
   }
-  sum = wave_sum_u64(sum);
-  wave_argmax(best, bi);
+  const uint64_t wsum = wave_sum_u64(sum);
+  const uint64_t wbest = wave_max_u64(bi < V ? max_key(best, bi) : 0);
   bad = __any(bad) ? 1 : 0;
   if (lane == 0) {
-    s_sum[w] = sum;
-    s_best[w] = best;
-    s_bi[w] = bi;
+    s_sum[w] = wsum;
+    s_best[w] = wbest;
     s_bad[w] = bad;
   }
   __syncthreads();
@@ -180,7 +178,7 @@ __global__ __launch_bounds__(kRowThreads, 6) void cdf24_row_kernel(const float* 
     int bd = 0;
     for (int k = 0; k < kRowWaves; ++k) {
       tot += s_sum[k];
-      argmax_merge(bv, b, s_best[k], s_bi[k]);
+      argmax_merge(bv, b, key_value(s_best[k]), key_index(s_best[k]));
       bd |= s_bad[k];
     }
     const int64_t r = int64_t(total) - int64_t(tot);
@@ -197,12 +195,7 @@ __global__ __launch_bounds__(kRowThreads, 6) void cdf24_row_kernel(const float* 
     const uint32_t i0 = q * kRowBlock + 4 * tid;
     uint32_t c4 = s_cnt[q][tid];
     if (rq.argmax >= i0 && rq.argmax < i0 + 4) c4 = uint32_t(int32_t(c4) + rq.residual);
-    uint32_t incl = c4;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += y;
-    }
+    const uint32_t incl = wave_scan_u32(c4);
     if (lane == 63) s_wt[w][q] = incl;
     s_cnt[q][tid] = incl - c4;
   }

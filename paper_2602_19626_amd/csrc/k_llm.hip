@@ -122,22 +122,15 @@ constexpr int KP = 64;
 // ssq[b] = sum of x^2 over the block by one fixed tree (block_ssq16); the scale adds the block
 // sums in block order.  Prefill and decode kernels therefore derive bitwise equal scales.
 
-// The value of the lane n further (cyclically) in the same sixteen lanes, by a register rotation.
-template <int n>
-__device__ __forceinline__ float lane_ror16(float v) {
-  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(
-      0, int(__float_as_uint(v)), 0x120 + n, 0xF, 0xF, true)));
-}
-
 // Block sum of squares of 16 values held by 16 consecutive lanes (lane % 16 = column); every lane
 // of the group returns the same bits: the tree of partners c ^ 8, c ^ 4, c ^ 2, c ^ 1 (after each
 // step the values repeat with half the period, so rotating by 8, 4, 2, 1 fetches the partner's).
 __device__ __forceinline__ float block_ssq16(float x) {
   float v = x * x;
-  v += lane_ror16<8>(v);
-  v += lane_ror16<4>(v);
-  v += lane_ror16<2>(v);
-  v += lane_ror16<1>(v);
+  v += dpp_f<kRor + 8>(v);
+  v += dpp_f<kRor + 4>(v);
+  v += dpp_f<kRor + 2>(v);
+  v += dpp_f<kRor + 1>(v);
   return v;
 }
 
@@ -740,7 +733,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, 2) void gemm_tile_kernel(
         for (int e = 0; e < 4; ++e) {
           v[e] = val(i, j, e);
           // the other half of the head: the pair's other block, or (hd = 16) the lane 8 further
-          const float other = val(i, j ^ 1, e), across = __shfl_xor(v[e], 8, 64);
+          const float other = val(i, j ^ 1, e), across = dpp_f<kRor + 8>(v[e]);
           pr[e] = n < nqk ? (a.hd == 16 ? across : other) : 0.f;
         }
         if (m >= a.M || n >= a.N) continue;
@@ -1002,7 +995,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
       const int t = t0 + threadIdx.x;
       const int m = min(t >> 4, M - 1), c = t & 15;
       const float v = sum(m, 0, c);
-      const float up = GS == 2 ? sum(m, GS - 1, c) : lane_ror16<8>(v);
+      const float up = GS == 2 ? sum(m, GS - 1, c) : dpp_f<kRor + 8>(v);
       const int col = GS == 2 ? gi * 16 + c : gi * 8 + (c & 7);
       if (t < M * 16 && (GS == 2 || c < 8) && col < N / 2)
         omax = fmaxf(omax, emit_glu<P>(a, r0 + m, col, v, up));
@@ -1040,7 +1033,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
       const int t = t0 + threadIdx.x;
       const int m = min(t >> 4, M - 1), c = t & 15;
       float v = sum(m, 0, c);
-      const float partner = lane_ror16<8>(v);  // the other half of the RoPE pair
+      const float partner = dpp_f<kRor + 8>(v);  // the other half of the RoPE pair
       if (t >= M * 16) continue;
       const int i = (gi & ((hd >> 4) - 1)) * 8 + (c & 7), within = i + (c >> 3) * h2;
       if (t0 > 0) {
@@ -1195,8 +1188,9 @@ __device__ __forceinline__ void chunk_softmax(v4f (&st)[4], const AttnArgs& a, c
       st[b][j] = ok ? st[b][j] * a.scale_log2 : -INFINITY;
       mx = fmaxf(mx, st[b][j]);
     }
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  auto larger = [](float x, float y) { return fmaxf(x, y); };
+  auto plus = [](float x, float y) { return x + y; };
+  mx = combine_x32(combine_x16(mx, larger), larger);
   float ls = 0.f;
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
@@ -1204,8 +1198,7 @@ __device__ __forceinline__ void chunk_softmax(v4f (&st)[4], const AttnArgs& a, c
     for (int j = 0; j < 4; ++j) st[b][j] = mx == -INFINITY ? 0.f : exp2f(st[b][j] - mx);
     ls += (st[b][0] + st[b][1]) + (st[b][2] + st[b][3]);
   }
-  ls += __shfl_xor(ls, 16, 64);
-  ls += __shfl_xor(ls, 32, 64);
+  ls = combine_x32(combine_x16(ls, plus), plus);
   m = mx;
   l = ls;
 }

@@ -29,19 +29,36 @@ __device__ __forceinline__ LsePart lse_merge(LsePart a, LsePart b) {
   return LsePart{M, a.s * expf(a.m - M) + b.s * expf(b.m - M)};
 }
 
-// logsumexp of the row from its segment partials, combined in segment order; the partials are
-// read 16 at a time before they are merged, so their loads overlap
-__device__ __forceinline__ float row_lse(const LsePart* parts, int nseg) {
-  LsePart acc{-INFINITY, 0.f};
-  for (int k0 = 0; k0 < nseg; k0 += 16) {
-    LsePart buf[16];
+// The logsumexp partial of a wave's 64 partials by one tree: lane L merges lane L + d for
+// d = 1, 2, 4, ... with the lower lane first.  Lanes whose partner is another tree node's (or
+// missing) hold values that no node of lane 0's tree reads.
+template <int kCtrl>
+__device__ __forceinline__ LsePart dpp_lse(LsePart a) {
+  return lse_merge(a, LsePart{dpp_f<kCtrl>(a.m), dpp_f<kCtrl>(a.s)});
+}
+__device__ __forceinline__ LsePart wave_lse(LsePart p) {
+  p = dpp_lse<kShl + 1>(p);
+  p = dpp_lse<kShl + 2>(p);
+  p = dpp_lse<kShl + 4>(p);
+  p = dpp_lse<kShl + 8>(p);
+  LsePart q[4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) buf[u] = k0 + u < nseg ? parts[k0 + u] : LsePart{-INFINITY, 0.f};
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (k0 + u < nseg) acc = k0 + u == 0 ? buf[u] : lse_merge(acc, buf[u]);
-  }
-  return acc.m + logf(acc.s);
+  for (int k = 0; k < 4; ++k) q[k] = LsePart{read_lane(p.m, 16 * k), read_lane(p.s, 16 * k)};
+  return lse_merge(lse_merge(q[0], q[1]), lse_merge(q[2], q[3]));
+}
+
+// Logsumexp of a row from its segment partials, merged in segment order; lane k of the wave holds
+// partial k (mine).  The running maxima of the fold are exact whatever the order, so lane k computes
+// the two factors of merge k and only the products and sums are serial.
+__device__ __forceinline__ float row_lse(const LsePart mine, int nseg, int lane) {
+  const float run = wave_scan_max(lane < nseg ? mine.m : -INFINITY);
+  const float prev = dpp_f<kWaveShr1>(run, -INFINITY);
+  const bool empty = run == -INFINITY;
+  const float e1 = empty ? 0.f : expf(prev - run);
+  const float e2 = empty ? 0.f : mine.s * expf(mine.m - run);
+  float acc = read_lane(mine.s, 0);
+  for (int k = 1; k < nseg; ++k) acc = acc * read_lane(e1, k) + read_lane(e2, k);
+  return read_lane(run, nseg - 1) + logf(acc);
 }
 
 struct RowIn {
@@ -131,11 +148,7 @@ __device__ __forceinline__ void v1_seg(const VocabParams& P, const StreamState& 
         for (int i = 0; i < 4; ++i) sum += expf(u[j][i] - m);
     part = LsePart{m, sum};
   }
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const LsePart o{__shfl_xor(part.m, d, 64), __shfl_xor(part.s, d, 64)};
-    part = (lane & d) ? lse_merge(o, part) : lse_merge(part, o);
-  }
+  part = wave_lse(part);
   if (lane == 0) wl[w] = part;
   __syncthreads();
   if (active && tid == 0) {
@@ -158,7 +171,9 @@ __device__ __forceinline__ RowIn make_row(const VocabParams& P, const StreamStat
   R.b = S.b + (size_t)s * P.V;
   R.png = S.png + (size_t)s * P.V;
   R.pk = S.pk ? S.pk + (size_t)s * P.K * P.V : nullptr;
-  R.lse = uses_llm(R.mode) ? row_lse(A.lse_parts + (size_t)r * nseg, nseg) : 0.f;
+  const int lane = threadIdx.x & 63;
+  const LsePart mine = A.lse_parts[(size_t)r * nseg + min(lane, nseg - 1)];
+  R.lse = uses_llm(R.mode) ? row_lse(mine, nseg, lane) : 0.f;
   for (int j = 0; j < kMaxExperts; ++j) R.w[j] = 0.f;
   row_weights(P, S.lw + (size_t)s * kMaxExperts, R.w);
   return R;
@@ -632,8 +647,8 @@ __device__ __forceinline__ NgRow ng_row(const VocabParams& P, const StreamState&
   const int nq = idq >= 0 ? nraw : 0;
 #pragma unroll
   for (int k = 0; k < kMaxOrder; ++k) {
-    g.id[k] = __shfl(idq, k, 64);
-    g.n[k] = __shfl(nq, k, 64);
+    g.id[k] = __builtin_amdgcn_readlane(idq, k);
+    g.n[k] = __builtin_amdgcn_readlane(nq, k);
   }
 #pragma unroll
   for (int k = 0; k < kMaxOrder; ++k) {
@@ -921,92 +936,6 @@ __global__ __launch_bounds__(kSegThreads) void ngram_fix_kernel(VocabParams P, S
 //   known_finish    the intervals of every position from the count partials.
 // Every value is computed by the expressions, and reduced in the order, of the step-by-step
 // kernels above, so the coded bits are those of the sequential decode.
-
-// Wave reductions in the lanes' registers (data-parallel primitives: a few cycles a step, where a
-// shuffle goes through LDS).  Integer sums and maxima, so the order does not matter; the result is
-// that of lane 63.
-template <int kCtrl, int kRows>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {  // 0 where there is no source lane
-  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false));
-}
-constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118, kBcast15 = 0x142,
-              kBcast31 = 0x143, kWaveShr1 = 0x138, kShl1 = 0x101, kShl2 = 0x102, kShl4 = 0x104, kShl8 = 0x108;
-
-template <int kCtrl, int kRows>
-__device__ __forceinline__ float dpp_low(float v) {  // -infinity where there is no source lane
-  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(
-      int(0xFF800000u), int(__float_as_uint(v)), kCtrl, kRows, 0xF, false)));
-}
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-  v += dpp_u32<kShr1, 0xF>(v);
-  v += dpp_u32<kShr2, 0xF>(v);
-  v += dpp_u32<kShr4, 0xF>(v);
-  v += dpp_u32<kShr8, 0xF>(v);
-  v += dpp_u32<kBcast15, 0xA>(v);
-  v += dpp_u32<kBcast31, 0xC>(v);
-  return __builtin_amdgcn_readlane(v, 63);
-}
-
-template <int kCtrl, int kRows>
-__device__ __forceinline__ uint64_t dpp_max_u64(uint64_t v) {
-  const uint64_t o = uint64_t(dpp_u32<kCtrl, kRows>(uint32_t(v))) |
-                     (uint64_t(dpp_u32<kCtrl, kRows>(uint32_t(v >> 32))) << 32);
-  return o > v ? o : v;
-}
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-  v = dpp_max_u64<kShr1, 0xF>(v);
-  v = dpp_max_u64<kShr2, 0xF>(v);
-  v = dpp_max_u64<kShr4, 0xF>(v);
-  v = dpp_max_u64<kShr8, 0xF>(v);
-  v = dpp_max_u64<kBcast15, 0xA>(v);
-  v = dpp_max_u64<kBcast31, 0xC>(v);
-  return uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(v), 63))) |
-         (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(v >> 32), 63))) << 32);
-}
-
-__device__ __forceinline__ float read_lane(float v, int lane) {
-  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
-}
-
-// The logsumexp partial of a wave's 64 partials by the tree of v1_seg: lane L merges lane L + d for
-// d = 1, 2, 4, ... with the lower lane first.  Lanes whose partner is another tree node's (or
-// missing) hold values that no node of lane 0's tree reads.
-template <int kCtrl>
-__device__ __forceinline__ LsePart dpp_lse(LsePart a) {
-  const LsePart o{__uint_as_float(dpp_u32<kCtrl, 0xF>(__float_as_uint(a.m))),
-                  __uint_as_float(dpp_u32<kCtrl, 0xF>(__float_as_uint(a.s)))};
-  return lse_merge(a, o);
-}
-__device__ __forceinline__ LsePart wave_lse(LsePart p) {
-  p = dpp_lse<kShl1>(p);
-  p = dpp_lse<kShl2>(p);
-  p = dpp_lse<kShl4>(p);
-  p = dpp_lse<kShl8>(p);
-  LsePart q[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) q[k] = LsePart{read_lane(p.m, 16 * k), read_lane(p.s, 16 * k)};
-  return lse_merge(lse_merge(q[0], q[1]), lse_merge(q[2], q[3]));
-}
-
-// row_lse with the lanes sharing the work: the running maxima of the fold are exact whatever the
-// order, so lane k computes the two factors of merge k and only the products and sums are serial.
-__device__ __forceinline__ float lane_row_lse(const LsePart mine, int nseg, int lane) {
-  float run = lane < nseg ? mine.m : -INFINITY;  // inclusive maximum of lanes 0 .. lane
-  run = fmaxf(run, dpp_low<kShr1, 0xF>(run));
-  run = fmaxf(run, dpp_low<kShr2, 0xF>(run));
-  run = fmaxf(run, dpp_low<kShr4, 0xF>(run));
-  run = fmaxf(run, dpp_low<kShr8, 0xF>(run));
-  run = fmaxf(run, dpp_low<kBcast15, 0xA>(run));
-  run = fmaxf(run, dpp_low<kBcast31, 0xC>(run));
-  const float prev = dpp_low<kWaveShr1, 0xF>(run);
-  const bool empty = run == -INFINITY;
-  const float e1 = empty ? 0.f : expf(prev - run);
-  const float e2 = empty ? 0.f : mine.s * expf(mine.m - run);
-  float acc = read_lane(mine.s, 0);
-  for (int k = 1; k < nseg; ++k) acc = acc * read_lane(e1, k) + read_lane(e2, k);
-  return read_lane(run, nseg - 1) + logf(acc);
-}
 
 // The order-k context of position i (tokens i - k .. i - 1) in table t: its pool index or -1, and
 // the empty slot where it would go.  Eight slots of the probe sequence per round of loads, one per
@@ -1447,7 +1376,7 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
   R.K = P.K;
   R.mode = mode;
   R.use_head = P.use_head;
-  R.lse = uses_llm(mode) ? lane_row_lse(mine, nseg, lane) : 0.f;
+  R.lse = uses_llm(mode) ? row_lse(mine, nseg, lane) : 0.f;
   R.w[0] = expf(lw[0]);
   R.w[1] = expf(lw[1]);
   float p[4][4], pt[4][4];
@@ -1468,8 +1397,7 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
       before += t < uint32_t(tok) ? c : 0u;
       if (t < uint32_t(V)) {
         if (!(x >= 0.f && x <= 1.f)) bad = 1;
-        // probabilities are not negative: their bits order them; the lowest index wins ties
-        const uint64_t key = (uint64_t(__float_as_uint(x)) << 32) | (0xFFFFFFFFu - t);
+        const uint64_t key = max_key(x, t);
         best = key > best ? key : best;
       }
       if (t == uint32_t(tok)) {
@@ -1496,15 +1424,14 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
     }
     if (learn && t0 < uint32_t(V)) *reinterpret_cast<f4v*>(b + t0) = nb;
   }
-  // (a thread's 16 counts are below 2^28, so a wave's fit in two sums of 16-bit halves)
-  const uint32_t lo = wave_sum_u32(sum & 0xFFFFu), hi = wave_sum_u32(sum >> 16);
+  const uint64_t wsum = wave_sum_u64(sum);
   before = wave_sum_u32(before);
   best = wave_max_u64(best);
   const int any_bad = __any(bad) ? 1 : 0;
   const bool lse2 = more && j + 1 < left && uses_llm(mode2);
   const LsePart part = lse2 ? known_lse(u) : LsePart{-INFINITY, 0.f};
   if (lane == 0) {
-    s_sum[w] = (uint64_t(hi) << 16) + lo;
+    s_sum[w] = wsum;
     s_before[w] = before;
     s_best[w] = best;
     s_bad[w] = any_bad;
@@ -1524,8 +1451,8 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
     }
     SegPartial sp;
     sp.sum = tot >= 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(tot);
-    sp.maxv = __uint_as_float(uint32_t(bk >> 32));
-    sp.maxi = 0xFFFFFFFFu - uint32_t(bk);
+    sp.maxv = key_value(bk);
+    sp.maxi = key_index(bk);
     sp.bad = bd;
     static_cast<SegPartial*>(C.segs)[row * nseg + seg] = sp;
     if (uint32_t(tok) / kSeg == uint32_t(seg)) C.rec[row].before = bf;
@@ -1655,11 +1582,7 @@ __global__ __launch_bounds__(kSegThreads) void ens_lse_kernel(const float* __res
 #pragma unroll
       for (int i = 0; i < 4; ++i) sum += expf(u[j][i] - m);
   LsePart part{m, sum};
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const LsePart o{__shfl_xor(part.m, d, 64), __shfl_xor(part.s, d, 64)};
-    part = (lane & d) ? lse_merge(o, part) : lse_merge(part, o);
-  }
+  part = wave_lse(part);
   if (lane == 0) wl[w] = part;
   __syncthreads();
   if (tid == 0) {
@@ -1667,16 +1590,6 @@ __global__ __launch_bounds__(kSegThreads) void ens_lse_kernel(const float* __res
     for (int k = 1; k < kSegWaves; ++k) acc = lse_merge(acc, wl[k]);
     parts[(size_t)r * nseg + seg] = acc;
   }
-}
-
-// The row's logsumexp with one wave per row: lane k fetches segment k's partial, every lane merges
-// them in segment order.
-__device__ __forceinline__ float wave_row_lse(const LsePart* parts, int nseg, int lane) {
-  const LsePart mine = parts[min(lane, nseg - 1)];
-  LsePart acc{__shfl(mine.m, 0, 64), __shfl(mine.s, 0, 64)};
-  for (int k = 1; k < nseg; ++k)
-    acc = lse_merge(acc, LsePart{__shfl(mine.m, k, 64), __shfl(mine.s, k, 64)});
-  return acc.m + logf(acc.s);
 }
 
 // Per row: lse, loss = -log p(t*), responsibilities r_j = w_j q_j(t*) / p(t*).  A chain of a few
@@ -1698,13 +1611,13 @@ __global__ __launch_bounds__(64 * kEnsRows) void ens_row_kernel(
   const float v = *src, bt = b[t];
   float w[kMaxExperts];
   gate_weights(theta, nexp, w);
-  const float lse = wave_row_lse(parts + (size_t)r * nseg, nseg, lane);
+  const float lse = row_lse(parts[(size_t)r * nseg + min(lane, nseg - 1)], nseg, lane);
   float q[kMaxExperts];
-  q[0] = expf(__shfl(v, 0, 64) + bt - lse);
+  q[0] = expf(read_lane(v, 0) + bt - lse);
   float p = w[0] * q[0];
 #pragma unroll
   for (int j = 1; j < kMaxExperts; ++j) {
-    q[j] = __shfl(v, j, 64);
+    q[j] = read_lane(v, j);
     p = j < nexp ? p + w[j] * q[j] : p;
   }
   if (lane == 0) {
@@ -1722,7 +1635,7 @@ __global__ __launch_bounds__(64 * kEnsRows) void ens_lse_to_row_kernel(
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * kEnsRows + (threadIdx.x >> 6);
   if (r >= rows) return;
-  const float v = wave_row_lse(parts + (size_t)r * nseg, nseg, lane);
+  const float v = row_lse(parts[(size_t)r * nseg + min(lane, nseg - 1)], nseg, lane);
   if (lane == 0) lse[r] = v;
 }
 
@@ -1801,9 +1714,9 @@ __global__ __launch_bounds__(kGradThreads) void ens_grad_kernel(
     const int tt = target[ru];
 #pragma unroll
     for (int u = 0; u < kGradRows; ++u) {
-      const float q0 = expf(x[u] + bt - __shfl(l, u, 64));
-      const float ind = __shfl(tt, u, 64) == t ? 1.f : 0.f;
-      const float d = __shfl(f, u, 64) * (q0 - ind);
+      const float q0 = expf(x[u] + bt - read_lane(l, u));
+      const float ind = __builtin_amdgcn_readlane(tt, u) == t ? 1.f : 0.f;
+      const float d = read_lane(f, u) * (q0 - ind);
       g = r0 + u < rows ? g + d : g;
     }
   }
