@@ -76,9 +76,10 @@ struct nc_ctx {
   int prec = P_F32, att = P_F32;
   int dev = 0;
   hipStream_t st = nullptr;
-  // chunks of known tokens: the transformer and output layer run on st, the n-gram side on st2 and
-  // the position-by-position chain on st3, on two sets of chunk buffers in turn
-  hipStream_t st2 = nullptr, st3 = nullptr;
+  // chunks of known tokens: the transformer passes run on st, the n-gram side on st2, the
+  // position-by-position chain on st3 and the output layer of passes of several chunks on st4, on
+  // two sets of chunk buffers in turn
+  hipStream_t st2 = nullptr, st3 = nullptr, st4 = nullptr;
   int d = 0, hq = 0, hk = 0, hd = 0, F = 0, V = 0, nl = 0, R = 0;
   // weights
   std::vector<void*> allocs;
@@ -133,12 +134,14 @@ struct nc_ctx {
     hipEvent_t ngram = nullptr, logits = nullptr, done = nullptr;
   } kb[2];
   DevBuf<int32_t> kbad;  // set by a chunk with an invalid distribution
-  // staged inputs of the passes over known tokens, two in turn
+  // passes over known tokens, two in turn: the staged inputs, and the pass's output-layer operand
+  // rows with their scales where several chunks follow (see keep_rows)
   struct StageSlot {
-    DevBuf<uint8_t> d;
+    DevBuf<uint8_t> d, y;
+    DevBuf<float> inv;
     void* h = nullptr;
     size_t bytes = 0;
-    hipEvent_t up = nullptr, done = nullptr;
+    hipEvent_t up = nullptr, rows = nullptr, done = nullptr;
   } slots[2];
   DevBuf<int32_t> steprows, arows;
   DevBuf<uint32_t> targets;
@@ -200,7 +203,7 @@ struct nc_ctx {
 
 nc_ctx::~nc_ctx() {
   if (dev >= 0) (void)hipSetDevice(dev);
-  for (hipStream_t q : {st, st2, st3})
+  for (hipStream_t q : {st, st2, st3, st4})
     if (q) (void)hipStreamSynchronize(q);
   for (void* p : allocs) (void)hipFree(p);
   DevBuf<float>* fb[] = {&yb, &xss, &aws, &xinv, &hinv, &amax, &rope, &b, &png, &pk, &lw, &Hd, &pmaxd, &hlast, &x, &ptok, &z, &zseg,
@@ -248,13 +251,16 @@ nc_ctx::~nc_ctx() {
   kbad.release();
   for (StageSlot& q : slots) {
     q.d.release();
+    q.y.release();
+    q.inv.release();
     if (q.h) (void)hipHostFree(q.h);
-    for (hipEvent_t e : {q.up, q.done})
+    for (hipEvent_t e : {q.up, q.rows, q.done})
       if (e) (void)hipEventDestroy(e);
   }
   for (auto& g : graphs) (void)hipGraphExecDestroy(g.second);
   for (auto& g : egraphs)
     if (g.second.ex) (void)hipGraphExecDestroy(g.second.ex);
+  if (st4) (void)hipStreamDestroy(st4);
   if (st3) (void)hipStreamDestroy(st3);
   if (st2) (void)hipStreamDestroy(st2);
   if (st) (void)hipStreamDestroy(st);
@@ -307,6 +313,7 @@ void sync(nc_ctx* c) {
   NC_HIP(hipStreamSynchronize(c->st));
   NC_HIP(hipStreamSynchronize(c->st2));
   NC_HIP(hipStreamSynchronize(c->st3));
+  NC_HIP(hipStreamSynchronize(c->st4));
   c->stats.wait_seconds +=
       std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   prof_flush(c);
@@ -835,12 +842,13 @@ void run_pass(nc_ctx* c, const PassPlan& p, const uint8_t* dstage, BodyOpts o = 
 }
 
 void run_lm_head(nc_ctx* c, const void* A, const float* Ainv, const int32_t* a_rows, int M,
-                 float* zout, bool calib = false) {
+                 float* zout, bool calib = false, hipStream_t st = nullptr) {
+  if (!st) st = c->st;
   const GemmArgs a = args_lm(c, A, Ainv, a_rows, M, zout, calib);
   const int prec = calib ? P_F32 : c->prec;
-  prof_begin(c, NC_K_LMHEAD);
-  launch_gemm(prec, A_NORM, E_STORE, a, c->st, tile_for(c, calib, NC_G_LMHEAD, M));
-  prof_end(c, NC_K_LMHEAD, gemm_bytes(a, A_NORM, E_STORE, prec, c->att), 2.0 * M * a.N * a.K);
+  prof_begin(c, NC_K_LMHEAD, st);
+  launch_gemm(prec, A_NORM, E_STORE, a, st, tile_for(c, calib, NC_G_LMHEAD, M));
+  prof_end(c, NC_K_LMHEAD, gemm_bytes(a, A_NORM, E_STORE, prec, c->att), 2.0 * M * a.N * a.K, st);
 }
 
 // Plan the appends of x positions [appended[s], upto] of each listed stream, in passes of at most
@@ -1153,12 +1161,31 @@ KnownChunk known_begin(nc_ctx* c, KnownRun& run, const nc_ctx::StageSlot& slot, 
   return C;
 }
 
-// The chunk's logits from rows ar[j * B + r] of the pass just run, then its chain.
-void known_end(nc_ctx* c, const KnownRun& run, const KnownChunk& C, const int32_t* ar, int p0) {
+// Keep the n output-layer operand rows of the pass just run, and their scales, in its slot: the next
+// pass overwrites yb while the output layer still works through this one's chunks.  With one chunk
+// there is nothing to gain from it (the output layer then follows the pass on st); with several
+// the pass runs beside the chains of the chunks before (64 BF16 streams of 1,000 tokens: 60.3
+// to 55.9 ms a call).
+void keep_rows(nc_ctx* c, nc_ctx::StageSlot& slot, size_t n) {
+  const size_t row = size_t(c->d) * prec_bytes(c->prec);
+  slot.y.alloc(n * row);
+  slot.inv.alloc(n);
+  NC_HIP(hipMemcpyAsync(slot.y.p, c->yb.p, n * row, hipMemcpyDeviceToDevice, c->st));
+  NC_HIP(hipMemcpyAsync(slot.inv.p, c->xinv.p, n * 4, hipMemcpyDeviceToDevice, c->st));
+  NC_HIP(hipEventRecord(slot.rows, c->st));
+}
+
+// The chunk's logits from rows ar[j * B + r] of the slot that keeps them (on st4), or of the pass
+// just run (on st); then its chain.
+void known_end(nc_ctx* c, const KnownRun& run, const KnownChunk& C, const nc_ctx::StageSlot* slot,
+               const int32_t* ar, int p0) {
   nc_ctx::KnownBufs& k = c->kb[(run.chunk - 1) & 1];
-  NC_HIP(hipStreamWaitEvent(c->st, k.done, 0));
-  run_lm_head(c, c->yb.p, c->xinv.p, ar, C.np * C.B, k.z.p);
-  NC_HIP(hipEventRecord(k.logits, c->st));
+  hipStream_t st = slot ? c->st4 : c->st;
+  NC_HIP(hipStreamWaitEvent(st, k.done, 0));
+  if (slot) NC_HIP(hipStreamWaitEvent(st, slot->rows, 0));
+  run_lm_head(c, slot ? static_cast<const void*>(slot->y.p) : c->yb.p,
+              slot ? slot->inv.p : c->xinv.p, ar, C.np * C.B, k.z.p, false, st);
+  NC_HIP(hipEventRecord(k.logits, st));
   NC_HIP(hipStreamWaitEvent(c->st3, k.ngram, 0));
   NC_HIP(hipStreamWaitEvent(c->st3, k.logits, 0));
   // per row: z read twice (for its logsumexp beside the position before, and for its own step),
@@ -1229,8 +1256,12 @@ bool encode_known(nc_ctx* c, const std::vector<const int32_t*>& tok,
       const int p0 = int(a + pc.i0);
       const KnownChunk K = known_begin(c, run, c->slots[slot], pc.off_left, 0, pc.B, pc.np, p0,
                                        true);
-      if (q == 0) run_pass(c, plan, dst);
-      known_end(c, run, K, reinterpret_cast<const int32_t*>(dst + pc.off_ar), p0);
+      if (q == 0) {
+        run_pass(c, plan, dst);
+        if (pieces.size() > 1) keep_rows(c, c->slots[slot], plan.rows.size());
+      }
+      known_end(c, run, K, pieces.size() > 1 ? &c->slots[slot] : nullptr,
+                reinterpret_cast<const int32_t*>(dst + pc.off_ar), p0);
     }
     NC_HIP(hipEventRecord(c->slots[slot].done, c->st3));
   }
@@ -1353,7 +1384,7 @@ void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
     if (np > 0) {
       const KnownChunk K = known_begin(c, run, c->slots[slot], off_left, s, 1, np, q0, false);
       run_pass(c, plan, dst);
-      known_end(c, run, K, reinterpret_cast<const int32_t*>(dst + off_ar), q0);
+      known_end(c, run, K, nullptr, reinterpret_cast<const int32_t*>(dst + off_ar), q0);
     } else {
       run_pass(c, plan, dst);
     }
@@ -1422,11 +1453,12 @@ nc_status nc_create(const nc_config* cfg, const float* w, nc_ctx** out) {
     NC_HIP(hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking));
     NC_HIP(hipStreamCreateWithFlags(&c->st2, hipStreamNonBlocking));
     NC_HIP(hipStreamCreateWithFlags(&c->st3, hipStreamNonBlocking));
+    NC_HIP(hipStreamCreateWithFlags(&c->st4, hipStreamNonBlocking));
     for (auto& k : c->kb)
       for (hipEvent_t* e : {&k.ngram, &k.logits, &k.done})
         NC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     for (auto& q : c->slots)
-      for (hipEvent_t* e : {&q.up, &q.done})
+      for (hipEvent_t* e : {&q.up, &q.rows, &q.done})
         NC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     c->kbad.alloc(1);
     // the attention chunk counters start at zero; every launch leaves them at zero
