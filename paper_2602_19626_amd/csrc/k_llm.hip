@@ -1080,7 +1080,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
 // chunk, MFMA row r of block b holds key 16 (r / 4) + 4 b + r % 4: a lane's P*V operand then
 // covers 16 consecutive keys over the 4 blocks, so its V^T reads are contiguous.
 
-constexpr int KCH = 64;      // keys per chunk
+constexpr int KCH = kAttnChunk;  // keys per chunk
 constexpr int QCH = 4;       // chunks per quad
 constexpr int GQ = 4;        // quads per group
 constexpr int MAXQ = 12;     // quads an item may span (window <= 2,048 keys + 15 query positions)
@@ -1175,32 +1175,69 @@ __device__ __forceinline__ void load_q(QFrag<PA>& q, const AttnArgs& a, const At
   }
 }
 
+// Every key of the chunk is in every column's window.
+__device__ __forceinline__ bool chunk_inside(const AttnItem& it, int g, int key0) {
+  return key0 >= it.cs_hi && key0 + KCH - 1 <= it.pos_base + it.c0 / g;
+}
+
 // Softmax of one chunk's masked scores st (in place: scores -> probabilities); returns (m, l).
+// exp2f is the hardware's exponential but below -126, where it scales its argument and result
+// to reach the denormals; a lane's smallest score tells whether any of its 16 needs that.  A chunk
+// inside every window has no masks.  Both are uniform branches; together they take a chunk
+// of BF16 attention, which is bound by these instructions, from about 900 to 350 of them.
 __device__ __forceinline__ void chunk_softmax(v4f (&st)[4], const AttnArgs& a, const AttnCol& c,
-                                              int key0, int grp, float& m, float& l) {
-  float mx = -INFINITY;
+                                              int key0, int grp, bool inside, float& m,
+                                              float& l) {
+  float mx = -INFINITY, mn = INFINITY;
+  if (inside) {
 #pragma unroll
-  for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int key = key0 + chunk_key(b, grp * 4 + j);
-      const bool ok = c.valid && key >= c.cs && key <= c.pos;
-      st[b][j] = ok ? st[b][j] * a.scale_log2 : -INFINITY;
-      mx = fmaxf(mx, st[b][j]);
-    }
+      for (int j = 0; j < 4; ++j) {
+        st[b][j] *= a.scale_log2;
+        mx = fmaxf(mx, st[b][j]);
+        mn = fminf(mn, st[b][j]);
+      }
+  } else {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int key = key0 + chunk_key(b, grp * 4 + j);
+        const bool ok = c.valid && key >= c.cs && key <= c.pos;
+        st[b][j] = ok ? st[b][j] * a.scale_log2 : -INFINITY;
+        mx = fmaxf(mx, st[b][j]);
+      }
+    mn = -INFINITY;
+  }
   auto larger = [](float x, float y) { return fmaxf(x, y); };
   auto plus = [](float x, float y) { return x + y; };
   mx = combine_x32(combine_x16(mx, larger), larger);
   float ls = 0.f;
+  if (__builtin_amdgcn_ballot_w64(!(mn <= mx && mn - mx >= -126.f)) == 0) {
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < 4; ++b) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) st[b][j] = mx == -INFINITY ? 0.f : exp2f(st[b][j] - mx);
-    ls += (st[b][0] + st[b][1]) + (st[b][2] + st[b][3]);
+      for (int j = 0; j < 4; ++j) st[b][j] = __builtin_amdgcn_exp2f(st[b][j] - mx);
+      ls += (st[b][0] + st[b][1]) + (st[b][2] + st[b][3]);
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) st[b][j] = mx == -INFINITY ? 0.f : exp2f(st[b][j] - mx);
+      ls += (st[b][0] + st[b][1]) + (st[b][2] + st[b][3]);
+    }
   }
   ls = combine_x32(combine_x16(ls, plus), plus);
   m = mx;
   l = ls;
+}
+
+// The probabilities of four keys as BF16, round to nearest even.
+__device__ __forceinline__ v4s prob_bf16(const v4f& p) {
+  typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(v4s, __builtin_convertvector(p, v4bf));
 }
 
 // One chunk partial for the 16 columns of this wave.
@@ -1259,12 +1296,10 @@ __device__ __forceinline__ ChunkState chunk_partial(const AttnArgs& a, const Att
           st[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, kf[b][s]),
                                                           q.b[s], st[b], 0, 0, 0);
     }
-    chunk_softmax(st, a, c, key0, grp, r.m, r.l);
+    chunk_softmax(st, a, c, key0, grp, chunk_inside(it, a.Hq / a.Hk, key0), r.m, r.l);
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      v4s pb;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) pb[j] = short(f2bf(st[b][j]));
+      const v4s pb = prob_bf16(st[b]);
 #pragma unroll
       for (int hb = 0; hb < HDMAX / 16; ++hb)
         if (hb < nhb) {
@@ -1310,7 +1345,7 @@ __device__ __forceinline__ ChunkState chunk_partial(const AttnArgs& a, const Att
 #pragma unroll
       for (int b = 0; b < 4; ++b)
         st[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[b][s >> 2][s & 3], q.f[s], st[b], 0, 0, 0);
-    chunk_softmax(st, a, c, key0, grp, r.m, r.l);
+    chunk_softmax(st, a, c, key0, grp, chunk_inside(it, a.Hq / a.Hk, key0), r.m, r.l);
     // the four hd blocks' P*V chains interleaved step by step (same order per chain)
 #pragma unroll
     for (int b = 0; b < 4; ++b)
@@ -1335,18 +1370,9 @@ __device__ __forceinline__ AttnCol attn_col(const AttnArgs& a, const AttnItem& i
   c.head = it.kvh * g + cc % g;
   c.pos = it.pos_base + qo;
   c.row = it.row_base + qo;
-  c.cs = window_start(c.pos, a.ctx_len, a.slide);
+  c.cs = it.cs_lo;
+  if (it.cs_lo != it.cs_hi) c.cs = window_start(c.pos, a.ctx_len, a.slide);
   return c;
-}
-
-// absolute chunk range [c_lo, c_hi] of an item
-__device__ __forceinline__ void item_chunks(const AttnArgs& a, const AttnItem& it, int& c_lo,
-                                            int& c_hi) {
-  const int g = a.Hq / a.Hk;
-  const int kmin = window_start(it.pos_base + it.c0 / g, a.ctx_len, a.slide);
-  const int kmax = it.pos_base + (it.c0 + it.ncols - 1) / g;
-  c_lo = kmin / KCH;
-  c_hi = kmax / KCH;
 }
 
 template <int PO>
@@ -1378,37 +1404,197 @@ __device__ __forceinline__ float attn_store(const AttnArgs& a, const AttnItem& i
   return omax;
 }
 
-// Many items (prefill): one wave per item, the three fold levels in registers.
-template <int PA, int PO>
-__global__ __launch_bounds__(256) void attention_seq_kernel(const AttnArgs a) {
-  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= a.n_items) return;
+// Groups of up to 4 consecutive items of one stream's kv head (several rows of a stream: prompts and
+// encode): a workgroup stages each K and V^T chunk of their windows in LDS once, and each wave takes
+// one item.  In the MFMA layouts a load asks for 16 bytes of each of 16 to 64 cache lines, one line a
+// cycle, for each item again; staged, the rows come whole and once.  LDS holds K rows of hd entries
+// and V^T rows of 64 keys in units of 16 bytes, XORed with the row so that the 16 rows of a fragment
+// read fall on different banks; the next chunk's units are in registers while this one is computed.
+// Every item folds its own chunks in the order of the other kernels, so the bits are theirs.  Full
+// shape, 512 rows of one FP32 stream: 67.8 us a layer (a wave per chunk, K and V for itself) to 37
+// (the FP32 matrix rate alone is 16); 32,768 rows of 64 BF16 streams: 177 to 81, bound by the
+// softmax's vector instructions.
+//  * kQuads (too few items to fill the chip with one wave each): a workgroup per (group, quad), the
+//    quads' states to the fold kernel as in attention_quad_kernel;
+//  * otherwise a workgroup per group runs over all its chunks, the three fold levels in registers.
+// Units of work are placed as in attention_quad_kernel, so that a stream's groups read one L2.
+constexpr int GI = 4;  // items of a group
+
+template <int PA, int PO, bool kQuads, bool kFull>
+__global__ __launch_bounds__(256) void attention_group_kernel(const AttnArgs a) {
+  constexpr int ES = PA == P_BF16 ? 2 : 4;
+  constexpr int U = KCH * ES / 16;     // 16-byte units of a row (64 hd entries or 64 keys)
+  constexpr int E = KCH * U / 256;     // units of K, and of V^T, that a thread stages
+  constexpr int NBUF = PA == P_BF16 ? 2 : 1;
+  __shared__ v4i s_kv[NBUF][2][KCH * U];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 15, grp = lane >> 4;
+  const int nu = gridDim.x, q8 = nu / 8, r8 = nu % 8, xcd = blockIdx.x % 8;
+  const int u = xcd * q8 + min(xcd, r8) + int(blockIdx.x) / 8;
+  const int gi = kQuads ? u % a.n_groups : u, qi = kQuads ? u / a.n_groups : 0;
+  const int gw = __builtin_amdgcn_readfirstlane(a.items[gi].group);
+  const int first = gw >> 2, last = first + (gw & 3);
+  int lo = a.items[first].c_lo, hi = a.items[last].c_hi;  // positions do not decrease
+  const int slot_lo = a.items[first].slot_lo;
+  const int item = __builtin_amdgcn_readfirstlane(min(first + wave, last));
+  const bool mine = first + wave <= last;
   const AttnItem it = a.items[item];
+  const int hd = kFull ? HDMAX : a.hd, nhb = hd / 16, g = a.Hq / a.Hk;
+  int base = slot_lo;
+  if constexpr (kQuads) {
+    const int q0 = (lo / QCH + qi) * QCH, c_first = lo;
+    lo = max(lo, q0);
+    hi = min(hi, q0 + QCH - 1);
+    if (lo > hi) return;
+    base += (lo - c_first) * KCH;
+    while (base >= a.ring) base -= a.ring;
+  }
   const AttnCol c = attn_col(a, it, col);
-  const int nhb = a.hd / 16;
   QFrag<PA> q;
   load_q<PA>(q, a, c, grp);
-  int c_lo, c_hi;
-  item_chunks(a, it, c_lo, c_hi);
+  const long long sbase = (long long)it.stream * a.kv_stride + (long long)it.kvh * a.ring * hd;
+  const char* Kc = static_cast<const char*>(a.k_cache) + sbase * ES;
+  const char* Vt = static_cast<const char*>(a.vt_cache) + sbase * ES;
+  constexpr int EPU = 16 / ES;  // entries of a unit
+  // the rows' XORs: the 16 K rows of a fragment are 16 (col / 4) + col % 4 (+ 4 b), the 16 V^T rows
+  // col (+ 16 hb); a BF16 row fills half the banks, so a row's lowest bit chooses the half
+  auto kx = [](int r) {
+    return PA == P_BF16 ? ((r >> 1) & 1) | ((r >> 3) & 6) : (r & 3) | ((r >> 2) & 12);
+  };
+  auto vx = [](int r) { return PA == P_BF16 ? (r >> 1) & 7 : r & 15; };
+  v4i kr[E], vr[E];
+  auto fetch = [&]() {  // the chunk at ring slot base (loads clamped into the head's rows)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + 256 * e, r = i / U, un = i % U;
+      int ks = base + r;
+      ks = ks >= a.ring ? ks - a.ring : ks;
+      const int k = kFull ? un * EPU : min(un * EPU, hd - EPU);
+      const v4i v = *reinterpret_cast<const v4i*>(Kc + ((long long)ks * hd + k) * ES);
+      kr[e] = kFull || un * EPU < hd ? v : v4i{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + 256 * e, r = i / U, un = i % U;
+      int vs = base + un * EPU;  // never wraps inside a unit: ring and chunk starts are 16 n
+      vs = vs >= a.ring ? vs - a.ring : vs;
+      const int d = kFull ? r : min(r, hd - 1);
+      const v4i v = *reinterpret_cast<const v4i*>(Vt + ((long long)d * a.ring + vs) * ES);
+      vr[e] = kFull || r < hd ? v : v4i{0, 0, 0, 0};
+    }
+  };
   ChunkState run, gs, qs;
   state_empty(run);
-  constexpr int GCH = QCH * GQ;
-  for (int g0 = (c_lo / GCH) * GCH; g0 <= c_hi; g0 += GCH) {
-    state_empty(gs);
-    for (int q0 = g0; q0 < g0 + GCH; q0 += QCH) {
-      if (q0 + QCH - 1 < c_lo || q0 > c_hi) continue;
-      state_empty(qs);
-      for (int ch = max(q0, c_lo); ch <= min(q0 + QCH - 1, c_hi); ++ch)
-        fold(qs, chunk_partial<PA>(a, it, c, q, ch, col, grp), nhb);
-      fold(gs, qs, nhb);
+  state_empty(gs);
+  state_empty(qs);
+  const int i_lo = mine ? it.c_lo : hi + 1, i_hi = it.c_hi;
+  fetch();
+  for (int ch = lo; ch <= hi; ++ch) {
+    v4i(*kv)[KCH * U] = s_kv[NBUF == 2 ? ch & 1 : 0];
+    if (NBUF == 1 && ch > lo) __syncthreads();  // the chunk before has been read
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid + 256 * e, r = i / U, un = i % U;
+      kv[0][r * U + (un ^ kx(r))] = kr[e];
+      kv[1][r * U + (un ^ vx(r))] = vr[e];
     }
-    fold(run, gs, nhb);
+    __syncthreads();
+    if (ch < hi) {
+      base += KCH;
+      base = base >= a.ring ? base - a.ring : base;
+      fetch();
+    }
+    if (ch < i_lo || ch > i_hi) continue;
+    const int key0 = ch * KCH;
+    const int krow = (col >> 2) * 16 + (col & 3), kxr = kx(krow), vxr = vx(col);
+    v4f st[4];
+    ChunkState r;
+#pragma unroll
+    for (int hb = 0; hb < HDMAX / 16; ++hb) r.o[hb] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) st[b] = v4f{0.f, 0.f, 0.f, 0.f};
+    if constexpr (PA == P_BF16) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (kFull || s * 32 < hd)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            st[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(v8bf, kv[0][(krow + 4 * b) * U + ((4 * s + grp) ^ kxr)]),
+                q.b[s], st[b], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        v4f kf[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          kf[b] = __builtin_bit_cast(v4f, kv[0][(krow + 4 * b) * U + ((4 * grp + qd) ^ kxr)]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            st[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[b][e], q.f[4 * qd + e], st[b], 0, 0, 0);
+      }
+    }
+    chunk_softmax(st, a, c, key0, grp, chunk_inside(it, g, key0), r.m, r.l);
+    if constexpr (PA == P_BF16) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        v4i vf[HDMAX / 16];
+#pragma unroll
+        for (int hb = 0; hb < HDMAX / 16; ++hb)
+          vf[hb] = kv[1][(hb * 16 + col) * U + ((2 * grp + h) ^ vxr)];
+#pragma unroll
+        for (int b = 2 * h; b < 2 * h + 2; ++b) {
+          const v4s pb = prob_bf16(st[b]);
+#pragma unroll
+          for (int hb = 0; hb < HDMAX / 16; ++hb)
+            if (hb < nhb) {
+              const v4i w = vf[hb];
+              const v4s va =
+                  __builtin_bit_cast(v4s, (b & 1) ? int2{w[2], w[3]} : int2{w[0], w[1]});
+              r.o[hb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, pb, r.o[hb], 0, 0, 0);
+            }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        v4f vf[HDMAX / 16];
+#pragma unroll
+        for (int hb = 0; hb < HDMAX / 16; ++hb)
+          vf[hb] = __builtin_bit_cast(v4f, kv[1][(hb * 16 + col) * U + ((4 * grp + b) ^ vxr)]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int hb = 0; hb < HDMAX / 16; ++hb)
+            if (hb < nhb)
+              r.o[hb] =
+                  __builtin_amdgcn_mfma_f32_16x16x4f32(vf[hb][j], st[b][j], r.o[hb], 0, 0, 0);
+      }
+    }
+    fold(qs, r, nhb);
+    if constexpr (!kQuads) {
+      if (ch % QCH == QCH - 1 || ch == i_hi) {
+        fold(gs, qs, nhb);
+        state_empty(qs);
+        if (ch % (QCH * GQ) == QCH * GQ - 1 || ch == i_hi) {
+          fold(run, gs, nhb);
+          state_empty(gs);
+        }
+      }
+    }
   }
-  float omax = attn_store<PO>(a, it, run, col, grp);
-  if (a.out_amax) {
-    omax = wave_max_f(omax);
-    if (lane == 0) atomic_max_abs(a.out_amax, omax);
+  if (!mine) return;
+  if constexpr (kQuads) {
+    if (hi < i_lo || lo > i_hi) return;
+    state_put(a.ws + ((long long)item * MAXQ + lo / QCH - i_lo / QCH) * QSTATE * 64, qs, lane);
+  } else {
+    float omax = attn_store<PO>(a, it, run, col, grp);
+    if (a.out_amax) {
+      omax = wave_max_f(omax);
+      if (lane == 0) atomic_max_abs(a.out_amax, omax);
+    }
   }
 }
 
@@ -1433,8 +1619,7 @@ __global__ __launch_bounds__(256) void attention_quad_kernel(const AttnArgs a) {
     qi = u / a.n_items;
   }
   const AttnItem it = a.items[item];
-  int c_lo, c_hi;
-  item_chunks(a, it, c_lo, c_hi);
+  const int c_lo = it.c_lo, c_hi = it.c_hi;
   const int q0 = (c_lo / QCH + qi) * QCH;
   if (q0 > c_hi) return;  // beyond the item: its fold never reads this quad
   const AttnCol c = attn_col(a, it, col);
@@ -1471,8 +1656,7 @@ __global__ __launch_bounds__(64 * FOLD_WAVES) void attention_fold_kernel(const A
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15, grp = lane >> 4;
   const int item = blockIdx.x, hb = blockIdx.y;
   const AttnItem it = a.items[item];
-  int c_lo, c_hi;
-  item_chunks(a, it, c_lo, c_hi);
+  const int c_lo = it.c_lo, c_hi = it.c_hi;
   const int qlo = c_lo / QCH, qhi = c_hi / QCH;
   const int gfirst = (qlo / GQ) * GQ;
   const int ng = (qhi - gfirst) / GQ + 1;  // <= FOLD_WAVES: qhi - qlo < MAXQ
@@ -1570,8 +1754,7 @@ __global__ __launch_bounds__(256) void attention_chunk_kernel(const AttnArgs a) 
   const int cw = blockIdx.x % QCH, rest = blockIdx.x / QCH;
   const int item = rest % a.n_items, qi = rest / a.n_items;
   const AttnItem it = a.items[item];
-  int c_lo, c_hi;
-  item_chunks(a, it, c_lo, c_hi);
+  const int c_lo = it.c_lo, c_hi = it.c_hi;
   const int q0 = (c_lo / QCH + qi) * QCH, ch = q0 + cw;
   if (ch < c_lo || ch > c_hi) return;  // not a chunk of the item (never counted)
   const AttnCol c = attn_col(a, it, col);
@@ -1622,7 +1805,7 @@ __global__ __launch_bounds__(256) void attention_chunk_kernel(const AttnArgs a) 
     for (int j = 0; j < 4; ++j) st[b][j] = s_st[b][j][lane];
   ChunkState r;
   state_empty(r);
-  chunk_softmax(st, a, c, key0, grp, r.m, r.l);
+  chunk_softmax(st, a, c, key0, grp, chunk_inside(it, a.Hq / a.Hk, key0), r.m, r.l);
   if (w < nhb) {
 #pragma unroll
     for (int b = 0; b < 4; ++b)
@@ -1904,28 +2087,38 @@ void launch_gemm(int prec, int amode, int epi, const GemmArgs& a, hipStream_t s,
   NC_HIP(hipGetLastError());
 }
 
-// Quads an item can span: its keys run from the window start of its first query to its last
-// query, at most ctx_len + 15 keys (a window holds at most ctx_len keys, an item at most 16
-// query positions), i.e. at most nch chunks at any alignment.
-static int attention_quads(int ctx_len) {
-  const int nch = (ctx_len + 15 + KCH - 1) / KCH + 1;
+// Quads that consecutive items of one stream can span: their keys run from the window start of the
+// first query to the last query, at most ctx_len + 16 items - 1 keys (a window holds at most
+// ctx_len keys, an item at most 16 query positions), i.e. at most nch chunks at any alignment.
+static int attention_quads(int ctx_len, int items = 1) {
+  const int nch = (ctx_len + 16 * items - 1 + KCH - 1) / KCH + 1;
   return (nch - 1 + QCH - 1) / QCH + 1;
 }
 
 template <int PA, int PO>
 static void attn_go(const AttnArgs& a, bool parallel, hipStream_t s) {
+  // shared staging needs 2 items a group to pay (FP32, 64 streams of 4 and 6 rows: one item a group 15.7 us
+  // alone and 23.5 grouped, two 36.6 and 28.2), and work for the chip (BF16, one stream of 32 and 43
+  // rows: 18 items 13.7 and 14.7, 27 items 15.1 and 14.3)
+  const bool grouped = a.n_items > kChunkItems && a.n_items >= 2 * a.n_groups;
   if (parallel) {
-    const int nq = attention_quads(a.ctx_len);
+    const int nq = std::min(a.quads, attention_quads(a.ctx_len));
     if (PA == P_F32 && a.ctr && a.n_items <= kChunkItems) {
       hipLaunchKernelGGL(attention_chunk_kernel, dim3(a.n_items * nq * QCH), dim3(256), 0, s, a);
+    } else if (grouped) {
+      hipLaunchKernelGGL((a.hd == HDMAX ? attention_group_kernel<PA, PO, true, true>
+                                        : attention_group_kernel<PA, PO, true, false>),
+                         dim3(a.n_groups * std::min(a.quads, attention_quads(a.ctx_len, GI))),
+                         dim3(256), 0, s, a);
     } else {
       hipLaunchKernelGGL((attention_quad_kernel<PA>), dim3(a.n_items * nq), dim3(256), 0, s, a);
     }
     hipLaunchKernelGGL((attention_fold_kernel<PO>), dim3(a.n_items, a.hd / 16),
                        dim3(64 * FOLD_WAVES), 0, s, a);
   } else {
-    hipLaunchKernelGGL((attention_seq_kernel<PA, PO>), dim3((a.n_items + 3) / 4), dim3(256), 0, s,
-                       a);
+    hipLaunchKernelGGL((a.hd == HDMAX ? attention_group_kernel<PA, PO, false, true>
+                                      : attention_group_kernel<PA, PO, false, false>),
+                       dim3(a.n_groups), dim3(256), 0, s, a);
   }
 }
 
@@ -1945,6 +2138,7 @@ void launch_attention(int prec_att, int prec_out, const AttnArgs& a, bool parall
   NC_CHECK(a.hd % 16 == 0 && a.hd <= HDMAX, NC_E_INVALID, "head_dim must be 16..64, x16");
   NC_CHECK(attention_quads(a.ctx_len) <= MAXQ, NC_E_INVALID, "context window too large");
   NC_CHECK(a.ring % 16 == 0, NC_E_INVALID, "ring must be a multiple of 16");
+  NC_CHECK(a.n_groups > 0 && a.n_groups <= a.n_items, NC_E_INVALID, "attention groups");
   if (parallel)
     NC_CHECK(a.ws && a.ws_bytes >= attention_ws_bytes(a.n_items), NC_E_INVALID,
              "attention workspace too small");

@@ -59,6 +59,8 @@ struct GemmArgs {
 // Attention work item: a block of up to 16 (query, head) columns of one stream and kv head.
 // Column c maps to global column cc = c0 + c, query row row_base + cc / g and head
 // kvh * g + cc % g, with g = Hq / Hkv.
+constexpr int kAttnChunk = 64;  // keys of an attention chunk
+
 struct AttnItem {
   int32_t stream;
   int32_t kvh;
@@ -66,7 +68,10 @@ struct AttnItem {
   int32_t pos_base;
   int32_t c0;
   int32_t ncols;
-  int32_t pad[2];
+  int32_t c_lo, c_hi;    // 64-key chunks [c_lo, c_hi] of the columns' windows
+  int32_t slot_lo;       // ring slot of chunk c_lo's first key
+  int32_t cs_lo, cs_hi;  // window starts of the first and the last column
+  int32_t group;         // of the group with this entry's index: 4 * its first item + its items - 1
 };
 
 struct AttnArgs {
@@ -83,6 +88,10 @@ struct AttnArgs {
   float scale_log2;     // log2(e) / sqrt(hd)
   float* ws;            // group states of the parallel path
   size_t ws_bytes;
+  // groups of up to 4 consecutive items of one stream's kv head, in AttnItem::group of entries
+  // 0 .. n_groups - 1
+  int n_groups;
+  int quads;            // quads (4 chunks) that a group spans at most
   int xcd_place;        // parallel path: items share a stream's K/V; place them XCD-aware
   int* ctr;             // parallel path, optional: attention_counters(n_items) counters, zero
                         // between launches (given: few FP32 items run one workgroup per chunk)

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <numeric>
@@ -181,12 +182,13 @@ struct nc_ctx {
   // captured transformer passes of the decode / probe paths, by pass shape; every buffer a pass
   // reads or writes is part of the key, so a reallocation selects (and captures) a new graph
   struct GraphKey {
-    int n, n_items, n_last;
+    int n, n_items, n_groups, quads, n_last;
     size_t off_rows, off_items, off_last;
     std::array<const void*, 12> bufs;
     bool operator<(const GraphKey& o) const {
-      return std::tie(n, n_items, n_last, off_rows, off_items, off_last, bufs) <
-             std::tie(o.n, o.n_items, o.n_last, o.off_rows, o.off_items, o.off_last, o.bufs);
+      return std::tie(n, n_items, n_groups, quads, n_last, off_rows, off_items, off_last, bufs) <
+             std::tie(o.n, o.n_items, o.n_groups, o.quads, o.n_last, o.off_rows, o.off_items,
+                      o.off_last, o.bufs);
     }
   };
   std::map<GraphKey, hipGraphExec_t> graphs;
@@ -493,6 +495,8 @@ struct PassPlan {
   std::vector<RowMeta> rows;
   std::vector<AttnItem> items;
   std::vector<int32_t> last;  // n_last source rows, then n_last destination streams
+  int n_groups = 0;           // attention groups (AttnItem::group)
+  int quads = 0;              // quads that a group spans, rounded up
   double attn_bytes = 0, attn_flops = 0;
   bool shared_kv = false;     // some stream's kv head has several attention items
   size_t off_rows = 0, off_items = 0, off_last = 0;
@@ -509,7 +513,7 @@ PassPlan plan_pass(nc_ctx* c, std::vector<RowMeta> rows, bool calib = false) {
   auto wstart = [&](int q) { return q < L ? 0 : C * (1 + (q - L) / C); };
   const double esa = double(prec_bytes(calib ? P_F32 : c->att));
   const double eso = double(prec_bytes(calib ? P_F32 : c->prec));
-  std::vector<int32_t> src, dst;
+  std::vector<int32_t> src, dst, groups;
   for (int i = 0; i < n;) {
     int j = i;
     while (j + 1 < n && R[j + 1].stream == R[i].stream && R[j + 1].pos == R[j].pos + 1) ++j;
@@ -524,6 +528,14 @@ PassPlan plan_pass(nc_ctx* c, std::vector<RowMeta> rows, bool calib = false) {
         it.pos_base = R[i].pos;
         it.c0 = c0;
         it.ncols = std::min(16, nq * g - c0);
+        const int pa = it.pos_base + c0 / g, pb = it.pos_base + (c0 + it.ncols - 1) / g;
+        it.cs_lo = wstart(pa);
+        it.cs_hi = wstart(pb);
+        it.c_lo = it.cs_lo / kAttnChunk;
+        it.c_hi = pb / kAttnChunk;
+        it.slot_lo = it.c_lo * kAttnChunk % c->R;
+        if (c0 / 16 % 4 == 0) groups.push_back(4 * int(p.items.size()) - 1);
+        ++groups.back();
         p.items.push_back(it);
         for (int cc = 0; cc < it.ncols; ++cc) {
           const int q = it.pos_base + (it.c0 + cc) / g;
@@ -538,6 +550,17 @@ PassPlan plan_pass(nc_ctx* c, std::vector<RowMeta> rows, bool calib = false) {
     dst.push_back(R[j].stream);
     i = j + 1;
   }
+  p.n_groups = int(groups.size());
+  for (int k = 0; k < p.n_groups; ++k) {
+    p.items[k].group = groups[k];
+    const int first = groups[k] >> 2, lo = p.items[first].c_lo / 4,
+              hi = p.items[first + (groups[k] & 3)].c_hi / 4;
+    p.quads = std::max(p.quads, hi - lo + 1);
+  }
+  // the attention grid holds a workgroup for each quad an item may have: as many as the pass's
+  // longest window has, in three steps (each has graphs of its own).  Ten of them for windows of one
+  // quad took 100 us of attention a layer where 64 FP32 streams have 22 rows each, one takes 20.
+  p.quads = p.quads <= 1 ? 1 : p.quads <= 4 ? 4 : INT_MAX;
   p.last = src;
   p.last.insert(p.last.end(), dst.begin(), dst.end());
   return p;
@@ -725,6 +748,8 @@ void pass_launches(nc_ctx* c, const PassPlan& p, const uint8_t* dstage, BodyOpts
     AttnArgs t{};
     t.items = ditems;
     t.n_items = int(p.items.size());
+    t.n_groups = p.n_groups;
+    t.quads = p.quads;
     t.q = c->qb.p;
     t.k_cache = a.k_cache;
     t.vt_cache = a.vt_cache;
@@ -812,7 +837,7 @@ void run_pass(nc_ctx* c, const PassPlan& p, const uint8_t* dstage, BodyOpts o = 
     pass_launches(c, p, dstage, o);
     return;
   }
-  nc_ctx::GraphKey k{n,          int(p.items.size()), int(p.last.size()),
+  nc_ctx::GraphKey k{n,          int(p.items.size()), p.n_groups, p.quads, int(p.last.size()),
                      p.off_rows, p.off_items,         p.off_last,
                      {dstage, c->x.p, c->xinv.p, c->xss.p, c->yb.p, c->qb.p, c->ob.p, c->hb.p,
                       c->aws.p, c->kc.p, c->hlast.p, c->hinv.p}};
