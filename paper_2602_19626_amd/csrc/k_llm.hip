@@ -1723,74 +1723,77 @@ __global__ __launch_bounds__(64 * FOLD_WAVES) void attention_fold_kernel(const A
   }
 }
 
-// ---- small kernels ------------------------------------------------------------------------
-
-// x[r] = E[tok]; one wave per row, which also writes the row's inverse RMS (row_inv_rms order).
-// x[r] = E[tok], the block sums of squares of the row, and y[r] = quantise(x[r] * gain)
-// Few items, FP32 (decode): the quad kernel's work spread over four workgroups per quad, so that
-// each chunk's MFMA chains run on four SIMDs instead of one.  Workgroup (item, quad, chunk):
-// wave w runs the score chain of key block w, the four blocks' scores meet in LDS, every wave
-// takes the chunk's softmax (the same code, the same bits), and wave w runs the P*V chain of
-// head-dimension block w.  The chunk state is published at device scope: each store is written
-// through to the device's coherence point, every wave waits until its stores are acknowledged
-// (s_waitcnt 0), and after a barrier one thread counts the chunk in with a device-scope atomic.
-// The workgroup that brings the count to the quad's number of chunks reads the quad's chunk
-// states from that point, folds them in order (as the quad kernel does, hd block w in wave w),
-// stores the quad state for the fold kernel and resets the count to zero for the next launch.
-// No thread waits for another workgroup, so the launch always drains.
+// Few items, FP32 (decode): the quad kernel's work spread over a workgroup per chunk, so that each
+// chunk's MFMA chains run on four SIMDs instead of one.  Wave w runs the score chain of key
+// block w, the four blocks' scores meet in LDS, every wave takes the chunk's softmax (the same
+// code, the same bits), and wave w runs the P*V chain of head-dimension block w.  A wave's 16 K rows
+// and 16 V^T rows arrive as whole rows, 1 KB an instruction (in the MFMA layout an instruction asks for
+// 16 bytes of each of 64 lines, and the vector cache takes a line a cycle), and turn in LDS of the
+// wave's own, their 16-byte units XORed with the row.  The chunk states go to memory for
+// attention_chunk_fold_kernel: handed over inside this kernel instead, by device-scope stores and a
+// counter a quad, they cost two more round trips to the coherence point than a wider fold costs.  One
+// FP32 row after 1,200 tokens, both kernels: 13.4 us a layer with the handover, 12.1 without; the
+// chain is the bound (item, K and V, 16 + 16 dependent MFMAs, states, folds), not the 5 MB of keys.
 constexpr int kChunkItems = 24;  // largest item count of the chunk-parallel path
 constexpr int CST = 6;           // floats per lane of one wave's chunk state: m, l, o[4]
 
 __device__ __forceinline__ float* chunk_slot(const AttnArgs& a, int item, int qi, int cw, int w) {
-  float* base = a.ws + (size_t)a.n_items * MAXQ * QSTATE * 64;  // after the quad states
-  return base + ((((size_t)item * MAXQ + qi) * QCH + cw) * 4 + w) * CST * 64;
+  return a.ws + ((((size_t)item * MAXQ + qi) * QCH + cw) * 4 + w) * CST * 64;
 }
 
 __global__ __launch_bounds__(256) void attention_chunk_kernel(const AttnArgs a) {
-  __shared__ float s_st[4][4][64];  // scores [key block][element][lane]
-  __shared__ int s_last;
+  __shared__ v4f s_kv[4][2][16 * 16];  // [wave][K, V^T][row * 16 + (unit ^ row)]
+  __shared__ float s_st[4][4][64];     // scores [key block][element][lane]
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int col = lane & 15, grp = lane >> 4;
-  const int cw = blockIdx.x % QCH, rest = blockIdx.x / QCH;
-  const int item = rest % a.n_items, qi = rest / a.n_items;
+  const int cw = blockIdx.x, item = blockIdx.y, qi = blockIdx.z;
   const AttnItem it = a.items[item];
-  const int c_lo = it.c_lo, c_hi = it.c_hi;
-  const int q0 = (c_lo / QCH + qi) * QCH, ch = q0 + cw;
-  if (ch < c_lo || ch > c_hi) return;  // not a chunk of the item (never counted)
-  const AttnCol c = attn_col(a, it, col);
-  const int hd = a.hd, nhb = hd / 16;
-  QFrag<P_F32> q;
-  load_q<P_F32>(q, a, c, grp);
+  const int q0 = (it.c_lo / QCH + qi) * QCH, ch = q0 + cw;
+  if (ch < it.c_lo || ch > it.c_hi) return;  // not a chunk of the item (the fold skips it)
+  const int hd = a.hd, nhb = hd / 16, g = a.Hq / a.Hk;
   const float* Kc = static_cast<const float*>(a.k_cache);
   const float* Vt = static_cast<const float*>(a.vt_cache);
   const long long sbase = (long long)it.stream * a.kv_stride + (long long)it.kvh * a.ring * hd;
   const int key0 = ch * KCH;
-  const int base = key0 % a.ring;
-  auto slot_of = [&](int off) {
-    const int t = base + off;
-    return t >= a.ring ? t - a.ring : t;
-  };
-  const int vslot = slot_of(16 * grp);
-  // key block w's K fragment and head-dimension block w's V^T fragment (loads clamped into
-  // range and masked afterwards, as in chunk_partial)
-  v4f kf[4], vf[4];
+  int base = it.slot_lo + (ch - it.c_lo) * KCH;
+  while (base >= a.ring) base -= a.ring;
+  // row 4 e + grp of the wave's K and V^T rows, unit col (loads clamped into the head's rows and
+  // masked afterwards, as in chunk_partial): key chunk_key(w, row), head entry 16 w + row
+  v4f kr[4], vr[4];
   {
-    const long long ks = sbase + (long long)slot_of(chunk_key(w, col)) * hd;
+    const int kc = min(4 * col, hd - 4);
+    int vs = base + 4 * col;
+    vs = vs >= a.ring ? vs - a.ring : vs;
 #pragma unroll
-    for (int qd = 0; qd < 4; ++qd) {
-      const int k = 16 * grp + 4 * qd;
-      const v4f v = *reinterpret_cast<const v4f*>(Kc + ks + min(k, hd - 4));
-      kf[qd] = k < hd ? v : v4f{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 4; ++e) {
+      int ks = base + 16 * e + 4 * w + grp;
+      ks = ks >= a.ring ? ks - a.ring : ks;
+      kr[e] = *reinterpret_cast<const v4f*>(Kc + sbase + (long long)ks * hd + kc);
     }
-    const int hc = min(w, nhb - 1);
+    const int d0 = 16 * min(w, nhb - 1) + grp;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const v4f v = *reinterpret_cast<const v4f*>(Vt + sbase + (long long)(hc * 16 + col) * a.ring +
-                                                  vslot + 4 * b);
-      vf[b] = w < nhb ? v : v4f{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int e = 0; e < 4; ++e)
+      vr[e] = *reinterpret_cast<const v4f*>(Vt + sbase + (long long)(d0 + 4 * e) * a.ring + vs);
   }
-  __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first MFMA
+  const AttnCol c = attn_col(a, it, col);
+  QFrag<P_F32> q;
+  load_q<P_F32>(q, a, c, grp);
+  __builtin_amdgcn_sched_barrier(0);  // every load above is issued before the first use
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int r = 4 * e + grp;
+    s_kv[w][0][r * 16 + (col ^ r)] = 4 * col < hd ? kr[e] : zero;
+    s_kv[w][1][r * 16 + (col ^ r)] = w < nhb ? vr[e] : zero;
+  }
+  // the wave reads what its own lanes wrote: LDS serves a wave's accesses in order
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  v4f kf[4], vf[4];
+#pragma unroll
+  for (int qd = 0; qd < 4; ++qd) kf[qd] = s_kv[w][0][col * 16 + ((4 * grp + qd) ^ col)];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) vf[b] = s_kv[w][1][col * 16 + ((4 * grp + b) ^ col)];
   v4f sw = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < HDMAX / 4; ++s)
@@ -1805,65 +1808,100 @@ __global__ __launch_bounds__(256) void attention_chunk_kernel(const AttnArgs a) 
     for (int j = 0; j < 4; ++j) st[b][j] = s_st[b][j][lane];
   ChunkState r;
   state_empty(r);
-  chunk_softmax(st, a, c, key0, grp, chunk_inside(it, a.Hq / a.Hk, key0), r.m, r.l);
-  if (w < nhb) {
+  chunk_softmax(st, a, c, key0, grp, chunk_inside(it, g, key0), r.m, r.l);
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+  for (int b = 0; b < 4; ++b)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        r.o[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[b][j], st[b][j], r.o[0], 0, 0, 0);
+    for (int j = 0; j < 4; ++j)
+      r.o[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[b][j], st[b][j], r.o[0], 0, 0, 0);
+  float* dst = chunk_slot(a, item, qi, cw, w) + lane;
+  dst[0] = r.m;
+  dst[64] = r.l;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) dst[(2 + j) * 64] = r.o[0][j];
+}
+
+// The chunk kernel's states -> quads -> groups -> output, one workgroup per (item, head-dimension
+// block hb).  Wave w folds the chunks of the item's w-th quad (their states loaded together), the
+// first waves then fold the quads of a group each and wave 0 the groups: the other kernels' folds
+// in their order.
+__global__ __launch_bounds__(64 * MAXQ) void attention_chunk_fold_kernel(const AttnArgs a) {
+  __shared__ float qst[MAXQ][CST * 64];
+  __shared__ float gst[FOLD_WAVES][CST * 64];
+  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int item = blockIdx.x, hb = blockIdx.y;
+  const AttnItem it = a.items[item];
+  const int qlo = it.c_lo / QCH, qhi = it.c_hi / QCH, gfirst = (qlo / GQ) * GQ;
+  const int ng = (qhi - gfirst) / GQ + 1;  // <= FOLD_WAVES: qhi - qlo < MAXQ
+  auto get = [&](ChunkState& st, const float* p) {
+    st.m = p[lane];
+    st.l = p[64 + lane];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) st.o[0][j] = p[(2 + j) * 64 + lane];
+  };
+  auto put = [&](float* p, const ChunkState& st) {
+    p[lane] = st.m;
+    p[64 + lane] = st.l;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) p[(2 + j) * 64 + lane] = st.o[0][j];
+  };
+  if (qlo + w <= qhi) {
+    const int q0 = (qlo + w) * QCH;
+    ChunkState qs, p[QCH];
+    // (a slot outside the item is inside the workspace, and is not folded)
+#pragma unroll
+    for (int k = 0; k < QCH; ++k) get(p[k], chunk_slot(a, item, w, k, hb));
+    state_empty(qs);
+#pragma unroll
+    for (int k = 0; k < QCH; ++k)
+      if (q0 + k >= it.c_lo && q0 + k <= it.c_hi) fold(qs, p[k], 1);
+    put(qst[w], qs);
   }
-  // publish this wave's part of the chunk state
-  {
-    float* dst = chunk_slot(a, item, qi, cw, w);
-    auto put = [&](int i, float v) {
-      __hip_atomic_store(dst + i * 64 + lane, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    put(0, r.m);
-    put(1, r.l);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) put(2 + j, r.o[0][j]);
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // this wave's device-scope stores are acknowledged
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nv = min(q0 + QCH - 1, c_hi) - max(q0, c_lo) + 1;  // the quad's chunks
-    const int old = __hip_atomic_fetch_add(a.ctr + item * MAXQ + qi, 1, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-    s_last = old == nv - 1;
+  // waves 0 .. ng - 1 exist: an item of one quad has one group, of q quads at most q
+  ChunkState run, gs;
+  state_empty(run);
+  state_empty(gs);
+  ChunkState t;
+  state_empty(t);
+  if (w < ng) {
+    const int g0 = gfirst + w * GQ;
+    for (int u = max(g0, qlo); u <= min(g0 + GQ - 1, qhi); ++u) {
+      get(t, qst[u - qlo]);
+      fold(gs, t, 1);
+    }
+    put(gst[w], gs);
   }
   __syncthreads();
-  if (!s_last) return;
-  if (threadIdx.x == 0)
-    __hip_atomic_store(a.ctr + item * MAXQ + qi, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // the quad state: its chunks folded in order from the empty state (hd block w in wave w)
-  ChunkState qs, p;
-  state_empty(qs);
-  state_empty(p);
-  for (int k = 0; k < QCH; ++k) {
-    if (q0 + k < c_lo || q0 + k > c_hi) continue;
-    const float* src = chunk_slot(a, item, qi, k, w);
-    auto get = [&](int i) {
-      return __hip_atomic_load(src + i * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    p.m = get(0);
-    p.l = get(1);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) p.o[0][j] = get(2 + j);
-    fold(qs, p, 1);
+  if (w != 0) return;
+  for (int k = 0; k < ng; ++k) {
+    get(t, gst[k]);
+    fold(run, t, 1);
   }
-  // the fold kernel's layout (state_put): m, l, then o[hb][j] at 2 + 4 hb + j
-  float* qd = a.ws + ((long long)item * MAXQ + qi) * QSTATE * 64;
-  if (w == 0) {
-    qd[lane] = qs.m;
-    qd[64 + lane] = qs.l;
-  }
-  if (w < nhb) {
+  if (col < it.ncols) {
+    const int g = a.Hq / a.Hk, cc = it.c0 + col;
+    const long long orow = it.row_base + cc / g;
+    float* o = static_cast<float*>(a.out) + orow * ((long long)a.Hq * a.hd) +
+               (long long)(it.kvh * g + cc % g) * a.hd + hb * 16 + grp * 4;
+    v4f v;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) qd[(2 + w * 4 + j) * 64 + lane] = qs.o[0][j];
+    for (int j = 0; j < 4; ++j) v[j] = run.o[0][j] / run.l;
+    *reinterpret_cast<v4f*>(o) = v;
+  }
+  if (a.out_amax) {
+    float omax = 0.f;
+    if (col < it.ncols)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) omax = fmaxf(omax, fabsf(run.o[0][j] / run.l));
+    omax = wave_max_f(omax);
+    if (lane == 0) atomic_max_abs(a.out_amax, omax);
   }
 }
 
+// ---- small kernels ------------------------------------------------------------------------
+
+// x[r] = E[tok], the block sums of squares of the row, and y[r] = quantise(x[r] * gain)
 template <int P>
 __global__ void embed_kernel(const float* __restrict__ E, const RowMeta* __restrict__ rows, int n,
                              int d, float* __restrict__ x, float* __restrict__ ssq, void* y,
@@ -2103,9 +2141,13 @@ static void attn_go(const AttnArgs& a, bool parallel, hipStream_t s) {
   const bool grouped = a.n_items > kChunkItems && a.n_items >= 2 * a.n_groups;
   if (parallel) {
     const int nq = std::min(a.quads, attention_quads(a.ctx_len));
-    if (PA == P_F32 && a.ctr && a.n_items <= kChunkItems) {
-      hipLaunchKernelGGL(attention_chunk_kernel, dim3(a.n_items * nq * QCH), dim3(256), 0, s, a);
-    } else if (grouped) {
+    if (PA == P_F32 && a.n_items <= kChunkItems) {
+      hipLaunchKernelGGL(attention_chunk_kernel, dim3(QCH, a.n_items, nq), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(attention_chunk_fold_kernel, dim3(a.n_items, a.hd / 16), dim3(64 * nq), 0,
+                         s, a);
+      return;
+    }
+    if (grouped) {
       hipLaunchKernelGGL((a.hd == HDMAX ? attention_group_kernel<PA, PO, true, true>
                                         : attention_group_kernel<PA, PO, true, false>),
                          dim3(a.n_groups * std::min(a.quads, attention_quads(a.ctx_len, GI))),
@@ -2125,10 +2167,8 @@ static void attn_go(const AttnArgs& a, bool parallel, hipStream_t s) {
 size_t attention_ws_bytes(int n_items) {
   const size_t quads = size_t(n_items) * MAXQ * QSTATE * 64;
   const size_t chunks = n_items <= kChunkItems ? size_t(n_items) * MAXQ * QCH * 4 * CST * 64 : 0;
-  return (quads + chunks) * sizeof(float);
+  return std::max(quads, chunks) * sizeof(float);
 }
-
-size_t attention_counters(int n_items) { return size_t(n_items) * MAXQ; }
 
 // parallel: a workgroup per (item, quad of chunks) and a fold kernel (few items, decode);
 // otherwise one wave per item (prefill).  Both produce the same bits.
