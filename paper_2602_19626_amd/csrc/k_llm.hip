@@ -1642,60 +1642,21 @@ __global__ __launch_bounds__(256) void attention_quad_kernel(const AttnArgs a) {
   state_put(a.ws + ((long long)item * MAXQ + qi) * QSTATE * 64, qs, lane);
 }
 
-// Few items, second kernel: quads -> groups -> output, one workgroup per (item, head-dimension
-// block hb): a state's m and l and its block hb fold on their own (the other blocks only scale
-// alike), so the four blocks' folds run side by side.  Wave w folds the quads of the item's w-th
-// group (their states loaded together) and leaves the group state in LDS; wave 0 then folds the
-// groups in order.  The folds are the sequential kernel's, in the same order, so the output is
-// the same.
-constexpr int FOLD_WAVES = (MAXQ + GQ - 2) / GQ + 1;  // groups an item may span
-constexpr int BSTATE = 2 + 4;                         // floats per lane of a one-block state
+constexpr int BSTATE = 2 + 4;  // floats per lane of a one-block state
+
+// Block hb of a state as a one-block state: o[0] holds what state_put laid out as o[hb].
+__device__ __forceinline__ void block_get(ChunkState& st, const float* q, int hb, int lane) {
+  st.m = q[lane];
+  st.l = q[64 + lane];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) st.o[0][j] = q[(2 + hb * 4 + j) * 64 + lane];
+}
+
+// Output block hb of the lane's column from its one-block state: attn_store for one block.
 template <int PO>
-__global__ __launch_bounds__(64 * FOLD_WAVES) void attention_fold_kernel(const AttnArgs a) {
-  __shared__ float gst[FOLD_WAVES][BSTATE * 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15, grp = lane >> 4;
-  const int item = blockIdx.x, hb = blockIdx.y;
-  const AttnItem it = a.items[item];
-  const int c_lo = it.c_lo, c_hi = it.c_hi;
-  const int qlo = c_lo / QCH, qhi = c_hi / QCH;
-  const int gfirst = (qlo / GQ) * GQ;
-  const int ng = (qhi - gfirst) / GQ + 1;  // <= FOLD_WAVES: qhi - qlo < MAXQ
-  const float* src = a.ws + (long long)item * MAXQ * QSTATE * 64;
-  // m, l and block hb of a quad state (state_put layout) as a one-block state
-  auto get_block = [&](ChunkState& st, const float* q) {
-    st.m = q[lane];
-    st.l = q[64 + lane];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) st.o[0][j] = q[(2 + hb * 4 + j) * 64 + lane];
-  };
-  if (w < ng) {
-    const int g0 = gfirst + w * GQ;
-    ChunkState gs, p[GQ];
-#pragma unroll
-    for (int u = 0; u < GQ; ++u)
-      if (g0 + u >= qlo && g0 + u <= qhi) get_block(p[u], src + (g0 + u - qlo) * QSTATE * 64);
-    state_empty(gs);
-#pragma unroll
-    for (int u = 0; u < GQ; ++u)
-      if (g0 + u >= qlo && g0 + u <= qhi) fold(gs, p[u], 1);
-    gst[w][lane] = gs.m;
-    gst[w][64 + lane] = gs.l;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) gst[w][(2 + j) * 64 + lane] = gs.o[0][j];
-  }
-  __syncthreads();
-  if (w != 0) return;
-  ChunkState run, gs;
-  state_empty(run);
-  state_empty(gs);
-  for (int k = 0; k < ng; ++k) {
-    gs.m = gst[k][lane];
-    gs.l = gst[k][64 + lane];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) gs.o[0][j] = gst[k][(2 + j) * 64 + lane];
-    fold(run, gs, 1);
-  }
-  // output block hb of the lane's column: attn_store's arithmetic for one block
+__device__ __forceinline__ void block_store(const AttnArgs& a, const AttnItem& it,
+                                            const ChunkState& run, int hb, int lane) {
+  const int col = lane & 15, grp = lane >> 4;
   float omax = 0.f;
   if (col < it.ncols) {
     const int g = a.Hq / a.Hk, hd = a.hd;
@@ -1723,6 +1684,90 @@ __global__ __launch_bounds__(64 * FOLD_WAVES) void attention_fold_kernel(const A
   }
 }
 
+// Few items, second kernel: quads -> groups -> output, one workgroup per (item, head-dimension
+// block hb): a state's m and l and its block hb fold on their own (the other blocks only scale
+// alike), so the four blocks' folds run side by side.  Wave w folds the quads of the item's w-th
+// group (their states loaded together) and leaves the group state in LDS; wave 0 then folds the
+// groups in order.  The folds are the sequential kernel's, in the same order, so the output is
+// the same.
+constexpr int FOLD_WAVES = (MAXQ + GQ - 2) / GQ + 1;  // groups an item may span
+template <int PO>
+__global__ __launch_bounds__(64 * FOLD_WAVES) void attention_fold_kernel(const AttnArgs a) {
+  __shared__ float gst[FOLD_WAVES][BSTATE * 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15, grp = lane >> 4;
+  const int item = blockIdx.x, hb = blockIdx.y;
+  const AttnItem it = a.items[item];
+  const int c_lo = it.c_lo, c_hi = it.c_hi;
+  const int qlo = c_lo / QCH, qhi = c_hi / QCH;
+  const int gfirst = (qlo / GQ) * GQ;
+  const int ng = (qhi - gfirst) / GQ + 1;  // <= FOLD_WAVES: qhi - qlo < MAXQ
+  const float* src = a.ws + (long long)item * MAXQ * QSTATE * 64;
+  if (w < ng) {
+    const int g0 = gfirst + w * GQ;
+    ChunkState gs, p[GQ];
+#pragma unroll
+    for (int u = 0; u < GQ; ++u)
+      if (g0 + u >= qlo && g0 + u <= qhi) block_get(p[u], src + (g0 + u - qlo) * QSTATE * 64, hb, lane);
+    state_empty(gs);
+#pragma unroll
+    for (int u = 0; u < GQ; ++u)
+      if (g0 + u >= qlo && g0 + u <= qhi) fold(gs, p[u], 1);
+    gst[w][lane] = gs.m;
+    gst[w][64 + lane] = gs.l;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) gst[w][(2 + j) * 64 + lane] = gs.o[0][j];
+  }
+  __syncthreads();
+  if (w != 0) return;
+  ChunkState run, gs;
+  state_empty(run);
+  state_empty(gs);
+  for (int k = 0; k < ng; ++k) {
+    gs.m = gst[k][lane];
+    gs.l = gst[k][64 + lane];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) gs.o[0][j] = gst[k][(2 + j) * 64 + lane];
+    fold(run, gs, 1);
+  }
+  block_store<PO>(a, it, run, hb, lane);
+}
+
+// Windows of one quad: a workgroup per item, one wave per chunk; wave hb then folds the chunks of
+// head-dimension block hb, takes the (one) quad through the group's fold and the last one, and
+// writes the output, so that no second kernel is needed.  A pass of 64 BF16 streams of 250 tokens: 6.6 us
+// a layer in place of 6.3 + 3.0 and the gap between two launches (64 streams' decode 245 to 220 ms).
+// Longer windows stay with two kernels: 16 waves and 4 quads in one workgroup, with the partials in
+// 98 KB of LDS, took 12.8 us for one BF16 row after 700 tokens where the two take 11.5.
+template <int PA, int PO>
+__global__ __launch_bounds__(256) void attention_item_kernel(const AttnArgs a) {
+  __shared__ float part[QCH][QSTATE * 64];
+  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const AttnItem it = a.items[blockIdx.x];
+  const int ch = (it.c_lo / QCH) * QCH + w;
+  const AttnCol c = attn_col(a, it, col);
+  if (ch >= it.c_lo && ch <= it.c_hi) {
+    QFrag<PA> q;
+    load_q<PA>(q, a, c, grp);
+    state_put(part[w], chunk_partial<PA>(a, it, c, q, ch, col, grp), lane);
+  }
+  __syncthreads();
+  if (w >= a.hd / 16) return;
+  ChunkState run, gs, qs, p;
+  state_empty(run);
+  state_empty(gs);
+  state_empty(qs);
+  state_empty(p);
+  for (int k = 0; k < QCH; ++k) {
+    if (ch - w + k < it.c_lo || ch - w + k > it.c_hi) continue;
+    block_get(p, part[k], w, lane);
+    fold(qs, p, 1);
+  }
+  fold(gs, qs, 1);
+  fold(run, gs, 1);
+  block_store<PO>(a, it, run, w, lane);
+}
+
 // Few items, FP32 (decode): the quad kernel's work spread over a workgroup per chunk, so that each
 // chunk's MFMA chains run on four SIMDs instead of one.  Wave w runs the score chain of key
 // block w, the four blocks' scores meet in LDS, every wave takes the chunk's softmax (the same
@@ -1733,7 +1778,7 @@ __global__ __launch_bounds__(64 * FOLD_WAVES) void attention_fold_kernel(const A
 // attention_chunk_fold_kernel: handed over inside this kernel instead, by device-scope stores and a
 // counter a quad, they cost two more round trips to the coherence point than a wider fold costs.  One
 // FP32 row after 1,200 tokens, both kernels: 13.4 us a layer with the handover, 12.1 without; the
-// chain is the bound (item, K and V, 16 + 16 dependent MFMAs, states, folds), not the 5 MB of keys.
+// chain is the bound (item, K and V, 16 + 16 dependent MFMAs, states, folds), not the 1.8 MB of keys.
 constexpr int kChunkItems = 24;  // largest item count of the chunk-parallel path
 constexpr int CST = 6;           // floats per lane of one wave's chunk state: m, l, o[4]
 
@@ -1879,24 +1924,7 @@ __global__ __launch_bounds__(64 * MAXQ) void attention_chunk_fold_kernel(const A
     get(t, gst[k]);
     fold(run, t, 1);
   }
-  if (col < it.ncols) {
-    const int g = a.Hq / a.Hk, cc = it.c0 + col;
-    const long long orow = it.row_base + cc / g;
-    float* o = static_cast<float*>(a.out) + orow * ((long long)a.Hq * a.hd) +
-               (long long)(it.kvh * g + cc % g) * a.hd + hb * 16 + grp * 4;
-    v4f v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = run.o[0][j] / run.l;
-    *reinterpret_cast<v4f*>(o) = v;
-  }
-  if (a.out_amax) {
-    float omax = 0.f;
-    if (col < it.ncols)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) omax = fmaxf(omax, fabsf(run.o[0][j] / run.l));
-    omax = wave_max_f(omax);
-    if (lane == 0) atomic_max_abs(a.out_amax, omax);
-  }
+  block_store<P_F32>(a, it, run, hb, lane);
 }
 
 // ---- small kernels ------------------------------------------------------------------------
@@ -2135,9 +2163,11 @@ static int attention_quads(int ctx_len, int items = 1) {
 
 template <int PA, int PO>
 static void attn_go(const AttnArgs& a, bool parallel, hipStream_t s) {
-  // shared staging needs 2 items a group to pay (FP32, 64 streams of 4 and 6 rows: one item a group 15.7 us
-  // alone and 23.5 grouped, two 36.6 and 28.2), and work for the chip (BF16, one stream of 32 and 43
-  // rows: 18 items 13.7 and 14.7, 27 items 15.1 and 14.3)
+  // Shared staging needs 2 items a group to pay (FP32, 64 streams: of 4 rows, one item a group,
+  // 15.7 us alone and 23.5 grouped; of 6 rows, two, 36.6 and 28.2) and work for the chip (one BF16
+  // stream after 1,200 tokens: 18 items 13.7 and 14.7, 27 items 15.1 and 14.3).  FP32 chunk by chunk is
+  // the shorter chain for few items also where one quad is the whole window (one row after 200 tokens:
+  // 11.1 us, and 12.5 an item a workgroup).
   const bool grouped = a.n_items > kChunkItems && a.n_items >= 2 * a.n_groups;
   if (parallel) {
     const int nq = std::min(a.quads, attention_quads(a.ctx_len));
@@ -2145,6 +2175,10 @@ static void attn_go(const AttnArgs& a, bool parallel, hipStream_t s) {
       hipLaunchKernelGGL(attention_chunk_kernel, dim3(QCH, a.n_items, nq), dim3(256), 0, s, a);
       hipLaunchKernelGGL(attention_chunk_fold_kernel, dim3(a.n_items, a.hd / 16), dim3(64 * nq), 0,
                          s, a);
+      return;
+    }
+    if (!grouped && nq == 1) {
+      hipLaunchKernelGGL((attention_item_kernel<PA, PO>), dim3(a.n_items), dim3(256), 0, s, a);
       return;
     }
     if (grouped) {
