@@ -1294,12 +1294,23 @@ __device__ __forceinline__ LsePart known_lse(const float (&u)[4][4]) {
       for (int i = 0; i < 4; ++i) sum += expf(u[q][i] - m);
   return wave_lse(LsePart{m, sum});
 }
-__device__ __forceinline__ void known_lse_store(const KnownChunk& C, int j, int r, int seg,
-                                                int nseg, const LsePart* wl) {
+__device__ __forceinline__ LsePart known_lse_sum(const LsePart* wl) {
   LsePart acc = wl[0];
   for (int k = 1; k < kSegWaves; ++k) acc = lse_merge(acc, wl[k]);
-  C.lse[((size_t)(j & 1) * C.B + r) * nseg + seg] = acc;
+  return acc;
 }
+__device__ __forceinline__ void known_lse_store(const KnownChunk& C, int j, int r, int seg,
+                                                int nseg, const LsePart* wl) {
+  C.lse[((size_t)(j & 1) * C.B + r) * nseg + seg] = known_lse_sum(wl);
+}
+
+// Two floats as one word that is not kUnset.
+constexpr uint64_t kUnset = ~uint64_t(0);
+__device__ __forceinline__ uint64_t sync_word(float lo, float hi) {
+  const uint64_t v = uint64_t(__float_as_uint(hi)) << 32 | __float_as_uint(lo);
+  return v == kUnset ? 0x7FC000007FC00000ull : v;  // (both NaN either way)
+}
+__device__ __forceinline__ uint64_t sync_word(const LsePart& p) { return sync_word(p.m, p.s); }
 
 // The chunk's first position: its logsumexp partials.
 __global__ __launch_bounds__(kSegThreads) void known_first_kernel(VocabParams P, StreamState S,
@@ -1322,21 +1333,107 @@ __global__ __launch_bounds__(kSegThreads) void known_first_kernel(VocabParams P,
   if ((tid & 63) == 0) wl[tid >> 6] = part;
   __syncthreads();
   if (tid == 0) known_lse_store(C, 0, r, seg, gridDim.x, wl);
+  if (!C.sync) return;
+  const int ns = gridDim.x + 1;
+  uint64_t* sync = C.sync + (size_t)r * ns;
+  if (tid == 0) sync[seg] = sync_word(known_lse_sum(wl));
+  for (int j = tid; j < C.np; j += kSegThreads) {
+    if (j > 0) sync[(size_t)j * C.B * ns + seg] = kUnset;
+    if (seg == 0) sync[(size_t)j * C.B * ns + ns - 1] = kUnset;
+  }
+}
+
+// A wave's part of a position's counts: their sum, the sum before the token, the largest entry.
+struct KnownSums {
+  uint64_t sum, best;
+  uint32_t before;
+  int bad;
+};
+
+// The wave's counts of row's position; the thread that holds the token's entry records it.
+__device__ __forceinline__ KnownSums known_counts(const VocabParams& P, const KnownChunk& C,
+                                                  size_t row, int seg, int tid, int mode, int tok,
+                                                  const float (&p)[4][4], const float (&pt)[4][4],
+                                                  const f4v (&g)[4]) {
+  const int V = P.V;
+  const uint32_t m = P.total - uint32_t(V);
+  uint32_t sum = 0, before = 0;
+  int bad = 0;
+  uint64_t best = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t t = seg_index(seg, q, tid, i);
+      const float x = p[q][i];
+      const uint32_t c = t < uint32_t(V) ? floor_count(x, m) : 0u;
+      sum += c;
+      before += t < uint32_t(tok) ? c : 0u;
+      if (t < uint32_t(V)) {
+        if (!(x >= 0.f && x <= 1.f)) bad = 1;
+        const uint64_t key = max_key(x, t);
+        best = key > best ? key : best;
+      }
+      if (t == uint32_t(tok)) {
+        KnownRec& o = C.rec[row];
+        o.c = c;
+        o.p = x;
+        o.pt = pt[q][i];
+        o.png = C.png ? g[q][i] : 0.f;
+        o.mode = mode;
+      }
+    }
+  return KnownSums{wave_sum_u64(sum), wave_max_u64(best), wave_sum_u32(before), __any(bad) ? 1 : 0};
+}
+
+// The position's count partial of the segment from its waves', and the counts before the token.
+__device__ __forceinline__ void known_store(const KnownChunk& C, size_t row, int seg, int nseg,
+                                            int tok, const KnownSums* ws) {
+  uint64_t tot = 0, bk = 0;
+  uint32_t bf = 0;
+  int bd = 0;
+#pragma unroll
+  for (int k = 0; k < kSegWaves; ++k) {
+    tot += ws[k].sum;
+    bf += ws[k].before;
+    bk = ws[k].best > bk ? ws[k].best : bk;
+    bd |= ws[k].bad;
+  }
+  SegPartial sp;
+  sp.sum = tot >= 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(tot);
+  sp.maxv = key_value(bk);
+  sp.maxi = key_index(bk);
+  sp.bad = bd;
+  static_cast<SegPartial*>(C.segs)[row * nseg + seg] = sp;
+  if (uint32_t(tok) / kSeg == uint32_t(seg)) C.rec[row].before = bf;
+}
+
+// Bias-head step on -log ptilde(t*), section 3.7 (b in place), and u = z2 + b of the next position.
+__device__ __forceinline__ void known_bias(const VocabParams& P, bool learn, int seg, int tid,
+                                           int tok, const float (&pt)[4][4], const f4v (&z2)[4],
+                                           f4v (&b)[4], float (&u)[4][4]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t t0 = seg_index(seg, q, tid, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float ind = int(t0) + i == tok ? 1.f : 0.f;
+      if (learn) b[q][i] = b[q][i] - P.head_lr * (pt[q][i] - ind);
+      u[q][i] = t0 >= uint32_t(P.V) ? -INFINITY : (P.use_head ? z2[q][i] + b[q][i] : z2[q][i]);
+    }
+  }
 }
 
 // Position j of the chunk, one workgroup per (segment, row); see above for what it leaves.  A chain
 // of np such launches is what a stream's encoding takes, so what counts is the time of one: every
 // load goes out at once, and the reductions stay in registers.  7.0 us a position at one stream
 // (V = 49,152), where logsumexp, count, scan and update were four dependent launches of 21.9 us
-// ordered against the n-gram's three by events: encoding 4,096 tokens took 208.5 ms, now 90.2 ms
-// (the transformer passes run beside the chain and bound it).  64 streams: 21.5 us a position
-// against 39.9 us, bound by memory.
+// ordered against the n-gram's three by events.  64 streams: 15.3 us a
+// position against 39.9 us, bound by memory.
 __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, StreamState S,
                                                                  KnownChunk C, int j) {
   __shared__ LsePart s_lse[kSegWaves];
-  __shared__ uint64_t s_sum[kSegWaves], s_best[kSegWaves];
-  __shared__ uint32_t s_before[kSegWaves];
-  __shared__ int s_bad[kSegWaves];
+  __shared__ KnownSums s_sums[kSegWaves];
   const int seg = blockIdx.x, r = blockIdx.y, nseg = gridDim.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int V = P.V, s = C.s0 + r;
@@ -1381,83 +1478,162 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
   R.w[1] = expf(lw[1]);
   float p[4][4], pt[4][4];
   row_probs<false>(R, v, seg, tid, p, pt);
-  // count partial of the segment, the counts before the token's, and the token's own entry
-  const uint32_t m = P.total - uint32_t(V);
-  uint32_t sum = 0, before = 0;
-  int bad = 0;
-  uint64_t best = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t t = seg_index(seg, q, tid, i);
-      const float x = p[q][i];
-      const uint32_t c = t < uint32_t(V) ? floor_count(x, m) : 0u;
-      sum += c;
-      before += t < uint32_t(tok) ? c : 0u;
-      if (t < uint32_t(V)) {
-        if (!(x >= 0.f && x <= 1.f)) bad = 1;
-        const uint64_t key = max_key(x, t);
-        best = key > best ? key : best;
-      }
-      if (t == uint32_t(tok)) {
-        KnownRec& o = C.rec[row];
-        o.c = c;
-        o.p = x;
-        o.pt = pt[q][i];
-        o.png = C.png ? v.g[q][i] : 0.f;
-        o.mode = mode;
-      }
-    }
-  // bias-head step on -log ptilde(t*), section 3.7, then the next position's logsumexp with it
+  const KnownSums sums = known_counts(P, C, row, seg, tid, mode, tok, p, pt, v.g);
+  // the bias-head step, then the next position's logsumexp with it
   const bool learn = P.use_head && uses_llm(mode);
   float u[4][4];
+  known_bias(P, learn, seg, tid, tok, pt, z2, v.b, u);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const uint32_t t0 = seg_index(seg, q, tid, 0);
-    f4v nb;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float ind = int(t0) + i == tok ? 1.f : 0.f;
-      nb[i] = learn ? v.b[q][i] - P.head_lr * (pt[q][i] - ind) : v.b[q][i];
-      u[q][i] = t0 >= uint32_t(V) ? -INFINITY : (P.use_head ? z2[q][i] + nb[i] : z2[q][i]);
-    }
-    if (learn && t0 < uint32_t(V)) *reinterpret_cast<f4v*>(b + t0) = nb;
+    if (learn && t0 < uint32_t(V)) *reinterpret_cast<f4v*>(b + t0) = v.b[q];
   }
-  const uint64_t wsum = wave_sum_u64(sum);
-  before = wave_sum_u32(before);
-  best = wave_max_u64(best);
-  const int any_bad = __any(bad) ? 1 : 0;
   const bool lse2 = more && j + 1 < left && uses_llm(mode2);
   const LsePart part = lse2 ? known_lse(u) : LsePart{-INFINITY, 0.f};
   if (lane == 0) {
-    s_sum[w] = wsum;
-    s_before[w] = before;
-    s_best[w] = best;
-    s_bad[w] = any_bad;
+    s_sums[w] = sums;
     s_lse[w] = part;
   }
   __syncthreads();
-  if (tid == 0) {
-    uint64_t tot = 0, bk = 0;
-    uint32_t bf = 0;
-    int bd = 0;
-#pragma unroll
-    for (int k = 0; k < kSegWaves; ++k) {
-      tot += s_sum[k];
-      bf += s_before[k];
-      bk = s_best[k] > bk ? s_best[k] : bk;
-      bd |= s_bad[k];
-    }
-    SegPartial sp;
-    sp.sum = tot >= 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(tot);
-    sp.maxv = key_value(bk);
-    sp.maxi = key_index(bk);
-    sp.bad = bd;
-    static_cast<SegPartial*>(C.segs)[row * nseg + seg] = sp;
-    if (uint32_t(tok) / kSeg == uint32_t(seg)) C.rec[row].before = bf;
-  }
+  if (tid == 0) known_store(C, row, seg, nseg, tok, s_sums);
   if (tid == 64 && lse2) known_lse_store(C, j + 1, r, seg, nseg, s_lse);
+}
+
+// The chunk's positions in one launch, one workgroup per (segment, row) over all of them: the bias
+// stays in registers and the next position's logits and n-gram probabilities arrive while this one is
+// computed.  Between two positions the row's workgroups exchange the segments' logsumexp partials and
+// the token's probabilities (which move the mixer): each is one 64-bit word of its own per position,
+// unset at first, stored and polled at device scope, so a word that is set is also whole.  The counts
+// come after the words are out.  One stream, V = 49,152: 5.2 us a position alone and 7.2 beside a
+// transformer pass, where a launch per position took 6.2 and 9.8; encoding 4,096 tokens 42.3 to 35.1
+// ms, bound by the passes again.
+// A workgroup waits for those of its own row only, so all that a wait needs is that they get to run:
+// two workgroups fit a CU, and kRunGroups is half of what the chip holds, which leaves room for a second
+// context's.  If they still do not run (many contexts at once) a wait ends after kSpinLimit polls, a
+// few tenths of a second, and raises the flag of an invalid distribution, with which the caller takes
+// the positions one by one.  More rows than that gain less: 33 BF16 streams of 1,000 tokens (396
+// workgroups) 39.5 ms, or 36.8 in one launch; 64 streams 68.1 and 68.2, 200 streams 66.4 and 68.0.
+constexpr int kRunGroups = 256;
+constexpr int kSpinLimit = 1 << 18;
+
+__device__ __forceinline__ uint64_t sync_load(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void sync_store(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, StreamState S,
+                                                                KnownChunk C) {
+  __shared__ LsePart s_lse[2][kSegWaves];
+  __shared__ KnownSums s_sums[2][kSegWaves];
+  const int seg = blockIdx.x, r = blockIdx.y, nseg = gridDim.x, ns = nseg + 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int V = P.V, s = C.s0 + r;
+  const int n = min(C.np, C.left[r]);
+  if (n <= 0) return;
+  const size_t step = (size_t)C.B * V;
+  float* b = S.b + (size_t)s * V;
+  uint32_t tc[4];  // (an index past the end reads the row's start; masked below)
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t t0 = seg_index(seg, q, tid, 0);
+    tc[q] = t0 < uint32_t(V) ? t0 : 0;
+  }
+  auto fetch = [&](f4v(&d)[4], const float* src) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d[q] = *reinterpret_cast<const f4v*>(src + tc[q]);
+  };
+  const float* z0 = C.z + (size_t)r * V;
+  const float* g0 = C.png ? C.png + (size_t)r * V : z0;
+  RowVec v;
+  f4v z2[4], z3[4], g2[4];
+  fetch(v.b, b);
+  fetch(v.z, z0);
+  fetch(v.g, g0);
+  fetch(z2, z0 + (n > 1 ? step : 0));
+  float lw[2] = {S.lw[(size_t)s * kMaxExperts], S.lw[(size_t)s * kMaxExperts + 1]};
+  int mode = C.mode[r], tok = C.tok[r], mode2 = C.mode[n > 1 ? C.B + r : r];
+  int last_mode = 0, last_tok = 0;
+  bool late = false;  // a wait of this wave has ended without its words
+  for (int j = 0; j < n; ++j) {
+    const size_t row = (size_t)j * C.B + r;
+    const bool more = j + 1 < n;
+    // the next position's inputs (the one after it for the logits)
+    fetch(z3, z0 + min(j + 2, n - 1) * step);
+    fetch(g2, g0 + min(j + 1, n - 1) * step);
+    const int tok2 = C.tok[more ? row + C.B : row];
+    const int mode3 = C.mode[(size_t)min(j + 2, n - 1) * C.B + r];
+    // the words of this position
+    const uint64_t* words = C.sync + row * ns;
+    const bool llm = uses_llm(mode);
+    uint64_t part = 0, out = 0;
+    for (int spin = 0;; ++spin) {
+      part = sync_load(words + min(lane, nseg - 1));
+      if (j > 0) out = sync_load(words - (size_t)C.B * ns + nseg);
+      const bool wait = (llm && part == kUnset) || out == kUnset;
+      if (__builtin_amdgcn_ballot_w64(wait) == 0) break;
+      if (late || spin >= kSpinLimit) {
+        late = true;
+        if (lane == 0) atomicOr(C.bad, 1);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    auto lo = [](uint64_t x) { return __uint_as_float(uint32_t(x)); };
+    auto hi = [](uint64_t x) { return __uint_as_float(uint32_t(x >> 32)); };
+    if (j > 0) mixer_step(P, last_mode, lo(out), hi(out), lw);
+    RowIn R;
+    R.V = V;
+    R.K = P.K;
+    R.mode = mode;
+    R.use_head = P.use_head;
+    R.lse = llm ? row_lse(LsePart{lo(part), hi(part)}, nseg, lane) : 0.f;
+    R.w[0] = expf(lw[0]);
+    R.w[1] = expf(lw[1]);
+    float p[4][4], pt[4][4], u[4][4];
+    row_probs<false>(R, v, seg, tid, p, pt);
+    if (more) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (seg_index(seg, q, tid, i) == uint32_t(tok))
+            sync_store(C.sync + row * ns + nseg, sync_word(pt[q][i], C.png ? v.g[q][i] : 0.f));
+    }
+    known_bias(P, P.use_head && llm, seg, tid, tok, pt, z2, v.b, u);
+    const bool lse2 = more && uses_llm(mode2);
+    if (lse2) {
+      const LsePart mine = known_lse(u);
+      if (lane == 0) s_lse[j & 1][w] = mine;
+    }
+    __syncthreads();
+    if (tid == 0 && lse2)
+      sync_store(C.sync + (row + C.B) * ns + seg, sync_word(known_lse_sum(s_lse[j & 1])));
+    // the position before's counts are complete
+    if (tid == 64 && j > 0)
+      known_store(C, row - C.B, seg, nseg, last_tok, s_sums[(j - 1) & 1]);
+    const KnownSums sums = known_counts(P, C, row, seg, tid, mode, tok, p, pt, v.g);
+    if (lane == 0) s_sums[j & 1][w] = sums;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v.z[q] = z2[q];
+      z2[q] = z3[q];
+      v.g[q] = g2[q];
+    }
+    last_mode = mode;
+    last_tok = tok;
+    mode = mode2;
+    mode2 = mode3;
+    tok = tok2;
+  }
+  __syncthreads();
+  if (tid == 64)
+    known_store(C, (size_t)(n - 1) * C.B + r, seg, nseg, last_tok, s_sums[(n - 1) & 1]);
+  if (seg == 0 && tid < 2) C.lw[((size_t)((n - 1) & 1) * C.B + r) * 2 + tid] = tid ? lw[1] : lw[0];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (seg_index(seg, q, tid, 0) < uint32_t(V)) *reinterpret_cast<f4v*>(b + tc[q]) = v.b[q];
 }
 
 // The intervals of the chunk's positions from their count partials, and the mixer weights after
@@ -1815,11 +1991,18 @@ void launch_known_ngram(const VocabParams& P, const StreamState& S, const KnownC
   NC_HIP(hipGetLastError());
 }
 
+bool known_in_one_launch(int B, int V) { return B * ceil_div(V, kSeg) <= kRunGroups; }
+
 void launch_known_steps(const VocabParams& P, const StreamState& S, const KnownChunk& C,
                         hipStream_t s) {
   if (C.B <= 0 || C.np <= 0) return;
   const dim3 grid(ceil_div(P.V, kSeg), C.B);
   hipLaunchKernelGGL(known_first_kernel, grid, dim3(kSegThreads), 0, s, P, S, C);
+  if (C.sync) {
+    hipLaunchKernelGGL(known_run_kernel, grid, dim3(kSegThreads), 0, s, P, S, C);
+    NC_HIP(hipGetLastError());
+    return;
+  }
   for (int j = 0; j < C.np; ++j)
     hipLaunchKernelGGL(known_step_kernel, grid, dim3(kSegThreads), 0, s, P, S, C, j);
   NC_HIP(hipGetLastError());

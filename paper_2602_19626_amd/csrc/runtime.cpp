@@ -5,7 +5,6 @@
 
 #include <algorithm>
 #include <chrono>
-#include <climits>
 #include <cmath>
 #include <cstring>
 #include <numeric>
@@ -77,10 +76,10 @@ struct nc_ctx {
   int prec = P_F32, att = P_F32;
   int dev = 0;
   hipStream_t st = nullptr;
-  // chunks of known tokens: the transformer passes run on st, the n-gram side on st2, the
-  // position-by-position chain on st3 and the output layer of passes of several chunks on st4, on
-  // two sets of chunk buffers in turn
-  hipStream_t st2 = nullptr, st3 = nullptr, st4 = nullptr;
+  // chunks of known tokens: the transformer passes run on st, the n-gram side on st2 (and the output
+  // layer of passes of several chunks) and the position-by-position chain on st3, on two sets of
+  // chunk buffers in turn
+  hipStream_t st2 = nullptr, st3 = nullptr;
   int d = 0, hq = 0, hk = 0, hd = 0, F = 0, V = 0, nl = 0, R = 0;
   // weights
   std::vector<void*> allocs;
@@ -131,6 +130,7 @@ struct nc_ctx {
     DevBuf<LsePart> lse;
     DevBuf<SegPartial> segs;
     DevBuf<KnownRec> rec;
+    DevBuf<uint64_t> sync;
     hipEvent_t ngram = nullptr, logits = nullptr, done = nullptr;
   } kb[2];
   DevBuf<int32_t> kbad;  // set by a chunk with an invalid distribution
@@ -204,7 +204,7 @@ struct nc_ctx {
 
 nc_ctx::~nc_ctx() {
   if (dev >= 0) (void)hipSetDevice(dev);
-  for (hipStream_t q : {st, st2, st3, st4})
+  for (hipStream_t q : {st, st2, st3})
     if (q) (void)hipStreamSynchronize(q);
   for (void* p : allocs) (void)hipFree(p);
   DevBuf<float>* fb[] = {&yb, &xss, &aws, &xinv, &hinv, &amax, &rope, &b, &png, &pk, &lw, &Hd, &pmaxd, &hlast, &x, &ptok, &z, &zseg,
@@ -245,6 +245,7 @@ nc_ctx::~nc_ctx() {
     k.lse.release();
     k.segs.release();
     k.rec.release();
+    k.sync.release();
     for (hipEvent_t e : {k.ngram, k.logits, k.done})
       if (e) (void)hipEventDestroy(e);
   }
@@ -260,7 +261,6 @@ nc_ctx::~nc_ctx() {
   for (auto& g : graphs) (void)hipGraphExecDestroy(g.second);
   for (auto& g : egraphs)
     if (g.second.ex) (void)hipGraphExecDestroy(g.second.ex);
-  if (st4) (void)hipStreamDestroy(st4);
   if (st3) (void)hipStreamDestroy(st3);
   if (st2) (void)hipStreamDestroy(st2);
   if (st) (void)hipStreamDestroy(st);
@@ -313,7 +313,6 @@ void sync(nc_ctx* c) {
   NC_HIP(hipStreamSynchronize(c->st));
   NC_HIP(hipStreamSynchronize(c->st2));
   NC_HIP(hipStreamSynchronize(c->st3));
-  NC_HIP(hipStreamSynchronize(c->st4));
   c->stats.wait_seconds +=
       std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   prof_flush(c);
@@ -494,7 +493,10 @@ struct PassPlan {
   std::vector<AttnItem> items;
   std::vector<int32_t> last;  // n_last source rows, then n_last destination streams
   int n_groups = 0;           // attention groups (AttnItem::group)
-  int quads = 0;              // quads that a group spans, rounded up
+  // quads that a group spans at most: the attention grid holds a workgroup for each (as many as the
+  // context length allows, for windows of one, took 100 us of attention a layer where 64 FP32
+  // streams have 22 rows each; one takes 20)
+  int quads = 0;
   double attn_bytes = 0, attn_flops = 0;
   bool shared_kv = false;     // some stream's kv head has several attention items
   size_t off_rows = 0, off_items = 0, off_last = 0;
@@ -555,10 +557,6 @@ PassPlan plan_pass(nc_ctx* c, std::vector<RowMeta> rows, bool calib = false) {
               hi = p.items[first + (groups[k] & 3)].c_hi / 4;
     p.quads = std::max(p.quads, hi - lo + 1);
   }
-  // the attention grid holds a workgroup for each quad an item may have: as many as the pass's
-  // longest window has, in three steps (each has graphs of its own).  Ten of them for windows of one
-  // quad took 100 us of attention a layer where 64 FP32 streams have 22 rows each, one takes 20.
-  p.quads = p.quads <= 1 ? 1 : p.quads <= 4 ? 4 : INT_MAX;
   p.last = src;
   p.last.insert(p.last.end(), dst.begin(), dst.end());
   return p;
@@ -1072,6 +1070,7 @@ nc_ctx::KnownBufs& known_bufs(nc_ctx* c, int par, int np, int B) {
   k.mode.alloc(n);
   k.left.alloc(B);
   k.lse.alloc(size_t(2) * B * nseg);
+  if (known_in_one_launch(B, c->V)) k.sync.alloc(n * (nseg + 1));
   k.segs.alloc(n * nseg + 16);
   k.rec.alloc(n);
   return k;
@@ -1101,7 +1100,8 @@ const uint8_t* upload_slot(nc_ctx* c, int slot, const Stage& s) {
 }
 
 // The chunk's position chain on st3, replayed from a captured graph from its shape's second use on
-// (one launch in place of one per position; the kernels and their arguments are the same).
+// (one launch in place of the first position's and one per position or per chunk; the kernels and
+// their arguments are the same).
 void known_chain(nc_ctx* c, const KnownChunk& C) {
   if ((c->cfg.features & NC_F_EAGER) || profiling(c) || C.np < 2) {
     launch_known_steps(c->vp, c->S, C, c->st3);
@@ -1109,7 +1109,7 @@ void known_chain(nc_ctx* c, const KnownChunk& C) {
   }
   auto num = [](size_t v) { return reinterpret_cast<const void*>(v); };
   const std::vector<const void*> key{num(C.np), num(C.B), num(C.s0), C.left, C.z, C.png, C.tok,
-                                     C.mode, C.lse, C.lw, C.segs, C.rec, c->S.b, c->S.lw};
+                                     C.mode, C.lse, C.lw, C.segs, C.rec, C.sync, c->S.b, c->S.lw};
   if (c->egraphs.size() >= 64 && !c->egraphs.count(key)) {
     NC_HIP(hipStreamSynchronize(c->st3));
     chain_graphs_clear(c);
@@ -1166,6 +1166,7 @@ KnownChunk known_begin(nc_ctx* c, KnownRun& run, const nc_ctx::StageSlot& slot, 
   C.tok = k.tok.p;
   C.mode = k.mode.p;
   C.lse = k.lse.p;
+  C.sync = known_in_one_launch(B, c->V) ? k.sync.p : nullptr;
   C.lw = k.lw.p;
   C.segs = k.segs.p;
   C.rec = k.rec.p;
@@ -1197,12 +1198,12 @@ void keep_rows(nc_ctx* c, nc_ctx::StageSlot& slot, size_t n) {
   NC_HIP(hipEventRecord(slot.rows, c->st));
 }
 
-// The chunk's logits from rows ar[j * B + r] of the slot that keeps them (on st4), or of the pass
-// just run (on st); then its chain.
+// The chunk's logits from rows ar[j * B + r] of the slot that keeps them (on st2, beside the chain of
+// the chunk before), or of the pass just run (on st); then its chain.
 void known_end(nc_ctx* c, const KnownRun& run, const KnownChunk& C, const nc_ctx::StageSlot* slot,
                const int32_t* ar, int p0) {
   nc_ctx::KnownBufs& k = c->kb[(run.chunk - 1) & 1];
-  hipStream_t st = slot ? c->st4 : c->st;
+  hipStream_t st = slot ? c->st2 : c->st;
   NC_HIP(hipStreamWaitEvent(st, k.done, 0));
   if (slot) NC_HIP(hipStreamWaitEvent(st, slot->rows, 0));
   run_lm_head(c, slot ? static_cast<const void*>(slot->y.p) : c->yb.p,
@@ -1273,6 +1274,7 @@ bool encode_known(nc_ctx* c, const std::vector<const int32_t*>& tok,
     }
     const int slot = int((a / C) & 1);
     const uint8_t* dst = upload_slot(c, slot, stg);
+    const bool keep = pieces.size() > 1;
     for (size_t q = 0; q < pieces.size(); ++q) {
       const Piece& pc = pieces[q];
       const int p0 = int(a + pc.i0);
@@ -1280,9 +1282,9 @@ bool encode_known(nc_ctx* c, const std::vector<const int32_t*>& tok,
                                        true);
       if (q == 0) {
         run_pass(c, plan, dst);
-        if (pieces.size() > 1) keep_rows(c, c->slots[slot], plan.rows.size());
+        if (keep) keep_rows(c, c->slots[slot], plan.rows.size());
       }
-      known_end(c, run, K, pieces.size() > 1 ? &c->slots[slot] : nullptr,
+      known_end(c, run, K, keep ? &c->slots[slot] : nullptr,
                 reinterpret_cast<const int32_t*>(dst + pc.off_ar), p0);
     }
     NC_HIP(hipEventRecord(c->slots[slot].done, c->st3));
@@ -1475,7 +1477,6 @@ nc_status nc_create(const nc_config* cfg, const float* w, nc_ctx** out) {
     NC_HIP(hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking));
     NC_HIP(hipStreamCreateWithFlags(&c->st2, hipStreamNonBlocking));
     NC_HIP(hipStreamCreateWithFlags(&c->st3, hipStreamNonBlocking));
-    NC_HIP(hipStreamCreateWithFlags(&c->st4, hipStreamNonBlocking));
     for (auto& k : c->kb)
       for (hipEvent_t* e : {&k.ngram, &k.logits, &k.done})
         NC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));

@@ -131,6 +131,7 @@ struct KnownChunk {
   int32_t* tok;         // [np * B]
   int32_t* mode;        // [np * B]
   LsePart* lse;         // [2][B][nseg], by the parity of j
+  uint64_t* sync;       // [np * B][nseg + 1] what the workgroups of a row tell each other, or null
   float* lw;            // [2][B][2] mixer log-weights entering position j >= 1, by its parity
   void* segs;           // SegPartial [np * B][nseg] (16 more are readable past the last)
   KnownRec* rec;        // [np * B]
@@ -141,6 +142,8 @@ struct KnownChunk {
 // The n-gram side of a chunk: table updates, every position's distribution and mode, counts.
 void launch_known_ngram(const VocabParams& P, const StreamState& S, const KnownChunk& C, int p0,
                         hipStream_t s);
+// A row's positions run in one launch (C.sync is then needed).
+bool known_in_one_launch(int B, int V);
 // The chunk's positions one after the other: probabilities, count partials, bias head, mixer.
 void launch_known_steps(const VocabParams& P, const StreamState& S, const KnownChunk& C,
                         hipStream_t s);

@@ -59,3 +59,52 @@ def test_invalid_distributions_are_refused_like_step_by_step():
     with pytest.raises(nc.NacrithError) as e:
         ctx.encode_stream([synth.make_stream(50, T.vocab, seed=1)])
     assert e.value.status == 6
+
+
+@pytest.mark.parametrize("vocab,streams,prec", [(8200, 1, "bf16"), (4100, 7, "fp32"),
+                                                (12292, 40, "bf16"), (16385 * 4, 40, "fp32")])
+def test_one_launch_chains_equal_streams_alone(vocab, streams, prec):
+    """Chains of 1 to 17 segments a row, rows that end inside a chunk, and row counts on both sides of
+    the one-launch rule (40 rows of 17 segments are past it): the bytes of each stream alone, whose
+    tokens decode (a step per token) gives back."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import paper_2602_19626_amd as nc
+    shape = dataclasses.replace(T, vocab=vocab)
+    w = synth.flat_weights(shape, synth.make_weights(shape, 5))
+    toks = [synth.make_stream(1 + (37 * i + 70) % 150, vocab, seed=i, span=(4, 32))
+            for i in range(streams)]
+    ctx = nc.Context(nc.make_config(shape, precision=prec, warmup=20, max_streams=streams), w)
+    data, _ = ctx.encode_stream(toks)
+    back = ctx.decode_stream(data, [len(t) for t in toks])
+    assert all(np.array_equal(a, b) for a, b in zip(back, toks))
+    one = nc.Context(nc.make_config(shape, precision=prec, warmup=20), w)
+    for i in range(0, streams, 6):
+        assert one.encode_stream([toks[i]])[0][0] == data[i], i
+
+
+def test_two_contexts_at_once():
+    """Chains of two contexts, each near the one-launch limit, run at the same time from two threads:
+    the bytes of either alone."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import threading
+
+    import paper_2602_19626_amd as nc
+    shape = dataclasses.replace(T, vocab=49152)
+    w = synth.flat_weights(shape, synth.make_weights(shape, 5))
+    toks = [synth.make_stream(200 + i, shape.vocab, seed=i, span=(4, 32)) for i in range(21)]
+    ctxs = [nc.Context(nc.make_config(shape, max_streams=len(toks)), w) for _ in range(2)]
+    ref = ctxs[0].encode_stream(toks)[0]
+    out = [None, None]
+
+    def code(k):
+        out[k] = [ctxs[k].encode_stream(toks)[0] for _ in range(3)]
+
+    threads = [threading.Thread(target=code, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k in range(2):
+        assert all(r == ref for r in out[k]), k
