@@ -1350,11 +1350,34 @@ struct KnownSums {
   int bad;
 };
 
-// The wave's counts of row's position; the thread that holds the token's entry records it.
+// The probabilities of the position's token, recorded by the thread that holds its entry; word, if
+// any, tells them to the row's other workgroups.
+__device__ __forceinline__ void known_outcome(const KnownChunk& C, size_t row, int seg, int tid,
+                                              int mode, int tok, const float (&p)[4][4],
+                                              const float (&pt)[4][4], const f4v (&g)[4],
+                                              uint64_t* word) {
+  if (uint32_t(tok) / kSeg != uint32_t(seg)) return;  // (uniform)
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (seg_index(seg, q, tid, i) == uint32_t(tok)) {
+        const float png = C.png ? g[q][i] : 0.f;
+        if (word)
+          __hip_atomic_store(word, sync_word(pt[q][i], png), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        KnownRec& o = C.rec[row];
+        o.p = p[q][i];
+        o.pt = pt[q][i];
+        o.png = png;
+        o.mode = mode;
+      }
+}
+
+// The wave's counts of row's position; the thread that holds the token's entry records its count.
 __device__ __forceinline__ KnownSums known_counts(const VocabParams& P, const KnownChunk& C,
-                                                  size_t row, int seg, int tid, int mode, int tok,
-                                                  const float (&p)[4][4], const float (&pt)[4][4],
-                                                  const f4v (&g)[4]) {
+                                                  size_t row, int seg, int tid, int tok,
+                                                  const float (&p)[4][4]) {
   const int V = P.V;
   const uint32_t m = P.total - uint32_t(V);
   uint32_t sum = 0, before = 0;
@@ -1374,14 +1397,7 @@ __device__ __forceinline__ KnownSums known_counts(const VocabParams& P, const Kn
         const uint64_t key = max_key(x, t);
         best = key > best ? key : best;
       }
-      if (t == uint32_t(tok)) {
-        KnownRec& o = C.rec[row];
-        o.c = c;
-        o.p = x;
-        o.pt = pt[q][i];
-        o.png = C.png ? g[q][i] : 0.f;
-        o.mode = mode;
-      }
+      if (t == uint32_t(tok)) C.rec[row].c = c;
     }
   return KnownSums{wave_sum_u64(sum), wave_max_u64(best), wave_sum_u32(before), __any(bad) ? 1 : 0};
 }
@@ -1478,7 +1494,8 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
   R.w[1] = expf(lw[1]);
   float p[4][4], pt[4][4];
   row_probs<false>(R, v, seg, tid, p, pt);
-  const KnownSums sums = known_counts(P, C, row, seg, tid, mode, tok, p, pt, v.g);
+  known_outcome(C, row, seg, tid, mode, tok, p, pt, v.g, nullptr);
+  const KnownSums sums = known_counts(P, C, row, seg, tid, tok, p);
   // the bias-head step, then the next position's logsumexp with it
   const bool learn = P.use_head && uses_llm(mode);
   float u[4][4];
@@ -1503,10 +1520,11 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
 // stays in registers and the next position's logits and n-gram probabilities arrive while this one is
 // computed.  Between two positions the row's workgroups exchange the segments' logsumexp partials and
 // the token's probabilities (which move the mixer): each is one 64-bit word of its own per position,
-// unset at first, stored and polled at device scope, so a word that is set is also whole.  The counts
-// come after the words are out.  One stream, V = 49,152: 5.2 us a position alone and 7.2 beside a
-// transformer pass, where a launch per position took 6.2 and 9.8; encoding 4,096 tokens 42.3 to 35.1
-// ms, bound by the passes again.
+// unset at first, stored and polled at device scope, so a word that is set is also whole.  A position is
+// bound by its instructions (one wave a SIMD), so the counts are left to known_count_kernel, which
+// takes all positions at once from the probabilities that this kernel leaves.  One stream, V = 49,152:
+// 3.1 us a position alone and 4.1 beside a transformer pass (5.2 and 7.2 with the counts in it), where
+// a launch per position took 6.2 and 9.8; encoding 4,096 tokens 42.5 to 33.8 ms, bound by the passes.
 // A workgroup waits for those of its own row only, so all that a wait needs is that they get to run:
 // two workgroups fit a CU, and kRunGroups is half of what the chip holds, which leaves room for a second
 // context's.  If they still do not run (many contexts at once) a wait ends after kSpinLimit polls, a
@@ -1526,7 +1544,6 @@ __device__ __forceinline__ void sync_store(uint64_t* p, uint64_t v) {
 __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, StreamState S,
                                                                 KnownChunk C) {
   __shared__ LsePart s_lse[2][kSegWaves];
-  __shared__ KnownSums s_sums[2][kSegWaves];
   const int seg = blockIdx.x, r = blockIdx.y, nseg = gridDim.x, ns = nseg + 1;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int V = P.V, s = C.s0 + r;
@@ -1544,7 +1561,7 @@ __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, S
 #pragma unroll
     for (int q = 0; q < 4; ++q) d[q] = *reinterpret_cast<const f4v*>(src + tc[q]);
   };
-  const float* z0 = C.z + (size_t)r * V;
+  float* z0 = C.z + (size_t)r * V;
   const float* g0 = C.png ? C.png + (size_t)r * V : z0;
   RowVec v;
   f4v z2[4], z3[4], g2[4];
@@ -1554,7 +1571,7 @@ __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, S
   fetch(z2, z0 + (n > 1 ? step : 0));
   float lw[2] = {S.lw[(size_t)s * kMaxExperts], S.lw[(size_t)s * kMaxExperts + 1]};
   int mode = C.mode[r], tok = C.tok[r], mode2 = C.mode[n > 1 ? C.B + r : r];
-  int last_mode = 0, last_tok = 0;
+  int last_mode = 0;
   bool late = false;  // a wait of this wave has ended without its words
   for (int j = 0; j < n; ++j) {
     const size_t row = (size_t)j * C.B + r;
@@ -1593,14 +1610,7 @@ __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, S
     R.w[1] = expf(lw[1]);
     float p[4][4], pt[4][4], u[4][4];
     row_probs<false>(R, v, seg, tid, p, pt);
-    if (more) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (seg_index(seg, q, tid, i) == uint32_t(tok))
-            sync_store(C.sync + row * ns + nseg, sync_word(pt[q][i], C.png ? v.g[q][i] : 0.f));
-    }
+    known_outcome(C, row, seg, tid, mode, tok, p, pt, v.g, C.sync + row * ns + nseg);
     known_bias(P, P.use_head && llm, seg, tid, tok, pt, z2, v.b, u);
     const bool lse2 = more && uses_llm(mode2);
     if (lse2) {
@@ -1610,11 +1620,11 @@ __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, S
     __syncthreads();
     if (tid == 0 && lse2)
       sync_store(C.sync + (row + C.B) * ns + seg, sync_word(known_lse_sum(s_lse[j & 1])));
-    // the position before's counts are complete
-    if (tid == 64 && j > 0)
-      known_store(C, row - C.B, seg, nseg, last_tok, s_sums[(j - 1) & 1]);
-    const KnownSums sums = known_counts(P, C, row, seg, tid, mode, tok, p, pt, v.g);
-    if (lane == 0) s_sums[j & 1][w] = sums;
+    // the probabilities take the place of the logits, which are in registers two positions on
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (seg_index(seg, q, tid, 0) < uint32_t(V))
+        *reinterpret_cast<f4v*>(z0 + j * step + tc[q]) = f4v{p[q][0], p[q][1], p[q][2], p[q][3]};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       v.z[q] = z2[q];
@@ -1622,18 +1632,37 @@ __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, S
       v.g[q] = g2[q];
     }
     last_mode = mode;
-    last_tok = tok;
     mode = mode2;
     mode2 = mode3;
     tok = tok2;
   }
-  __syncthreads();
-  if (tid == 64)
-    known_store(C, (size_t)(n - 1) * C.B + r, seg, nseg, last_tok, s_sums[(n - 1) & 1]);
   if (seg == 0 && tid < 2) C.lw[((size_t)((n - 1) & 1) * C.B + r) * 2 + tid] = tid ? lw[1] : lw[0];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     if (seg_index(seg, q, tid, 0) < uint32_t(V)) *reinterpret_cast<f4v*>(b + tc[q]) = v.b[q];
+}
+
+// Count partials of every position of the chunk, a workgroup per (segment, position and row).
+__global__ __launch_bounds__(kSegThreads) void known_count_kernel(VocabParams P, KnownChunk C) {
+  __shared__ KnownSums s_sums[kSegWaves];
+  const int seg = blockIdx.x, nseg = gridDim.x, tid = threadIdx.x;
+  const size_t row = blockIdx.y;
+  if (int(row) / C.B >= C.left[int(row) % C.B]) return;
+  const float* z = C.z + row * P.V;
+  const int tok = C.tok[row];
+  float p[4][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t t0 = seg_index(seg, q, tid, 0);
+    const bool in = t0 < uint32_t(P.V);
+    const f4v x = *reinterpret_cast<const f4v*>(z + (in ? t0 : 0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[q][i] = in ? x[i] : 0.f;
+  }
+  const KnownSums sums = known_counts(P, C, row, seg, tid, tok, p);
+  if ((tid & 63) == 0) s_sums[tid >> 6] = sums;
+  __syncthreads();
+  if (tid == 0) known_store(C, row, seg, nseg, tok, s_sums);
 }
 
 // The intervals of the chunk's positions from their count partials, and the mixer weights after
@@ -2000,6 +2029,7 @@ void launch_known_steps(const VocabParams& P, const StreamState& S, const KnownC
   hipLaunchKernelGGL(known_first_kernel, grid, dim3(kSegThreads), 0, s, P, S, C);
   if (C.sync) {
     hipLaunchKernelGGL(known_run_kernel, grid, dim3(kSegThreads), 0, s, P, S, C);
+    hipLaunchKernelGGL(known_count_kernel, dim3(grid.x, C.np * C.B), dim3(kSegThreads), 0, s, P, C);
     NC_HIP(hipGetLastError());
     return;
   }

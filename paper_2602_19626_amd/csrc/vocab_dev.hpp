@@ -123,7 +123,7 @@ struct KnownRec {
 struct KnownChunk {
   int B, np, s0;
   const int32_t* left;  // [B]
-  const float* z;       // [np * B][V] logits
+  float* z;             // [np * B][V] logits (probabilities after a chain in one launch)
   float* png;           // [np * B][V] n-gram distributions, or null (no n-gram)
   int2* slots;          // [np * B][K][kSlots] slots of the order-k context (token, count)
   int2* counts;         // [np * B][K] slots used, sum of counts (0: no such context)
