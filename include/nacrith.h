@@ -49,8 +49,8 @@ enum {
   NC_F_MIXER = 1u << 3,     /* linear context mixer, section 3.6 */
   NC_F_ENSEMBLE = 1u << 4,  /* softmax-gated {LLM, n-gram orders 1..K} head trained by SGD */
   NC_F_EAGER = 1u << 5,     /* launch every kernel directly: no captured HIP graph is replayed
-                               (the batched encode replays captured chunks of its per-position
-                               steps otherwise; same bits either way) */
+                               (encode and prompts replay the captured position chains of
+                               their chunks otherwise; same bits either way) */
   NC_F_DECODE_GRAPHS = 1u << 6  /* also replay captured HIP graphs of the decode / probe
                                    transformer passes (same bits; measured about 1.5% slower
                                    than direct launches, so off by default) */

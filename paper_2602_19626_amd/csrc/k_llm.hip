@@ -1688,7 +1688,7 @@ __device__ __forceinline__ void block_store(const AttnArgs& a, const AttnItem& i
 // block hb): a state's m and l and its block hb fold on their own (the other blocks only scale
 // alike), so the four blocks' folds run side by side.  Wave w folds the quads of the item's w-th
 // group (their states loaded together) and leaves the group state in LDS; wave 0 then folds the
-// groups in order.  The folds are the sequential kernel's, in the same order, so the output is
+// groups in order.  The folds are the group kernel's, in the same order, so the output is
 // the same.
 constexpr int FOLD_WAVES = (MAXQ + GQ - 2) / GQ + 1;  // groups an item may span
 template <int PO>
