@@ -37,10 +37,12 @@ KERNEL_SOURCES = {"qkv": "k_llm.hip", "attn": "k_llm.hip", "oproj": "k_llm.hip",
 # rocprofv3 kernel names of each class (demangled); oproj and down share one kernel and have none
 KERNEL_NAME_RE = {"qkv": r"gemm_\w*kernel<\d+, \d+, 3\b", "gateup": r"gemm_\w*kernel<\d+, \d+, 2\b",
                   "lmhead": r"gemm_\w*kernel<\d+, \d+, 0\b", "attn": r"attention_\w*kernel",
-                  "vocab": r"(vocab_\w*|ensemble_bias)_kernel", "ngram": r"ngram_\w*_kernel"}
+                  "vocab": r"(vocab_\w*|ensemble_bias|known_(first|step|run|count))_kernel",
+                  "ngram": r"(ngram_\w*|known_(advance|dense|fix|tokens|commit))_kernel"}
 # one dispatch per class launch matches these (a class launch may run several kernels)
-KERNEL_PRIMARY_RE = {"attn": r"attention_(quad|chunk|seq)_kernel", "vocab": r"vocab_lse_kernel",
-                     "ngram": r"ngram_dense_kernel"}
+KERNEL_PRIMARY_RE = {"attn": r"attention_(quad|chunk|group|item|seq)_kernel",
+                     "vocab": r"(vocab_lse|known_first)_kernel",
+                     "ngram": r"(ngram|known)_dense_kernel"}
 PROBE_RE = r"neg"   # the plain streaming probe kernel (torch.neg: reads N bytes, writes N bytes)
 
 
