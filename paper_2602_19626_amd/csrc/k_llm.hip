@@ -2211,7 +2211,8 @@ void launch_attention(int prec_att, int prec_out, const AttnArgs& a, bool parall
   if (a.n_items <= 0) return;
   NC_CHECK(a.hd % 16 == 0 && a.hd <= HDMAX, NC_E_INVALID, "head_dim must be 16..64, x16");
   NC_CHECK(attention_quads(a.ctx_len) <= MAXQ, NC_E_INVALID, "context window too large");
-  NC_CHECK(a.ring % 16 == 0, NC_E_INVALID, "ring must be a multiple of 16");
+  NC_CHECK(a.ring % 16 == 0 && a.ring >= KCH, NC_E_INVALID,
+           "ring must be a multiple of 16 and hold a chunk");
   NC_CHECK(a.n_groups > 0 && a.n_groups <= a.n_items, NC_E_INVALID, "attention groups");
   if (parallel)
     NC_CHECK(a.ws && a.ws_bytes >= attention_ws_bytes(a.n_items), NC_E_INVALID,

@@ -1493,7 +1493,9 @@ nc_status nc_create(const nc_config* cfg, const float* w, nc_ctx** out) {
     c->F = cfg->d_ffn;
     c->V = cfg->vocab;
     c->nl = cfg->n_layers;
-    c->R = cfg->ctx_len + cfg->slide;  // ring: any batch spanning < slide positions is safe
+    // ring: any batch spanning < slide positions is safe; no shorter than an attention chunk, so that
+    // a chunk's slots are distinct and one subtraction takes any of them back into the ring
+    c->R = std::max(cfg->ctx_len + cfg->slide, kAttnChunk);
     const size_t d = c->d, nqkv = (size_t)(c->hq + 2 * c->hk) * c->hd, F = c->F;
     // flat layout: E, per layer (attn_norm, Wq, Wk, Wv, Wo, mlp_norm, Wg, Wu, Wd), final_norm
     const float* p = w;

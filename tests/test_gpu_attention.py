@@ -58,3 +58,39 @@ def test_many_streams_of_uneven_rows(prec):
         assert one.encode_stream([streams[i]])[0][0] == data[i], i
     back = ctx.decode_stream(data, [len(s) for s in streams])
     assert all(np.array_equal(a, b) for a, b in zip(back, streams))
+
+
+@pytest.mark.parametrize("ctx_len,slide,heads", [(8, 8, 8), (12, 4, 8), (16, 16, 4), (32, 16, 4),
+                                                 (24, 24, 8), (32, 32, 4)])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_contexts_shorter_than_a_chunk(ctx_len, slide, heads, prec):
+    """Contexts whose ctx_len + slide is below the 64 keys of an attention chunk, or just there: streams
+    of several items a group, one stream alone, one row a pass and the decoder agree, and the
+    distributions are the oracle's (float32 against float64: 1e-5; BF16 passes only among themselves)."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import paper_2602_19626_amd as nc
+    from oracle import pipeline as op
+    shape = dataclasses.replace(synth.TINY, ctx_len=ctx_len, slide=slide, n_heads=heads)
+    w = synth.make_weights(shape, 3)
+    flat = synth.flat_weights(shape, w)
+    n_streams = 9   # 36 items in 18 groups a pass (16 rows or 8, 2 or 4 query heads a kv head)
+    toks = [synth.make_stream(5 * (ctx_len + slide) + 3 * i, shape.vocab, seed=i, span=(4, 32))
+            for i in range(n_streams)]
+    kw = dict(ngram_order=3, precision=prec, skip="none", mix_init="uniform", warmup=20)
+    ctx = nc.Context(nc.make_config(shape, max_streams=n_streams, **kw), flat)
+    data, _ = ctx.encode_stream(toks)
+    back = ctx.decode_stream(data, [len(t) for t in toks])
+    assert all(np.array_equal(a, b) for a, b in zip(back, toks))
+    one = nc.Context(nc.make_config(shape, **kw), flat)
+    assert [one.encode_stream([t])[0][0] for t in toks] == data
+    t = toks[-1]
+    pos = [0, 1, ctx_len - 1, ctx_len, ctx_len + slide + 1, len(t) - 1]
+    ref = op.encode(op.Settings(vocab=shape.vocab, ngram_order=3, mix_init="uniform",
+                                skip="none", use_skip=False, warmup=20), shape, w,
+                    t, record=pos, block=1)
+    one.reset(1, len(t) + 1)
+    for i in sorted(pos):
+        p = one.probs_for_context(0, t[:i])
+        if prec == "fp32":
+            assert np.max(np.abs(p - ref.records[i]["p"])) < 1e-5, i
