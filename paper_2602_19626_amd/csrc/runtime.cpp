@@ -1108,8 +1108,10 @@ void known_chain(nc_ctx* c, const KnownChunk& C) {
     return;
   }
   auto num = [](size_t v) { return reinterpret_cast<const void*>(v); };
-  const std::vector<const void*> key{num(C.np), num(C.B), num(C.s0), C.left, C.z, C.png, C.tok,
-                                     C.mode, C.lse, C.lw, C.segs, C.rec, C.sync, c->S.b, c->S.lw};
+  // (every size and buffer that launch_known_steps hands to its kernels: a buffer that grows moves, and
+  // the others may come back at their old addresses)
+  const std::vector<const void*> key{num(C.np), num(C.B), num(C.s0), C.left, C.z, C.png, C.tok, C.mode,
+                                     C.lse, C.sync, C.lw, C.segs, C.rec, C.bad, c->S.b, c->S.lw};
   if (c->egraphs.size() >= 64 && !c->egraphs.count(key)) {
     NC_HIP(hipStreamSynchronize(c->st3));
     chain_graphs_clear(c);
