@@ -212,6 +212,19 @@ nc_status nc_decode_stream(nc_ctx* ctx, uint32_t n_streams, const uint8_t* const
 /* Statistics of the last nc_encode_stream / nc_decode_stream call. */
 nc_status nc_get_stats(const nc_ctx* ctx, nc_stats* out);
 
+/* Encode and prompts (nc_probs_for_context) take the tokens they are given in chunks, and go back to
+ * one coding step per token, from the reset state, where a call's chunks cannot be used: the same
+ * bits, at a step's speed.  The calls of a context for which they did: */
+typedef struct nc_fallbacks {
+  uint64_t invalid;  /* some distribution was invalid */
+  uint64_t expired;  /* the workgroups that code one stream together did not get to run together in
+                        time (more contexts at work on the GPU than it holds) */
+} nc_fallbacks;
+nc_status nc_get_fallbacks(const nc_ctx* ctx, nc_fallbacks* out);
+/* Polls before those workgroups give up waiting for one another; at most, and by default, 2^18 (a few
+ * tenths of a second). */
+nc_status nc_chunk_polls(nc_ctx* ctx, uint32_t max_polls);
+
 /* ---- measurement ----------------------------------------------------------------------------
  * Kernel classes of the pipeline.  With profiling on for one class, the library records a pair
  * of HIP events on its own stream around every launch of that class and accumulates the elapsed

@@ -14,7 +14,7 @@ from . import _lib
 from ._lib import (NC_BF16, NC_F_DECODE_GRAPHS, NC_F_EAGER, NC_F_ENSEMBLE, NC_F_HEAD,
                    NC_F_MIXER, NC_F_NGRAM, NC_F_SKIP, NC_FP8,
                    NC_FP32, NC_SKIP_ENTROPY, NC_SKIP_NONE, NC_SKIP_PMAX, NacrithError, NcConfig,
-                   NcProbe, NcStats, check, lib)
+                   NcFallbacks, NcProbe, NcStats, check, lib)
 
 __all__ = ["quantize_cdf24", "quantize_cdf24_noalloc", "cdf_interval", "encode_bound", "ac_encode", "ac_decode_static",
            "make_config", "Context", "NacrithError", "lib"]
@@ -251,6 +251,16 @@ class Context:
         k = NcKstat()
         check(lib().nc_profile_read(self._h, KERNEL_CLASSES[kernel_class], C.byref(k)))
         return {f: getattr(k, f) for f, _ in NcKstat._fields_}
+
+    def fallbacks(self) -> dict:
+        """Calls whose known tokens went back from chunks to one step per token, by reason."""
+        f = NcFallbacks()
+        check(lib().nc_get_fallbacks(self._h, C.byref(f)))
+        return {k: getattr(f, k) for k, _ in NcFallbacks._fields_}
+
+    def chunk_polls(self, max_polls: int):
+        """Polls before the workgroups that code one stream together give up (at most 2^18)."""
+        check(lib().nc_chunk_polls(self._h, int(max_polls)))
 
     def stats(self) -> dict:
         s = NcStats()

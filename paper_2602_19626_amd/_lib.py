@@ -44,6 +44,10 @@ class NcStats(C.Structure):
                 ("graph_replays", C.c_uint64), ("graph_captures", C.c_uint64)]
 
 
+class NcFallbacks(C.Structure):
+    _fields_ = [("invalid", C.c_uint64), ("expired", C.c_uint64)]
+
+
 class NcTile(C.Structure):
     _fields_ = [("gemm", C.c_int32), ("max_rows", C.c_int32), ("kind", C.c_int32),
                 ("mb", C.c_int32), ("waves", C.c_int32), ("us_best", C.c_float),
@@ -80,6 +84,8 @@ _SIG = {
     "nc_encode_stream": (C.c_int, [_P, C.c_uint32, _P, _P, _P, _P, _P, _P]),
     "nc_decode_stream": (C.c_int, [_P, C.c_uint32, _P, _P, _P, _P]),
     "nc_get_stats": (C.c_int, [_P, C.POINTER(NcStats)]),
+    "nc_get_fallbacks": (C.c_int, [_P, C.POINTER(NcFallbacks)]),
+    "nc_chunk_polls": (C.c_int, [_P, C.c_uint32]),
     "nc_profile": (C.c_int, [_P, C.c_int32, C.c_uint32]),
     "nc_autotune": (C.c_int, [_P, C.c_uint32, C.c_uint32, C.c_void_p, C.c_uint32,
                               C.POINTER(C.c_uint32)]),

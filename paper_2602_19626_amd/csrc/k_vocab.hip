@@ -1527,12 +1527,10 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
 // a launch per position took 6.2 and 9.8; encoding 4,096 tokens 42.5 to 33.8 ms, bound by the passes.
 // A workgroup waits for those of its own row only, so all that a wait needs is that they get to run:
 // two workgroups fit a CU, and kRunGroups is half of what the chip holds, which leaves room for a second
-// context's.  If they still do not run (many contexts at once) a wait ends after kSpinLimit polls, a
-// few tenths of a second, and raises the flag of an invalid distribution, with which the caller takes
-// the positions one by one.  More rows than that gain less: 33 BF16 streams of 1,000 tokens (396
+// context's.  If they still do not run (many contexts at once) a wait ends after C.polls polls, a
+// few tenths of a second, and raises its flag, with which the caller takes the positions one by one.  More rows than that gain less: 33 BF16 streams of 1,000 tokens (396
 // workgroups) 39.5 ms, or 36.8 in one launch; 64 streams 68.1 and 68.2, 200 streams 66.4 and 68.0.
 constexpr int kRunGroups = 256;
-constexpr int kSpinLimit = 1 << 18;
 
 __device__ __forceinline__ uint64_t sync_load(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1590,9 +1588,9 @@ __global__ __launch_bounds__(kSegThreads) void known_run_kernel(VocabParams P, S
       if (j > 0) out = sync_load(words - (size_t)C.B * ns + nseg);
       const bool wait = (llm && part == kUnset) || out == kUnset;
       if (__builtin_amdgcn_ballot_w64(wait) == 0) break;
-      if (late || spin >= kSpinLimit) {
+      if (late || spin >= C.polls) {
         late = true;
-        if (lane == 0) atomicOr(C.bad, 1);
+        if (lane == 0) atomicOr(C.bad, KB_EXPIRED);
         break;
       }
       __builtin_amdgcn_s_sleep(1);
@@ -1682,7 +1680,7 @@ __global__ __launch_bounds__(64) void known_finish_kernel(VocabParams P, StreamS
   uint32_t cl = q.start + o.before, c = o.c;
   if (q.argmax / kSeg == seg && q.argmax < tok) cl += uint32_t(q.residual);
   if (q.argmax == tok) c += uint32_t(q.residual);
-  if (q.status) atomicOr(C.bad, 1);
+  if (q.status) atomicOr(C.bad, KB_INVALID);
   if (C.iv) {
     const size_t at = (size_t)s * S.maxT + p0 + j;
     C.iv[2 * at] = cl;

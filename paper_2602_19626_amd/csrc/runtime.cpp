@@ -133,7 +133,9 @@ struct nc_ctx {
     DevBuf<uint64_t> sync;
     hipEvent_t ngram = nullptr, logits = nullptr, done = nullptr;
   } kb[2];
-  DevBuf<int32_t> kbad;  // set by a chunk with an invalid distribution
+  DevBuf<int32_t> kbad;  // KB_* bits of the call's chunks
+  int polls = kChunkPolls;
+  nc_fallbacks fallbacks{};
   // passes over known tokens, two in turn: the staged inputs, and the pass's output-layer operand
   // rows with their scales where several chunks follow (see keep_rows)
   struct StageSlot {
@@ -1111,7 +1113,8 @@ void known_chain(nc_ctx* c, const KnownChunk& C) {
   // (every size and buffer that launch_known_steps hands to its kernels: a buffer that grows moves, and
   // the others may come back at their old addresses)
   const std::vector<const void*> key{num(C.np), num(C.B), num(C.s0), C.left, C.z, C.png, C.tok, C.mode,
-                                     C.lse, C.sync, C.lw, C.segs, C.rec, C.bad, c->S.b, c->S.lw};
+                                     C.lse, C.sync, C.lw, C.segs, C.rec, C.bad, num(C.polls), c->S.b,
+                                     c->S.lw};
   if (c->egraphs.size() >= 64 && !c->egraphs.count(key)) {
     NC_HIP(hipStreamSynchronize(c->st3));
     chain_graphs_clear(c);
@@ -1175,6 +1178,7 @@ KnownChunk known_begin(nc_ctx* c, KnownRun& run, const nc_ctx::StageSlot& slot, 
   C.iv = intervals ? c->iv.p : nullptr;
   C.ptok = intervals ? c->ptok.p : nullptr;
   C.bad = c->kbad.p;
+  C.polls = c->polls;
   NC_HIP(hipStreamWaitEvent(c->st2, k.done, 0));  // the set's last chunk has been consumed
   NC_HIP(hipStreamWaitEvent(c->st2, slot.up, 0));
   NC_HIP(hipMemcpyAsync(k.left.p, slot.d.p + off_left, size_t(B) * 4, hipMemcpyDeviceToDevice,
@@ -1223,6 +1227,18 @@ void known_end(nc_ctx* c, const KnownRun& run, const KnownChunk& C, const nc_ctx
   NC_HIP(hipEventRecord(k.done, c->st3));
 }
 
+// Whether the results of the call's chunks can be used; if not, the caller codes step by step.
+bool known_ok(nc_ctx* c) {
+  int32_t bad = 0;
+  d2h(c, &bad, c->kbad.p, 1);
+  // (after a wait that gave up, the values that it was for are made up and may well be invalid)
+  if (bad & KB_EXPIRED)
+    c->fallbacks.expired += 1;
+  else if (bad)
+    c->fallbacks.invalid += 1;
+  return bad == 0;
+}
+
 // Transformer rows of x positions [a, a + C) of every stream with a token there (teacher forcing);
 // off[k]: the pass row of stream k's position a.
 std::vector<RowMeta> known_rows(const std::vector<const int32_t*>& tok,
@@ -1238,8 +1254,8 @@ std::vector<RowMeta> known_rows(const std::vector<const int32_t*>& tok,
 }
 
 // Encode from reset streams whose tokens are in hist (lengths not increasing): intervals and
-// probabilities of every position into iv and ptok, in chunks of known tokens.  False if some
-// distribution was invalid; nothing is then to be used.
+// probabilities of every position into iv and ptok, in chunks of known tokens.  False: nothing is to be
+// used (known_ok).
 bool encode_known(nc_ctx* c, const std::vector<const int32_t*>& tok,
                   const std::vector<size_t>& len) {
   const size_t C = c->cfg.slide, maxn = len.empty() ? 0 : len[0];
@@ -1292,13 +1308,11 @@ bool encode_known(nc_ctx* c, const std::vector<const int32_t*>& tok,
     NC_HIP(hipEventRecord(c->slots[slot].done, c->st3));
   }
   sync(c);
-  int32_t bad = 0;
-  d2h(c, &bad, c->kbad.p, 1);
-  return bad == 0;
+  return known_ok(c);
 }
 
 // The same, one coding step per position (the ensemble head, and streams with an invalid
-// distribution): every position's counts take its known token.
+// distribution or a chain that could not run): every position's counts take its known token.
 void encode_steps(nc_ctx* c, const std::vector<const int32_t*>& tok,
                   const std::vector<size_t>& len) {
   const size_t C = c->cfg.slide, maxn = len.empty() ? 0 : len[0];
@@ -1381,7 +1395,8 @@ void reset_stream(nc_ctx* c, int s) {
 // logits come from passes of up to `slide` rows and their coding steps run as chunks of known
 // tokens: one launch per token in place of a transformer pass.  The passes also append position n,
 // whose distribution the caller asks for.  Bits are those of commit_steps, which takes over
-// (from a reset stream) if a distribution is invalid: its models stop at such a position.
+// (from a reset stream) if the chunks' results cannot be used; where a distribution is invalid,
+// its models stop at that position.
 void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
   auto& h = c->hhist[s];
   if (c->cfg.features & NC_F_ENSEMBLE) return commit_steps(c, s, tokens, n);
@@ -1420,9 +1435,7 @@ void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
   sync(c);
   h.insert(h.end(), tokens + first, tokens + n);
   c->appended[s] = int(n) + 1;
-  int32_t bad = 0;
-  d2h(c, &bad, c->kbad.p, 1);
-  if (bad) {
+  if (!known_ok(c)) {
     reset_stream(c, s);
     return commit_steps(c, s, tokens, n);
   }
@@ -1909,6 +1922,20 @@ nc_status nc_decode_stream(nc_ctx* c, uint32_t ns, const uint8_t* const* in,
     for (int s = 0; s < n; ++s) c->stats.tokens += n_tokens[s];
     c->stats.seconds =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  });
+}
+
+nc_status nc_get_fallbacks(const nc_ctx* c, nc_fallbacks* out) {
+  return guard([&] {
+    NC_CHECK(c && out, NC_E_INVALID, "NULL argument");
+    *out = c->fallbacks;
+  });
+}
+
+nc_status nc_chunk_polls(nc_ctx* c, uint32_t max_polls) {
+  return guard([&] {
+    NC_CHECK(c, NC_E_INVALID, "NULL context");
+    c->polls = int(std::min<uint32_t>(max_polls, kChunkPolls));
   });
 }
 

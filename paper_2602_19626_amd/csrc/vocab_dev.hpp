@@ -137,8 +137,14 @@ struct KnownChunk {
   KnownRec* rec;        // [np * B]
   uint32_t* iv;         // [S][maxT][2] intervals, or null
   float* ptok;          // [S][maxT]
-  int32_t* bad;         // set if a position's distribution is invalid
+  int32_t* bad;         // bits below, set if the chunk's results are not to be used
+  int polls;            // polls before a wait between the workgroups of a row gives up
 };
+enum {
+  KB_INVALID = 1,  // a position's distribution is invalid
+  KB_EXPIRED = 2   // a wait gave up
+};
+constexpr int kChunkPolls = 1 << 18;  // a few tenths of a second
 // The n-gram side of a chunk: table updates, every position's distribution and mode, counts.
 void launch_known_ngram(const VocabParams& P, const StreamState& S, const KnownChunk& C, int p0,
                         hipStream_t s);
