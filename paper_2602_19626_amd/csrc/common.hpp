@@ -27,12 +27,16 @@ void set_last_error(const std::string& msg);
   throw Error{st, std::string(buf)};
 }
 
+// (the failure is taken from the runtime's last error, where the check after a later launch would
+// find it again)
 #define NC_HIP(call)                                                                    \
   do {                                                                                  \
     hipError_t e_ = (call);                                                             \
-    if (e_ != hipSuccess)                                                               \
+    if (e_ != hipSuccess) {                                                             \
+      (void)hipGetLastError();                                                          \
       ::nc::fail(e_ == hipErrorOutOfMemory ? NC_E_NOMEM : NC_E_DEVICE, "%s: %s (%s:%d)", \
                  #call, hipGetErrorString(e_), __FILE__, __LINE__);                     \
+    }                                                                                   \
   } while (0)
 
 #define NC_CHECK(cond, st, ...)            \

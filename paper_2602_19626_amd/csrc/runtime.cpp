@@ -281,6 +281,7 @@ void* pinned(nc_ctx* c, size_t bytes) {
   if (bytes > c->pin_bytes) {
     if (c->pin) NC_HIP(hipHostFree(c->pin));
     c->pin = nullptr;
+    c->pin_bytes = 0;
     NC_HIP(hipHostMalloc(&c->pin, bytes, hipHostMallocDefault));
     c->pin_bytes = bytes;
   }
@@ -421,6 +422,7 @@ void build_rope(nc_ctx* c, int max_pos) {
       t[((size_t)p * h2 + i) * 2 + 0] = (float)std::cos(a);
       t[((size_t)p * h2 + i) * 2 + 1] = (float)std::sin(a);
     }
+  c->rope_pos = 0;  // (the old table is gone if the new one does not fit)
   c->rope.alloc(t.size());
   NC_HIP(hipMemcpy(c->rope.p, t.data(), t.size() * 4, hipMemcpyHostToDevice));
   c->rope_pos = max_pos;
@@ -429,6 +431,7 @@ void build_rope(nc_ctx* c, int max_pos) {
 void ensure_rows(nc_ctx* c, int rows) {
   if (rows <= c->rows_alloc) return;
   const int r = std::max(rows, 64);
+  c->rows_alloc = 0;  // until all of them have grown
   c->x.alloc((size_t)r * c->d);
   c->xinv.alloc(r);
   c->xss.alloc((size_t)r * (c->d / 16));
@@ -578,6 +581,7 @@ uint8_t* upload_stage(nc_ctx* c, const Stage& s) {
   if (n > c->spin_bytes) {
     if (c->spin) NC_HIP(hipHostFree(c->spin));
     c->spin = nullptr;
+    c->spin_bytes = 0;
     NC_HIP(hipHostMalloc(&c->spin, n * 2, hipHostMallocDefault));
     c->spin_bytes = n * 2;
   }
@@ -957,6 +961,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
            c->cfg.max_streams);
   NC_CHECK(maxT >= 1, NC_E_INVALID, "max_tokens must be >= 1");
   sync(c);  // an earlier call that failed may have left work on the streams
+  c->n_streams = 0;  // no stream can be used if this call fails
   const int K = c->cfg.ngram_order;
   const int V = c->V;
   if (n > c->S_alloc || maxT > c->T_alloc) {
@@ -964,6 +969,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
     int cap = 1;
     while (cap < 2 * (Ta + 1)) cap <<= 1;
     const int maxctx = std::min(Ta, c->cfg.ngram_max_contexts);
+    c->S_alloc = c->T_alloc = 0;  // until every buffer has grown
     c->b.alloc((size_t)Sa * V);
     c->png.alloc((size_t)Sa * V);
     if (c->cfg.features & NC_F_ENSEMBLE) c->pk.alloc((size_t)Sa * K * V);
