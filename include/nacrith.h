@@ -219,11 +219,16 @@ typedef struct nc_fallbacks {
   uint64_t invalid;  /* some distribution was invalid */
   uint64_t expired;  /* the workgroups that code one stream together did not get to run together in
                         time (more contexts at work on the GPU than it holds) */
+  uint64_t memory;   /* the chunks' buffers did not fit, in the device or in their limit */
 } nc_fallbacks;
 nc_status nc_get_fallbacks(const nc_ctx* ctx, nc_fallbacks* out);
 /* Polls before those workgroups give up waiting for one another; at most, and by default, 2^18 (a few
  * tenths of a second). */
 nc_status nc_chunk_polls(nc_ctx* ctx, uint32_t max_polls);
+/* Most device memory, in bytes, that the chunks' buffers may take (default: no limit).  They grow to
+ * the largest call so far and are kept for the next, until nc_destroy or a limit below what they hold:
+ * two sets of logits and n-gram distributions, of up to slide x vocab floats each for prompts. */
+nc_status nc_chunk_bytes(nc_ctx* ctx, uint64_t max_bytes);
 
 /* ---- measurement ----------------------------------------------------------------------------
  * Kernel classes of the pipeline.  With profiling on for one class, the library records a pair

@@ -262,6 +262,10 @@ class Context:
         """Polls before the workgroups that code one stream together give up (at most 2^18)."""
         check(lib().nc_chunk_polls(self._h, int(max_polls)))
 
+    def chunk_bytes(self, max_bytes: int):
+        """Most device memory that the buffers of known-token chunks may take."""
+        check(lib().nc_chunk_bytes(self._h, int(max_bytes)))
+
     def stats(self) -> dict:
         s = NcStats()
         check(lib().nc_get_stats(self._h, C.byref(s)))

@@ -45,7 +45,7 @@ class NcStats(C.Structure):
 
 
 class NcFallbacks(C.Structure):
-    _fields_ = [("invalid", C.c_uint64), ("expired", C.c_uint64)]
+    _fields_ = [("invalid", C.c_uint64), ("expired", C.c_uint64), ("memory", C.c_uint64)]
 
 
 class NcTile(C.Structure):
@@ -86,6 +86,7 @@ _SIG = {
     "nc_get_stats": (C.c_int, [_P, C.POINTER(NcStats)]),
     "nc_get_fallbacks": (C.c_int, [_P, C.POINTER(NcFallbacks)]),
     "nc_chunk_polls": (C.c_int, [_P, C.c_uint32]),
+    "nc_chunk_bytes": (C.c_int, [_P, C.c_uint64]),
     "nc_profile": (C.c_int, [_P, C.c_int32, C.c_uint32]),
     "nc_autotune": (C.c_int, [_P, C.c_uint32, C.c_uint32, C.c_void_p, C.c_uint32,
                               C.POINTER(C.c_uint32)]),

@@ -120,7 +120,7 @@ struct nc_ctx {
   size_t spin_bytes = 0;
   // step buffers
   DevBuf<float> z;
-  DevBuf<float> zseg;  // tuner: output-layer scratch
+  DevBuf<float> zseg;  // logits of several positions coded step by step; tuner: output-layer scratch
   // buffers of a chunk of known tokens (KnownChunk), and the events that order its streams
   struct KnownBufs {
     DevBuf<float> z, png, lw;
@@ -132,9 +132,15 @@ struct nc_ctx {
     DevBuf<KnownRec> rec;
     DevBuf<uint64_t> sync;
     hipEvent_t ngram = nullptr, logits = nullptr, done = nullptr;
+    template <class F>
+    void each(F&& f) {
+      f(z), f(png), f(lw), f(slots), f(counts), f(ngp), f(tok), f(mode), f(left), f(lse), f(segs);
+      f(rec), f(sync);
+    }
   } kb[2];
   DevBuf<int32_t> kbad;  // KB_* bits of the call's chunks
   int polls = kChunkPolls;
+  size_t chunk_bytes = SIZE_MAX;  // most that the chunk buffers may take
   nc_fallbacks fallbacks{};
   // passes over known tokens, two in turn: the staged inputs, and the pass's output-layer operand
   // rows with their scales where several chunks follow (see keep_rows)
@@ -164,6 +170,7 @@ struct nc_ctx {
   // host mirrors
   std::vector<std::vector<int32_t>> hhist;  // committed tokens per stream
   std::vector<int> appended;                // x positions in the KV cache per stream
+  std::vector<uint8_t> lost;                // streams that a call left part way: unusable until reset
   nc_stats stats{};
   VocabParams vp{};
   // measurement: events around the launches of the enabled kernel classes
@@ -240,14 +247,7 @@ nc_ctx::~nc_ctx() {
     (void)hipEventDestroy(pr.first.second);
   }
   for (KnownBufs& k : kb) {
-    for (DevBuf<float>* q : {&k.z, &k.png, &k.lw}) q->release();
-    for (DevBuf<int2>* q : {&k.slots, &k.counts}) q->release();
-    for (DevBuf<int32_t>* q : {&k.tok, &k.mode, &k.left}) q->release();
-    k.ngp.release();
-    k.lse.release();
-    k.segs.release();
-    k.rec.release();
-    k.sync.release();
+    k.each([](auto& b) { b.release(); });
     for (hipEvent_t e : {k.ngram, k.logits, k.done})
       if (e) (void)hipEventDestroy(e);
   }
@@ -1025,6 +1025,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
   sync(c);
   c->hhist.assign(n, {});
   c->appended.assign(n, 0);
+  c->lost.assign(n, 0);
 }
 
 StepArgs step_args(nc_ctx* c, int B, bool decode) {
@@ -1061,26 +1062,45 @@ void vocab_commit_step(nc_ctx* c, const StepArgs& A) {
 
 // ---- passes over known tokens ---------------------------------------------------------------
 
-// Output-layer rows of a chunk that runs beside the next one's output layer.
+size_t known_bytes(nc_ctx* c) {
+  size_t bytes = 0;
+  for (nc_ctx::KnownBufs& k : c->kb) k.each([&](auto& b) { bytes += b.n * sizeof(*b.p); });
+  return bytes;
+}
+
+// Give the chunks' buffers back (after whatever is queued has run).
+void known_release(nc_ctx* c) {
+  sync(c);
+  for (nc_ctx::KnownBufs& k : c->kb) k.each([](auto& b) { b.release(); });
+}
+
+// The chunk set of parity par for np positions of B streams.
 nc_ctx::KnownBufs& known_bufs(nc_ctx* c, int par, int np, int B) {
   nc_ctx::KnownBufs& k = c->kb[par];
   const size_t n = size_t(np) * B, V = c->V, K = c->cfg.ngram_order;
   const size_t nseg = ceil_div(V, kSeg);
-  k.z.alloc(n * V);
+  size_t bytes = known_bytes(c);
+  auto grow = [&](auto& b, size_t count) {
+    if (count <= b.n) return;
+    bytes += (count - b.n) * sizeof(*b.p);
+    NC_CHECK(bytes <= c->chunk_bytes, NC_E_NOMEM, "chunk buffers exceed their limit");
+    b.alloc(count);
+  };
+  grow(k.z, n * V);
   if (ngram_on(c)) {
-    k.png.alloc(n * V);
-    k.slots.alloc(n * K * kSlots);
-    k.counts.alloc(n * K);
-    k.ngp.alloc(n * nseg);
+    grow(k.png, n * V);
+    grow(k.slots, n * K * kSlots);
+    grow(k.counts, n * K);
+    grow(k.ngp, n * nseg);
   }
-  k.lw.alloc(size_t(2) * B * 2);
-  k.tok.alloc(n);
-  k.mode.alloc(n);
-  k.left.alloc(B);
-  k.lse.alloc(size_t(2) * B * nseg);
-  if (known_in_one_launch(B, c->V)) k.sync.alloc(n * (nseg + 1));
-  k.segs.alloc(n * nseg + 16);
-  k.rec.alloc(n);
+  grow(k.lw, size_t(2) * B * 2);
+  grow(k.tok, n);
+  grow(k.mode, n);
+  grow(k.left, B);
+  grow(k.lse, size_t(2) * B * nseg);
+  if (known_in_one_launch(B, c->V)) grow(k.sync, n * (nseg + 1));
+  grow(k.segs, n * nseg + 16);
+  grow(k.rec, n);
   return k;
 }
 
@@ -1327,7 +1347,6 @@ void encode_steps(nc_ctx* c, const std::vector<const int32_t*>& tok,
   std::iota(ids.begin(), ids.end(), 0);
   set_steprows(c, ids.data(), ids.size());
   const bool given = ngram_on(c) && !(c->cfg.features & NC_F_ENSEMBLE);
-  nc_ctx::KnownBufs& k = c->kb[0];
   for (size_t a = 0; a < maxn; a += C) {
     std::vector<int> off(n, 0);
     PassPlan plan = plan_pass(c, known_rows(tok, len, a, C, off));
@@ -1346,13 +1365,13 @@ void encode_steps(nc_ctx* c, const std::vector<const int32_t*>& tok,
     run_pass(c, plan, dst);
     const int32_t* seg_ar = reinterpret_cast<const int32_t*>(dst + off_ar);
     const int pc = std::max(1, std::min(int(seg_len), kEncodeHeadRows / n));
-    k.z.alloc(size_t(pc) * n * c->V);
+    c->zseg.alloc(size_t(pc) * n * c->V);
     for (size_t i0 = 0; i0 < seg_len; i0 += pc) {
       const int np = int(std::min(size_t(pc), seg_len - i0));
-      run_lm_head(c, c->yb.p, c->xinv.p, seg_ar + i0 * n, np * n, k.z.p);
+      run_lm_head(c, c->yb.p, c->xinv.p, seg_ar + i0 * n, np * n, c->zseg.p);
       for (size_t i = i0; i < i0 + np; ++i) {
         StepArgs A = step_args(c, active[i], false);
-        A.z = k.z.p + (i - i0) * n * size_t(c->V);
+        A.z = c->zseg.p + (i - i0) * n * size_t(c->V);
         A.step_out = nullptr;
         A.iv = c->iv.p;
         A.ptok = c->ptok.p;
@@ -1397,19 +1416,10 @@ void reset_stream(nc_ctx* c, int s) {
   c->appended[s] = 0;
 }
 
-// Commit tokens[done .. n) of stream s (steprows holds s).  The tokens are known, so the positions'
-// logits come from passes of up to `slide` rows and their coding steps run as chunks of known
-// tokens: one launch per token in place of a transformer pass.  The passes also append position n,
-// whose distribution the caller asks for.  Bits are those of commit_steps, which takes over
-// (from a reset stream) if the chunks' results cannot be used; where a distribution is invalid,
-// its models stop at that position.
-void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
-  auto& h = c->hhist[s];
-  if (c->cfg.features & NC_F_ENSEMBLE) return commit_steps(c, s, tokens, n);
-  // a position that is in the cache already has its output-layer operand in hlast only
-  if (c->appended[s] > int(h.size())) commit_steps(c, s, tokens, h.size() + 1);
-  if (h.size() == n) return;
-  const int first = int(h.size()), C = c->cfg.slide;
+// Tokens h .. n - 1 of stream s, h of them committed, in chunks, and the pass rows up to position n.
+// False: nothing is to be used (known_ok).
+bool commit_chunks(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
+  const int first = int(c->hhist[s].size()), C = c->cfg.slide;
   h2d(c, c->hist.p + (size_t)s * c->T_alloc + first, tokens + first, n - first);
   NC_HIP(hipMemsetAsync(c->kbad.p, 0, 4, c->st));
   sync(c);
@@ -1439,14 +1449,41 @@ void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
     NC_HIP(hipEventRecord(c->slots[slot].done, np > 0 ? c->st3 : c->st));
   }
   sync(c);
-  h.insert(h.end(), tokens + first, tokens + n);
-  c->appended[s] = int(n) + 1;
-  if (!known_ok(c)) {
-    reset_stream(c, s);
-    return commit_steps(c, s, tokens, n);
+  return known_ok(c);
+}
+
+// Commit tokens[done .. n) of stream s (steprows holds s).  The tokens are known, so the positions'
+// logits come from passes of up to `slide` rows and their coding steps run as chunks of known
+// tokens: one launch per token in place of a transformer pass.  The passes also append position n,
+// whose distribution the caller asks for.  Bits are those of commit_steps, which takes over
+// (from a reset stream) if the chunks' results cannot be used or their buffers do not fit; where a
+// distribution is invalid, its models stop at that position.  A failure part way leaves the models
+// somewhere between the host's history and n: the stream then stays lost until it is reset.
+void commit_tokens(nc_ctx* c, int s, const int32_t* tokens, size_t n) {
+  auto& h = c->hhist[s];
+  if (c->cfg.features & NC_F_ENSEMBLE) return commit_steps(c, s, tokens, n);
+  // a position that is in the cache already has its output-layer operand in hlast only
+  if (c->appended[s] > int(h.size())) commit_steps(c, s, tokens, h.size() + 1);
+  if (h.size() == n) return;
+  c->lost[s] = 1;
+  bool ok = false;
+  try {
+    ok = commit_chunks(c, s, tokens, n);
+  } catch (const Error& e) {
+    if (e.status != NC_E_NOMEM) throw;
+    known_release(c);
+    c->fallbacks.memory += 1;
   }
-  if (ngram_on(c))
-    launch_ngram_predict(c->vp, c->S, c->steprows.p, 1, c->ngp.p, nullptr, nullptr, c->st);
+  if (ok) {
+    h.insert(h.end(), tokens + h.size(), tokens + n);
+    c->appended[s] = int(n) + 1;
+    if (ngram_on(c))
+      launch_ngram_predict(c->vp, c->S, c->steprows.p, 1, c->ngp.p, nullptr, nullptr, c->st);
+  } else {
+    reset_stream(c, s);
+    commit_steps(c, s, tokens, n);
+  }
+  c->lost[s] = 0;
 }
 
 void check_config(const nc_config* cfg) {
@@ -1673,6 +1710,7 @@ nc_status nc_probs_for_context(nc_ctx* c, uint32_t s, const int32_t* tokens, siz
     NC_HIP(hipSetDevice(c->dev));
     NC_CHECK(c->fp8_ready, NC_E_STATE, "FP8 context needs nc_calibrate_fp8 first");
     NC_CHECK(int(s) < c->n_streams, NC_E_STATE, "stream %u not reset (call nc_streams_reset)", s);
+    NC_CHECK(!c->lost[s], NC_E_STATE, "an earlier call on stream %u ended part way (reset it)", s);
     NC_CHECK(int(n) < c->maxT, NC_E_STATE, "history longer than the reset max_tokens");
     validate_tokens(c, tokens, n);
     auto& h = c->hhist[s];
@@ -1726,6 +1764,7 @@ nc_status nc_mix_update(nc_ctx* c, uint32_t s, int32_t token) {
     NC_CHECK(c, NC_E_INVALID, "NULL context");
     NC_HIP(hipSetDevice(c->dev));
     NC_CHECK(int(s) < c->n_streams, NC_E_STATE, "stream %u not reset", s);
+    NC_CHECK(!c->lost[s], NC_E_STATE, "an earlier call on stream %u ended part way (reset it)", s);
     validate_tokens(c, &token, 1);
     auto& h = c->hhist[s];
     const size_t j = h.size();
@@ -1942,6 +1981,15 @@ nc_status nc_chunk_polls(nc_ctx* c, uint32_t max_polls) {
   return guard([&] {
     NC_CHECK(c, NC_E_INVALID, "NULL context");
     c->polls = int(std::min<uint32_t>(max_polls, kChunkPolls));
+  });
+}
+
+nc_status nc_chunk_bytes(nc_ctx* c, uint64_t max_bytes) {
+  return guard([&] {
+    NC_CHECK(c, NC_E_INVALID, "NULL context");
+    NC_HIP(hipSetDevice(c->dev));
+    c->chunk_bytes = size_t(max_bytes);
+    if (known_bytes(c) > c->chunk_bytes) known_release(c);
   });
 }
 

@@ -1,4 +1,5 @@
-"""Device memory that runs out: the call reports it, and the context can be used again."""
+"""Device memory that runs out: the call reports it, and the context can be used again; or the call
+does without."""
 import dataclasses
 
 import numpy as np
@@ -34,3 +35,32 @@ def test_a_reset_that_does_not_fit():
     assert np.array_equal(ctx.probs_for_context(0, toks[:40]), p)
     assert ctx.encode_stream([toks]) == ref
     assert np.array_equal(ctx.decode_stream(ref[0], [150])[0], toks)
+
+
+def test_a_prompt_whose_second_chunk_does_not_fit():
+    """Chunks of 32 positions, whose buffers (2.1 MB of logits and n-gram distributions and 0.1 MB
+    beside them a set) are limited to one set: the first chunk's tokens are in the models when the
+    second finds no room.  The prompt's results are those of the same tokens one by one, and so are
+    those of the tokens after it, of a prompt of one chunk and of one without any buffer."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import paper_2602_19626_amd as nc
+    shape = dataclasses.replace(T, vocab=8200)
+    ctx = nc.Context(nc.make_config(shape, warmup=20, max_streams=2),
+                     synth.flat_weights(shape, synth.make_weights(shape, 5)))
+    toks = synth.make_stream(150, shape.vocab, seed=3, span=(4, 32))
+    ctx.chunk_bytes(3_000_000)
+    ctx.reset(2, 200)
+    done = 0
+    for cut, memory in ((20, 0), (100, 1), (101, 1), (125, 1), (150, 2), (150, 2)):
+        if cut == 150:
+            ctx.chunk_bytes(1000)
+        got, g = ctx.probs_for_context(0, toks[:cut], probe=True)
+        for t in toks[done:cut]:
+            ctx.mix_update(1, t)
+        done = cut
+        ref, r = ctx.probs_for_context(1, toks[:cut], probe=True)
+        assert np.array_equal(got, ref), cut
+        for k in ("mode", "mix_w", "entropy_bits", "pmax"):
+            assert g[k] == r[k], (cut, k)
+        assert ctx.fallbacks() == {"invalid": 0, "expired": 0, "memory": memory}, cut
