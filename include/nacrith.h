@@ -227,7 +227,8 @@ nc_status nc_get_fallbacks(const nc_ctx* ctx, nc_fallbacks* out);
 nc_status nc_chunk_polls(nc_ctx* ctx, uint32_t max_polls);
 /* Most device memory, in bytes, that the chunks' buffers may take (default: no limit).  They grow to
  * the largest call so far and are kept for the next, until nc_destroy or a limit below what they hold:
- * two sets of logits and n-gram distributions, of up to slide x vocab floats each for prompts. */
+ * two sets of logits and n-gram distributions, of up to slide x vocab floats each for prompts and
+ * 2,048 x vocab for encode (1.6 GB at vocab = 49,152, 8.6 GB at 262,144). */
 nc_status nc_chunk_bytes(nc_ctx* ctx, uint64_t max_bytes);
 
 /* ---- measurement ----------------------------------------------------------------------------

@@ -1827,7 +1827,17 @@ nc_status nc_encode_stream(nc_ctx* c, uint32_t ns, const int32_t* const* tokens,
           NC_HIP(hipMemcpyAsync(c->hist.p + (size_t)k * c->T_alloc, tok[k], len[k] * 4,
                                 hipMemcpyHostToDevice, c->st));
       sync(c);
-      if (known ? encode_known(c, tok, len) : (encode_steps(c, tok, len), true)) break;
+      if (!known) {
+        encode_steps(c, tok, len);
+        break;
+      }
+      try {
+        if (encode_known(c, tok, len)) break;
+      } catch (const Error& e) {
+        if (e.status != NC_E_NOMEM) throw;
+        known_release(c);  // step by step, the logits of 2,048 rows are all it takes
+        c->fallbacks.memory += 1;
+      }
     }
     // host coder, one thread per stream
     std::vector<size_t> rank(n);

@@ -64,3 +64,25 @@ def test_a_prompt_whose_second_chunk_does_not_fit():
         for k in ("mode", "mix_w", "entropy_bits", "pmax"):
             assert g[k] == r[k], (cut, k)
         assert ctx.fallbacks() == {"invalid": 0, "expired": 0, "memory": memory}, cut
+
+
+@pytest.mark.parametrize("limit", [0, 1_000_000, 8_000_000])
+def test_encode_whose_chunks_do_not_fit(limit):
+    """No room for a chunk, none for its n-gram side, none for the second set (three streams of 150
+    tokens take 6.6 MB a set): the same bytes, which decode, and chunks again once there is room."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import paper_2602_19626_amd as nc
+    shape = dataclasses.replace(T, vocab=8200)
+    ctx = nc.Context(nc.make_config(shape, warmup=20, max_streams=3),
+                     synth.flat_weights(shape, synth.make_weights(shape, 5)))
+    toks = [synth.make_stream(n, shape.vocab, seed=n, span=(4, 32)) for n in (150, 33, 70)]
+    ref = ctx.encode_stream(toks)
+    ctx.chunk_bytes(limit)
+    assert ctx.encode_stream(toks) == ref
+    assert ctx.fallbacks() == {"invalid": 0, "expired": 0, "memory": 1}
+    back = ctx.decode_stream(ref[0], [150, 33, 70])
+    assert all(np.array_equal(a, b) for a, b in zip(back, toks))
+    ctx.chunk_bytes(1 << 40)
+    assert ctx.encode_stream(toks) == ref
+    assert ctx.fallbacks()["memory"] == 1
