@@ -1,5 +1,6 @@
 // CDF-24 quantise + scan over batches of probability rows (paper section 3.4) and the interval
 // lookup used by the arithmetic coder (section 3.9).
+#include <algorithm>
 #include <mutex>
 #include <unordered_map>
 
@@ -99,9 +100,10 @@ __global__ __launch_bounds__(kSegThreads) void cdf24_scan_kernel(
 // stores the row's alignment allows.  The kernel holds no row in registers: its 48 KiB of LDS and
 // few registers let three rows overlap on a CU, so one row's loads, another's scan and a third's
 // stores keep the memory busy.  Every result is an integer or a comparison, so it equals the
-// two-kernel result.  It is never the faster one (V = 49,152: 27 us against 17 us for the segment
-// kernels at 128 rows, 100 at 1,024 and 386 against 376 at 4,096), so only calls that must not use
-// a workspace run it.
+// two-kernel result.  It is never the faster one (us a call, against the segment kernels': V = 49,152,
+// 128 / 1,024 / 4,096 rows 31 / 101 / 383 against 15 / 101 / 376; V = 4,096 14 / 32 / 94 against
+// 10 / 12 / 38; V = 64, 1,024 / 65,000 rows 28 / 1,330 against 10 / 211), so only calls that must not
+// use a workspace run it.
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 constexpr int kRowThreads = 512;
@@ -286,11 +288,17 @@ void launch_quantize_cdf(const float* p, uint32_t rows, uint32_t V, uint32_t tot
   }
   const uint32_t nseg = uint32_t(ceil_div(V, kSeg));
   SegPartial* parts = static_cast<SegPartial*>(workspace);
-  const dim3 grid(nseg, rows);
-  hipLaunchKernelGGL(cdf24_reduce_kernel, grid, dim3(kSegThreads), 0, s, p, V, total, nseg, parts);
-  hipLaunchKernelGGL(cdf24_scan_kernel, grid, dim3(kSegThreads), 0, s, p, V, total, nseg, parts,
-                     cdf, status);
-  NC_HIP(hipGetLastError());
+  // (a grid holds 65,535 rows in its second dimension)
+  constexpr uint32_t kGridRows = 65535;
+  for (uint32_t r0 = 0; r0 < rows; r0 += kGridRows) {
+    const dim3 grid(nseg, std::min(rows - r0, kGridRows));
+    const float* pr = p + size_t(r0) * V;
+    SegPartial* prt = parts + size_t(r0) * nseg;
+    hipLaunchKernelGGL(cdf24_reduce_kernel, grid, dim3(kSegThreads), 0, s, pr, V, total, nseg, prt);
+    hipLaunchKernelGGL(cdf24_scan_kernel, grid, dim3(kSegThreads), 0, s, pr, V, total, nseg, prt,
+                       cdf + size_t(r0) * (size_t(V) + 1), status ? status + r0 : nullptr);
+    NC_HIP(hipGetLastError());
+  }
 }
 
 // Scratch of the no-allocation variant: the segment partials of up to kScratchParts segments

@@ -209,3 +209,17 @@ def test_rows_that_start_on_any_word(nc, rows, v):
     got = cdf.cpu().numpy().view(np.uint32).astype(np.int64)
     for r in range(0, rows, max(1, rows // 7)):
         assert np.array_equal(got[r], quantize_cdf(p[r])), r
+
+
+@pytest.mark.parametrize("rows,v", [(65535, 64), (65536, 5), (70_000, 64), (140_001, 8)])
+def test_more_rows_than_a_grid_dimension_holds(nc, rows, v):
+    """Rows on both sides of 65,535 and 131,070 are bit-exact with the oracle, and every row's CDF
+    runs from 0 to the total."""
+    p = np.random.default_rng(v).dirichlet(np.full(v, 0.3), size=rows).astype(np.float32)
+    cdf, st = nc.quantize_cdf24(torch.from_numpy(p).cuda())
+    got = cdf.cpu().numpy().view(np.uint32).astype(np.int64)
+    assert not st.any()
+    assert np.all(got[:, 0] == 0) and np.all(got[:, -1] == 1 << 24) and np.all(np.diff(got) > 0)
+    for r in sorted({0, 1, rows // 2, 65533, 65534, 65535, 65536, 131069, 131070, rows - 1}):
+        if r < rows:
+            assert np.array_equal(got[r], quantize_cdf(p[r])), r
