@@ -33,7 +33,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {  // round to nearest even (f
   u += 0x7FFFu + ((u >> 16) & 1u);
   return uint16_t(u >> 16);
 }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
 // float -> OCP fp8 e4m3 (bias 7, max 448, no infinity), round to nearest even, saturating.
 __device__ __forceinline__ uint8_t f2fp8(float f) {
@@ -58,40 +57,20 @@ struct PT;
 template <>
 struct PT<P_F32> {
   static constexpr int ES = 4;
-  __device__ static void put4(uint8_t* dst, const float (&v)[4], float) {
-    *reinterpret_cast<v4f*>(dst) = v4f{v[0], v[1], v[2], v[3]};
-  }
   __device__ static void store(void* base, long long i, float v, float) {
     static_cast<float*>(base)[i] = v;
-  }
-  __device__ static float load(const void* base, long long i) {
-    return static_cast<const float*>(base)[i];
   }
 };
 template <>
 struct PT<P_BF16> {
   static constexpr int ES = 2;
-  __device__ static void put4(uint8_t* dst, const float (&v)[4], float) {
-    uint2 w;
-    w.x = uint32_t(f2bf(v[0])) | (uint32_t(f2bf(v[1])) << 16);
-    w.y = uint32_t(f2bf(v[2])) | (uint32_t(f2bf(v[3])) << 16);
-    *reinterpret_cast<uint2*>(dst) = w;
-  }
   __device__ static void store(void* base, long long i, float v, float) {
     static_cast<uint16_t*>(base)[i] = f2bf(v);
-  }
-  __device__ static float load(const void* base, long long i) {
-    return bf2f(static_cast<const uint16_t*>(base)[i]);
   }
 };
 template <>
 struct PT<P_FP8> {
   static constexpr int ES = 1;
-  __device__ static void put4(uint8_t* dst, const float (&v)[4], float inv_scale) {
-    *reinterpret_cast<uint32_t*>(dst) =
-        uint32_t(f2fp8(v[0] * inv_scale)) | (uint32_t(f2fp8(v[1] * inv_scale)) << 8) |
-        (uint32_t(f2fp8(v[2] * inv_scale)) << 16) | (uint32_t(f2fp8(v[3] * inv_scale)) << 24);
-  }
   __device__ static void store(void* base, long long i, float v, float inv_scale) {
     static_cast<uint8_t*>(base)[i] = f2fp8(v * inv_scale);
   }
@@ -285,10 +264,6 @@ struct Frag<P_F32> {
       for (int e = 0; e < 4; ++e) f[4 * q + e] = v[e];
     }
   }
-  __device__ static void zero(T& f) {
-#pragma unroll
-    for (int t = 0; t < 16; ++t) f[t] = 0.f;
-  }
   // straight from a global row: entries k0 + 16 g + 0..15, zero at or beyond K.  The load itself is
   // unconditional (its offset clamped into the row), so that no branch separates it from the loads
   // issued around it
@@ -317,7 +292,6 @@ struct Frag<P_BF16> {
 #pragma unroll
     for (int t = 0; t < 2; ++t) f[t] = *reinterpret_cast<const v4i*>(row + (32 * t + 8 * g) * 2);
   }
-  __device__ static void zero(T& f) { f[0] = f[1] = v4i{0, 0, 0, 0}; }
   __device__ static void load_clamped(T& f, const uint8_t* row, int k0, int K, int g) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -343,7 +317,6 @@ struct Frag<P_FP8> {
 #pragma unroll
     for (int t = 0; t < 2; ++t) f[t] = *reinterpret_cast<const long*>(row + 32 * t + 8 * g);
   }
-  __device__ static void zero(T& f) { f[0] = f[1] = 0; }
   __device__ static void load_clamped(T& f, const uint8_t* row, int k0, int K, int g) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -367,7 +340,7 @@ struct Frag<P_FP8> {
 // next normed GEMM's operand quantise(xn * y_gain[n]).  Every lane of the wave must call this;
 // lanes with ok == false pass xn = 0 and store nothing.  Returns |xn * y_gain[n]|.
 template <int P>
-__device__ __forceinline__ float resid_out_g(const GemmArgs& a, int m, int n, float xn, int c,
+__device__ __forceinline__ float resid_out(const GemmArgs& a, int m, int n, float xn, int c,
                                              bool ok, float gain) {
   const float sq = block_ssq16(xn);
   if (!ok) return 0.f;
@@ -377,18 +350,6 @@ __device__ __forceinline__ float resid_out_g(const GemmArgs& a, int m, int n, fl
   PT<P>::store(a.y_out, (long long)m * a.N + n, yv, a.y_inv_scale);
   return fabsf(yv);
 }
-template <int P>
-__device__ __forceinline__ float resid_out(const GemmArgs& a, int m, int n, float xn, int c,
-                                           bool ok) {
-  const float sq = block_ssq16(xn);
-  if (!ok) return 0.f;
-  if (a.ssq_out && c == 0) a.ssq_out[(long long)m * (a.N / 16) + n / 16] = sq;
-  if (!a.y_out) return 0.f;
-  const float yv = xn * a.y_gain[n];
-  PT<P>::store(a.y_out, (long long)m * a.N + n, yv, a.y_inv_scale);
-  return fabsf(yv);
-}
-
 __device__ __forceinline__ void amax_flush(float* dst, float v, int lane) {
   if (!dst) return;
   v = wave_max_f(v);
@@ -660,7 +621,7 @@ __global__ __launch_bounds__(64 * WVM * WVN, 2) void gemm_tile_kernel(
             xn = xo[i][j][e] + val(i, j, e);
             a.out_f32[(long long)m * a.ldo + n] = xn;
           }
-          ymax = fmaxf(ymax, resid_out_g<P>(a, m, n, xn, fr, ok, gn[j]));
+          ymax = fmaxf(ymax, resid_out<P>(a, m, n, xn, fr, ok, gn[j]));
         }
       }
     amax_flush(a.y_amax, ymax, lane);
@@ -1016,7 +977,7 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) void gemm_split_kernel(const Gemm
         *o = xn;
       }
       const float g = t0 == 0 ? pre_g : (ok && a.y_out ? a.y_gain[n] : 0.f);
-      ymax = fmaxf(ymax, resid_out_g<P>(a, r0 + m, n, xn, c, ok, g));
+      ymax = fmaxf(ymax, resid_out<P>(a, r0 + m, n, xn, c, ok, g));
     }
     amax_flush(a.y_amax, ymax, lane);
   } else if constexpr (EPI == E_STORE) {

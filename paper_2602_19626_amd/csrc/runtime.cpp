@@ -108,8 +108,6 @@ struct nc_ctx {
   DevBuf<float> x;
   DevBuf<uint8_t> qb, ob, hb;
   DevBuf<RowMeta> rowsd;
-  DevBuf<AttnItem> itemsd;
-  DevBuf<int32_t> lastrow;  // per stream: row of its last position in the latest pass
   DevBuf<float> xinv;       // inverse RMS of each pass row's residual
   DevBuf<float> aws;        // attention group states (decode path)
   DevBuf<float> xss;        // block sums of squares of each pass row's residual [rows][d/16]
@@ -151,7 +149,7 @@ struct nc_ctx {
     size_t bytes = 0;
     hipEvent_t up = nullptr, rows = nullptr, done = nullptr;
   } slots[2];
-  DevBuf<int32_t> steprows, arows;
+  DevBuf<int32_t> steprows;
   DevBuf<uint32_t> targets;
   DevBuf<LsePart> lsep;
   DevBuf<SegPartial> segp;
@@ -220,7 +218,7 @@ nc_ctx::~nc_ctx() {
                          &dbgp, &dbgpt};
   for (auto* q : fb) q->release();
   DevBuf<int32_t>* ib[] = {&uni, &nseen, &hist, &ncommit, &moded, &next_ctx, &keys, &kidx,
-                           &pool, &pool_n, &pool_sum, &nctx, &lastrow, &steprows, &arows};
+                           &pool, &pool_n, &pool_sum, &nctx, &steprows};
   for (auto* q : ib) q->release();
   kc.release();
   vc.release();
@@ -231,7 +229,6 @@ nc_ctx::~nc_ctx() {
   targets.release();
   dbgcdf.release();
   rowsd.release();
-  itemsd.release();
   lsep.release();
   segp.release();
   ngp.release();
@@ -441,7 +438,6 @@ void ensure_rows(nc_ctx* c, int rows) {
   c->ob.alloc((size_t)r * c->hq * c->hd * 4);
   c->hb.alloc((size_t)r * c->F * 4);
   c->rowsd.alloc(r);
-  c->itemsd.alloc((size_t)r * c->hk + 64);
   c->rows_alloc = r;
 }
 
@@ -449,7 +445,6 @@ void ensure_step(nc_ctx* c, int B) {
   const int nseg = int(ceil_div(c->V, kSeg));
   c->z.alloc((size_t)B * c->V);
   c->steprows.alloc(B);
-  c->arows.alloc(B);
   c->targets.alloc(B);
   c->lsep.alloc((size_t)B * nseg);
   c->segp.alloc((size_t)B * nseg);
