@@ -188,13 +188,13 @@ struct nc_ctx {
   // captured transformer passes of the decode / probe paths, by pass shape; every buffer a pass
   // reads or writes is part of the key, so a reallocation selects (and captures) a new graph
   struct GraphKey {
-    int n, n_items, n_groups, quads, n_last;
+    int n, n_items, n_groups, quads, n_last, S_alloc;  // (S_alloc: the caches' layer stride)
     size_t off_rows, off_items, off_last;
-    std::array<const void*, 12> bufs;
+    std::array<const void*, 14> bufs;
     bool operator<(const GraphKey& o) const {
-      return std::tie(n, n_items, n_groups, quads, n_last, off_rows, off_items, off_last, bufs) <
-             std::tie(o.n, o.n_items, o.n_groups, o.quads, o.n_last, o.off_rows, o.off_items,
-                      o.off_last, o.bufs);
+      return std::tie(n, n_items, n_groups, quads, n_last, S_alloc, off_rows, off_items, off_last,
+                      bufs) < std::tie(o.n, o.n_items, o.n_groups, o.quads, o.n_last, o.S_alloc,
+                                       o.off_rows, o.off_items, o.off_last, o.bufs);
     }
   };
   std::map<GraphKey, hipGraphExec_t> graphs;
@@ -833,10 +833,10 @@ void run_pass(nc_ctx* c, const PassPlan& p, const uint8_t* dstage, BodyOpts o = 
     pass_launches(c, p, dstage, o);
     return;
   }
-  nc_ctx::GraphKey k{n,          int(p.items.size()), p.n_groups, p.quads, int(p.last.size()),
+  nc_ctx::GraphKey k{n,          int(p.items.size()), p.n_groups, p.quads, int(p.last.size()), c->S_alloc,
                      p.off_rows, p.off_items,         p.off_last,
                      {dstage, c->x.p, c->xinv.p, c->xss.p, c->yb.p, c->qb.p, c->ob.p, c->hb.p,
-                      c->aws.p, c->kc.p, c->hlast.p, c->hinv.p}};
+                      c->aws.p, c->kc.p, c->vc.p, c->rope.p, c->hlast.p, c->hinv.p}};
   auto it = c->graphs.find(k);
   if (it == c->graphs.end()) {
     if (c->graphs.size() >= kMaxGraphs) graphs_clear(c);

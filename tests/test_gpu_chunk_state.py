@@ -45,6 +45,22 @@ def test_captured_chains_follow_their_buffers():
     assert all(np.array_equal(a, b) for a, b in zip(back, wider))
 
 
+def test_captured_decode_passes_follow_their_buffers():
+    """Decode passes are captured with the addresses and the layer stride of the caches, which move when
+    a later call has more streams or longer ones: the tokens stay those of direct launches."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    sets = [_streams(lens) for lens in ([40], [40, 25], [90], [40] * 7, [300, 40], [40], [40, 25])]
+    ref = _ctx(max_streams=7, warmup=20)
+    ctx = _ctx(max_streams=7, warmup=20, decode_graphs=True)
+    for toks in sets:
+        data, _ = ref.encode_stream(toks)
+        for _ in range(2):
+            back = ctx.decode_stream(data, [len(t) for t in toks])
+            assert all(np.array_equal(a, b) for a, b in zip(back, toks))
+    assert ctx.stats()["graph_replays"] > 0
+
+
 NONE = {"invalid": 0, "expired": 0}
 
 
