@@ -1,7 +1,8 @@
 // Device building blocks of the CDF-24 quantiser (paper section 3.4).
 //
 // Counts: c_i = max(1, floor(p_i * (T - V))) where the floor is that of the exact product (never
-// of a rounded one, see floor_count); the residual T - sum(c), which may be negative, goes to the lowest index among the maximal p_i;
+// of a rounded one, see floor_count); the residual T - sum(c), which may be negative, goes to the
+// lowest index among the maximal p_i;
 // cdf[i + 1] = c_0 + ... + c_i.
 //
 // Work split: a row of V entries is cut into segments of kSeg = 4096 entries, one 256-thread

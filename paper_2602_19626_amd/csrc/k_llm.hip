@@ -2129,6 +2129,11 @@ static void attn_go(const AttnArgs& a, bool parallel, hipStream_t s) {
   // stream after 1,200 tokens: 18 items 13.7 and 14.7, 27 items 15.1 and 14.3).  FP32 chunk by chunk is
   // the shorter chain for few items also where one quad is the whole window (one row after 200 tokens:
   // 11.1 us, and 12.5 an item a workgroup).
+  // From 1,024 items on (not parallel) a workgroup takes a group over its whole window whatever the
+  // group's size: where groups are one item (decode of over 340 streams, three kv heads) three of its
+  // waves only stage, but the chip is full.  Against four items a workgroup, each wave reading keys
+  // for itself, on average over a decode of 250 tokens: BF16 400 / 1,000 streams 18.2 / 36.2 us and
+  // 20.6 / 35.5, FP32 36.1 / 77.0 and 41.9 / 70.5; 700 tokens, 400 streams, 33.2 and 39.9, 67.2 and 80.5.
   const bool grouped = a.n_items > kChunkItems && a.n_items >= 2 * a.n_groups;
   if (parallel) {
     const int nq = std::min(a.quads, attention_quads(a.ctx_len));
@@ -2165,8 +2170,8 @@ size_t attention_ws_bytes(int n_items) {
   return std::max(quads, chunks) * sizeof(float);
 }
 
-// parallel: a workgroup per (item, quad of chunks) and a fold kernel (few items, decode);
-// otherwise one wave per item (prefill).  Both produce the same bits.
+// parallel: the work of an item or group is spread over workgroups, with a fold kernel (few items);
+// otherwise a workgroup per group of items (prefill).  Both produce the same bits.
 void launch_attention(int prec_att, int prec_out, const AttnArgs& a, bool parallel,
                       hipStream_t s) {
   if (a.n_items <= 0) return;

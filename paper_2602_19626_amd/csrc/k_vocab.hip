@@ -931,8 +931,11 @@ __global__ __launch_bounds__(kSegThreads) void ngram_fix_kernel(VocabParams P, S
 //   known_dense,    the n-gram distribution, entropy and mode of every position of the chunk at
 //   known_fix       once;
 //   known_commit    unigram counts;
-//   known_step      one launch per position: probabilities, count partials, the bias step and the
-//                   logsumexp partials of the next position, whose bias is then known;
+//   known_first     the logsumexp partials of the chunk's first position;
+//   known_run,      up to kRunGroups workgroups: probabilities and the bias step of all positions in
+//   known_count     one launch, then every position's count partials;
+//   known_step      more workgroups, one launch per position: probabilities, count partials, the bias
+//                   step and the logsumexp partials of the next position, whose bias is then known;
 //   known_finish    the intervals of every position from the count partials.
 // Every value is computed by the expressions, and reduced in the order, of the step-by-step
 // kernels above, so the coded bits are those of the sequential decode.

@@ -56,11 +56,11 @@ struct GemmArgs {
   int Hq, Hk, hd, ring;
 };
 
+constexpr int kAttnChunk = 64;  // keys of an attention chunk
+
 // Attention work item: a block of up to 16 (query, head) columns of one stream and kv head.
 // Column c maps to global column cc = c0 + c, query row row_base + cc / g and head
 // kvh * g + cc % g, with g = Hq / Hkv.
-constexpr int kAttnChunk = 64;  // keys of an attention chunk
-
 struct AttnItem {
   int32_t stream;
   int32_t kvh;

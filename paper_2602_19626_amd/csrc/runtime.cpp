@@ -469,8 +469,8 @@ struct BodyOpts {
   bool graph = false;  // replay a captured graph of the pass (decode and probe paths)
 };
 
-// Attention of a pass with fewer items runs the parallel quad + fold pair (decode), otherwise one
-// wave per item (prefill); both give the same bits.
+// Attention of a pass with fewer items spreads an item's window over workgroups and folds (decode,
+// short prompts), otherwise a workgroup takes a group of items (prefill); both give the same bits.
 constexpr size_t kAttnParallelItems = 1024;
 // Captured pass shapes kept per context (each a HIP graph of ~180 kernel nodes).
 constexpr size_t kMaxGraphs = 512;
