@@ -731,8 +731,11 @@ void pass_launches(nc_ctx* c, const PassPlan& p, const uint8_t* dstage, BodyOpts
   const AttnItem* ditems = reinterpret_cast<const AttnItem*>(dstage + p.off_items);
   const int prec = o.calib ? P_F32 : c->prec;
   const int att = o.calib ? P_F32 : c->att;
-  launch_embed(c->E32, drows, n, c->d, c->x.p, c->xss.p, c->yb.p, c->layers[0].g_attn, prec,
-               op_inv_scale(prec, c->layers[0].sa_qkv), o.calib ? c->amax.p : nullptr, c->st);
+  // the first normed GEMM: layer 0's QKV, or (no layers) the output layer
+  launch_embed(c->E32, drows, n, c->d, c->x.p, c->xss.p, c->yb.p,
+               c->nl ? c->layers[0].g_attn : c->g_final, prec,
+               op_inv_scale(prec, c->nl ? c->layers[0].sa_qkv : c->sa_lm),
+               o.calib ? c->amax.p : nullptr, c->st);
   for (int l = 0; l < c->nl; ++l) {
     Layer& L = c->layers[l];
     float* am = o.calib ? c->amax.p + 4 * l : nullptr;
@@ -1005,8 +1008,8 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
   c->maxT = maxT;
   c->S = make_state(c);
   if (ngram_on(c)) NC_HIP(hipMemsetAsync(c->kidx.p, 0xFF, c->kidx.n * 4, c->st));
-  NC_HIP(hipMemsetAsync(c->kc.p, 0, c->kc.n, c->st));
-  NC_HIP(hipMemsetAsync(c->vc.p, 0, c->vc.n, c->st));
+  for (DevBuf<uint8_t>* q : {&c->kc, &c->vc})
+    if (q->n) NC_HIP(hipMemsetAsync(q->p, 0, q->n, c->st));
   NC_HIP(hipMemsetAsync(c->hlast.p, 0, c->hlast.n * 4, c->st));
   NC_HIP(hipMemsetAsync(c->hinv.p, 0, c->hinv.n * 4, c->st));
   launch_state_reset(c->vp, c->S, 0, c->S_alloc, c->cfg.mix_w_llm, c->st);
@@ -1642,8 +1645,8 @@ nc_status nc_calibrate_fp8(nc_ctx* c, const int32_t* tokens, size_t n) {
     const size_t kvb = (size_t)c->nl * c->S_alloc * c->kv_stride * 4;
     k32.alloc(kvb);
     v32.alloc(kvb);
-    NC_HIP(hipMemsetAsync(k32.p, 0, kvb, c->st));
-    NC_HIP(hipMemsetAsync(v32.p, 0, kvb, c->st));
+    for (DevBuf<uint8_t>* q : {&k32, &v32})
+      if (kvb) NC_HIP(hipMemsetAsync(q->p, 0, kvb, c->st));
     std::swap(c->kc, k32);
     std::swap(c->vc, v32);
     try {
@@ -2070,7 +2073,7 @@ nc_status nc_autotune(nc_ctx* c, uint32_t max_rows, uint32_t reps, nc_tile* out,
       static const int kAm[NC_G_COUNT] = {A_NORM, A_DIRECT, A_NORM, A_DIRECT, A_NORM};
       for (int b = 0; b < kRowBuckets; ++b) {
         const int lo = b ? kRowBucketHi[b - 1] + 1 : 1;
-        if (lo > top) {
+        if (lo > top || (g != NC_G_LMHEAD && c->nl == 0)) {
           c->tiles[g][b] = GemmTile{};
           continue;
         }
@@ -2139,6 +2142,8 @@ nc_status nc_tiles_set(nc_ctx* c, const nc_tile* t, uint32_t n) {
     for (uint32_t i = 0; i < n; ++i) {
       const nc_tile& e = t[i];
       NC_CHECK(e.gemm >= 0 && e.gemm < NC_G_COUNT, NC_E_INVALID, "entry %u: bad GEMM id", i);
+      NC_CHECK(c->nl > 0 || e.gemm == NC_G_LMHEAD, NC_E_INVALID,
+               "entry %u: a model without layers has the output layer only", i);
       NC_CHECK(e.max_rows >= 1, NC_E_INVALID, "entry %u: max_rows must be >= 1", i);
       NC_CHECK(e.kind >= T_AUTO && e.kind <= T_WIDE, NC_E_INVALID, "entry %u: bad kind", i);
       const GemmTile g{e.kind, e.mb, e.waves};

@@ -157,3 +157,38 @@ def test_mix_update_through_the_abi_reproduces_encode():
     with pytest.raises(nc.NacrithError) as e:
         ctx.probs_for_context(0, np.array([toks[0] + 1], np.int32))
     assert e.value.status == 6
+
+
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp8"])
+def test_a_model_without_layers(prec):
+    """n_layers = 0 (embedding, final norm and output layer): round trip, the oracle's distributions
+    (float32 against float64: 1e-5), the tuner, and launch shapes of GEMMs that it does not have."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import dataclasses
+
+    import paper_2602_19626_amd as nc
+    shape = dataclasses.replace(synth.TINY, n_layers=0)
+    w = synth.make_weights(shape, 2)
+    ctx = nc.Context(nc.make_config(shape, ngram_order=3, precision=prec, skip="none",
+                                    mix_init="uniform", warmup=20, max_streams=2),
+                     synth.flat_weights(shape, w))
+    toks = [synth.make_stream(n, shape.vocab, seed=n, span=(4, 32)) for n in (90, 40)]
+    if prec == "fp8":
+        ctx.calibrate_fp8(toks[0])
+    data, _ = ctx.encode_stream(toks)
+    back = ctx.decode_stream(data, [90, 40])
+    assert all(np.array_equal(a, b) for a, b in zip(back, toks))
+    if prec == "fp32":
+        pos = [0, 1, 30, 89]
+        ref = op.encode(op.Settings(vocab=shape.vocab, ngram_order=3, mix_init="uniform", skip="none",
+                                    use_skip=False, warmup=20), shape, w, toks[0], record=pos, block=1)
+        ctx.reset(1, 100)
+        for i in pos:
+            p = ctx.probs_for_context(0, toks[0][:i])
+            assert np.max(np.abs(p - ref.records[i]["p"])) < 1e-5, i
+    assert {e["gemm"] for e in ctx.autotune(4, 1)} == {"lmhead"}
+    with pytest.raises(nc.NacrithError) as e:
+        ctx.tiles_set([{"gemm": "qkv", "max_rows": 1, "kind": "tile_small"}])
+    assert e.value.status == 1
+    assert ctx.encode_stream(toks)[0] == data
