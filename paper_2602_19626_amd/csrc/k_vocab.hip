@@ -1531,8 +1531,9 @@ __global__ __launch_bounds__(kSegThreads) void known_step_kernel(VocabParams P, 
 // A workgroup waits for those of its own row only, so all that a wait needs is that they get to run:
 // two workgroups fit a CU, and kRunGroups is half of what the chip holds, which leaves room for a second
 // context's.  If they still do not run (many contexts at once) a wait ends after C.polls polls, a
-// few tenths of a second, and raises its flag, with which the caller takes the positions one by one.  More rows than that gain less: 33 BF16 streams of 1,000 tokens (396
-// workgroups) 39.5 ms, or 36.8 in one launch; 64 streams 68.1 and 68.2, 200 streams 66.4 and 68.0.
+// few tenths of a second, and raises its flag, with which the caller takes the positions one by one.
+// More rows than that gain less: 33 BF16 streams of 1,000 tokens (396 workgroups) 39.5 ms, or 36.8 in
+// one launch; 64 streams 68.1 and 68.2, 200 streams 66.4 and 68.0.
 constexpr int kRunGroups = 256;
 
 __device__ __forceinline__ uint64_t sync_load(const uint64_t* p) {

@@ -998,13 +998,12 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
     c->vc.alloc(kvb);
     c->iv.alloc((size_t)Sa * Ta * 2);
     c->ptok.alloc((size_t)Sa * Ta);
+    build_rope(c, Ta + 2);
     c->S_alloc = Sa;
     c->T_alloc = Ta;
     c->S.cap = cap;
     c->S.maxctx = std::max(1, maxctx);
-    build_rope(c, Ta + 2);
   }
-  c->n_streams = n;
   c->maxT = maxT;
   c->S = make_state(c);
   if (ngram_on(c)) NC_HIP(hipMemsetAsync(c->kidx.p, 0xFF, c->kidx.n * 4, c->st));
@@ -1024,6 +1023,7 @@ void reset_streams(nc_ctx* c, int n, int maxT) {
   c->hhist.assign(n, {});
   c->appended.assign(n, 0);
   c->lost.assign(n, 0);
+  c->n_streams = n;
 }
 
 StepArgs step_args(nc_ctx* c, int B, bool decode) {
