@@ -1637,19 +1637,35 @@ nc_status nc_calibrate_fp8(nc_ctx* c, const int32_t* tokens, size_t n) {
     validate_tokens(c, tokens, n);
     reset_streams(c, 1, int(n) + 1);
     NC_HIP(hipMemsetAsync(c->amax.p, 0, c->amax.n * 4, c->st));
-    // FP32 passes over x_0..x_{n-1} (BOS, t_0, ..) recording every GEMM input's |max|
-    const auto att_save = c->att;
-    c->att = P_F32;
-    // the FP32 pass needs float32 KV caches: use a temporary allocation
-    DevBuf<uint8_t> k32, v32;
-    const size_t kvb = (size_t)c->nl * c->S_alloc * c->kv_stride * 4;
-    k32.alloc(kvb);
-    v32.alloc(kvb);
-    for (DevBuf<uint8_t>* q : {&k32, &v32})
-      if (kvb) NC_HIP(hipMemsetAsync(q->p, 0, kvb, c->st));
-    std::swap(c->kc, k32);
-    std::swap(c->vc, v32);
-    try {
+    // FP32 passes over x_0..x_{n-1} (BOS, t_0, ..) recording every GEMM input's |max|.  They need
+    // float32 KV caches: a temporary allocation takes the caches' place, and goes however this ends
+    {
+      struct Float32Caches {
+        nc_ctx* c;
+        int att = P_F32;
+        DevBuf<uint8_t> k, v;
+        DevBuf<float> z;  // logits of a pass
+        bool in = false;
+        void swap() {
+          std::swap(c->kc, k);
+          std::swap(c->vc, v);
+          std::swap(c->att, att);
+          in = !in;
+        }
+        ~Float32Caches() {
+          (void)hipStreamSynchronize(c->st);
+          if (in) swap();
+          k.release();
+          v.release();
+          z.release();
+        }
+      } f32{c};
+      const size_t kvb = (size_t)c->nl * c->S_alloc * c->kv_stride * 4;
+      f32.k.alloc(kvb);
+      f32.v.alloc(kvb);
+      for (DevBuf<uint8_t>* q : {&f32.k, &f32.v})
+        if (kvb) NC_HIP(hipMemsetAsync(q->p, 0, kvb, c->st));
+      f32.swap();
       const int C = c->cfg.slide;
       for (size_t a = 0; a < n; a += C) {
         std::vector<RowMeta> rows;
@@ -1665,26 +1681,12 @@ nc_status nc_calibrate_fp8(nc_ctx* c, const int32_t* tokens, size_t n) {
         const size_t off_ar = stg.put(idx.data(), idx.size() * 4);
         const uint8_t* d = upload_stage(c, stg);
         run_pass(c, p, d, o);
-        DevBuf<float> zt;
-        zt.alloc(p.rows.size() * (size_t)c->V);
+        f32.z.alloc(p.rows.size() * (size_t)c->V);
         run_lm_head(c, c->yb.p, c->xinv.p, reinterpret_cast<const int32_t*>(d + off_ar), int(p.rows.size()),
-                    zt.p, true);
+                    f32.z.p, true);
         sync(c);
-        zt.release();
       }
-    } catch (...) {
-      std::swap(c->kc, k32);
-      std::swap(c->vc, v32);
-      k32.release();
-      v32.release();
-      c->att = att_save;
-      throw;
     }
-    std::swap(c->kc, k32);
-    std::swap(c->vc, v32);
-    k32.release();
-    v32.release();
-    c->att = att_save;
     std::vector<float> am(c->amax.n);
     d2h(c, am.data(), c->amax.p, am.size());
     auto sc = [](float m) { return m > 0 ? m / 448.f : 1.f; };

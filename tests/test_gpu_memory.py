@@ -86,3 +86,24 @@ def test_encode_whose_chunks_do_not_fit(limit):
     ctx.chunk_bytes(1 << 40)
     assert ctx.encode_stream(toks) == ref
     assert ctx.fallbacks()["memory"] == 1
+
+
+def test_a_calibration_that_does_not_fit():
+    """Bfloat16 caches of 16,000 streams (2 x 84 GB) and then float32 ones beside them, which no card
+    holds: the calibration fails, and a context calibrated before codes as it did."""
+    if not gpu_available():
+        pytest.skip("no GPU")
+    import paper_2602_19626_amd as nc
+    shape = dataclasses.replace(T, head_dim=64, n_heads=8, n_kv_heads=8, ctx_len=2048, slide=512)
+    ctx = nc.Context(nc.make_config(shape, precision="fp8", use_ngram=False, skip="none",
+                                    use_mixer=False, max_streams=16_000),
+                     synth.flat_weights(shape, synth.make_weights(shape, 5)))
+    toks = synth.make_stream(150, shape.vocab, seed=1, span=(4, 32))
+    ctx.calibrate_fp8(toks)
+    ref = ctx.encode_stream([toks])
+    ctx.reset(16_000, 4)
+    with pytest.raises(nc.NacrithError) as e:
+        ctx.calibrate_fp8(toks[:100])
+    assert e.value.status == 3
+    assert ctx.encode_stream([toks]) == ref
+    assert np.array_equal(ctx.decode_stream(ref[0], [150])[0], toks)
